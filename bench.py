@@ -203,7 +203,7 @@ def bench_visibility(args, B, log):
         "data": "synthetic",
         "config": {"workload": VIS_WORKLOAD, "rays": rays, "tris": int(F.shape[0]), "views": n_views, "res": res},
         "stages_ms": stage_ms,
-        "roofline": {"kernel": "visibility_kernel (camera rays, first hit)", "bound": "alu", "achieved": achieved,
+        "roofline": {"kernel": "tile_rays_kernel (camera rays, first hit)", "bound": "alu", "achieved": achieved,
                      "peak": VALU_PEAK_TOPS, "unit": "TOP/s", "frac": achieved / VALU_PEAK_TOPS, "traffic": None,
                      "box_tests_per_ray": n_box / rays, "tri_tests_per_ray": n_tri / rays,
                      "lane_utilisation": (n_box / 2 + n_tri) / (64 * trips) if trips else None,
@@ -287,7 +287,7 @@ def bench_view_maps(args, B, log):
         "config": {"workload": MAP_WORKLOAD, "covered_texels": covered, "views": K, "depth_res": img,
                    "tris": int(F.shape[0])},
         "stages_ms": stage_ms,
-        "roofline": {"kernel": "visibility_kernel (depth rays, first hit)", "bound": "alu", "achieved": achieved,
+        "roofline": {"kernel": "tile_rays_kernel (depth rays, first hit)", "bound": "alu", "achieved": achieved,
                      "peak": VALU_PEAK_TOPS, "unit": "TOP/s", "frac": achieved / VALU_PEAK_TOPS, "traffic": None,
                      "box_tests_per_ray": n_box / rays_depth, "tri_tests_per_ray": n_tri / rays_depth,
                      "lane_utilisation": (n_box / 2 + n_tri) / (64 * trips) if trips else None,
