@@ -652,7 +652,7 @@ int32_t noalloc_scratch(void** out) {
 // the mesh as its high-poly and no low-poly (its BVH build is the bake's),
 // then the flood fill's arrays and the camera rays' spill columns.
 struct VisLayout {
-    size_t deg, off, cur, adj, vis, ext, front0, front1, scan_tmp, spill, total;
+    size_t deg, off, cur, adj, vis, met, parent, seen, scan_tmp, spill, total;
 };
 
 int32_t plan_visibility(int64_t nv, int64_t nf, Plan* P, VisLayout* V) {
@@ -675,9 +675,9 @@ int32_t plan_visibility(int64_t nv, int64_t nf, Plan* P, VisLayout* V) {
     V->cur = take(4 * (size_t)(nv + 1));
     V->adj = take(4 * (size_t)(3 * nf + 1));
     V->vis = take(4 * (size_t)(nf + 1));
-    V->ext = take(4 * (size_t)(nf + 1));
-    V->front0 = take(4 * (size_t)(nf + 1));
-    V->front1 = take(4 * (size_t)(nf + 1));
+    V->met = take(4 * (size_t)(nf + 1));
+    V->parent = take(4 * (size_t)(nf + 1));
+    V->seen = take(4 * (size_t)(nf + 1));
     V->scan_tmp = take(4 * (size_t)(scan_tmp_elems(nv + 1) + 1));
     V->spill = take(4 * (size_t)kMaxDepth * (size_t)kMaxLanes);
     V->total = off;
@@ -1018,9 +1018,9 @@ int32_t bake_visibility(const float* V, const int32_t* F, int64_t n_v, int64_t n
     fr.off = (uint32_t*)(ws + VL.off);
     fr.cur = (uint32_t*)(ws + VL.cur);
     fr.adj = (uint32_t*)(ws + VL.adj);
-    fr.ext = (uint32_t*)(ws + VL.ext);
-    fr.front0 = (uint32_t*)(ws + VL.front0);
-    fr.front1 = (uint32_t*)(ws + VL.front1);
+    fr.met = (uint32_t*)(ws + VL.met);
+    fr.parent = (uint32_t*)(ws + VL.parent);
+    fr.seen = (uint32_t*)(ws + VL.seen);
     fr.scan_tmp = (uint32_t*)(ws + VL.scan_tmp);
     fr.visible = vis;
     fr.visible_out = visible_out;

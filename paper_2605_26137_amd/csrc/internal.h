@@ -339,10 +339,13 @@ struct MapRun {
     float* inc_out;      // device [n_views][res^2], pre-filled with 0
 };
 hipError_t launch_view_maps(const BatchHost& H, const MapRun& m, hipStream_t s);
-// Vertex -> face lists and the normal-gated flood fill from `visible` into
-// `ext` (both [n_f] u32 flags), then both written out as bytes.
+// Vertex -> face lists and the normal-gated flood fill from `visible` ([n_f]
+// u32 flags); the visible and the exterior flags are written out as bytes.
 struct FillRun {
-    uint32_t *deg, *off, *cur, *adj, *ext, *front0, *front1, *scan_tmp;
+    uint32_t *deg, *off, *cur, *adj, *scan_tmp;
+    uint32_t *parent;  // union-find over the hidden faces
+    uint32_t *met;     // a hidden face agrees with a visible neighbour
+    uint32_t *seen;    // at a root: some face of the set does
     const uint32_t* visible;
     uint8_t *visible_out, *exterior_out;
 };
