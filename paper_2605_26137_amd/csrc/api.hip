@@ -1089,7 +1089,7 @@ int32_t bake_view_maps(const float* V, const int32_t* F, const float* UV, int64_
                             (int64_t)(L.table / 4)));
     forget_saved(workspace);
     HIP_OR_FAIL(launch_lo_prep(H, s));
-    HIP_OR_FAIL(launch_raster(H, s));
+    HIP_OR_FAIL(launch_raster(H, s, false));
     HIP_OR_FAIL(tim_record(tim, 1, s));
     HIP_OR_FAIL(launch_bvh_build(H, s));
     HIP_OR_FAIL(tim_record(tim, 2, s));
@@ -1108,9 +1108,6 @@ int32_t bake_view_maps(const float* V, const int32_t* F, const float* UV, int64_
     vr.count = (flags & BAKE_FLAG_COUNT) != 0;
     HIP_OR_FAIL(launch_visibility_rays(H, vr, s));
     HIP_OR_FAIL(tim_record(tim, 3, s));
-    const int64_t tex = (int64_t)res * res;
-    HIP_OR_FAIL(fill_u32((uint32_t*)uv_out, 0xBF800000u, 2 * (int64_t)n_views * tex, s));  // -1.0f
-    HIP_OR_FAIL(fill_u32((uint32_t*)inc_out, 0u, (int64_t)n_views * tex, s));
     MapRun mr{};
     mr.eyes = eyes;
     for (int k = 0; k < 3; ++k) mr.target[k] = target[k];

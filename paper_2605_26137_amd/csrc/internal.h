@@ -221,6 +221,44 @@ __device__ __forceinline__ int block_asset(const Batch& B, int g, int64_t blk, i
 
 __device__ __forceinline__ void set_status(const Batch& B, uint32_t bits) { atomicOr(B.status, bits); }
 
+// ---------------------------------------------------------------------------
+// Coverage of a texel centre, exact in integers (corners snapped to 1/256
+// texel)
+// ---------------------------------------------------------------------------
+
+constexpr uint32_t kNoFace = 0x7FFFFFFFu;  // face map entry of an uncovered texel
+
+// Edge functions of the edges opposite corners 0, 1, 2 at texel (i, j) and
+// their sum; true when the face covers the centre.
+__device__ __forceinline__ bool cover_at(const int32_t X[3], const int32_t Y[3], int32_t i, int32_t j, int64_t E[3],
+                                         int64_t* S) {
+    const int64_t cx = 256 * (int64_t)j + 128, cy = 256 * (int64_t)i + 128;
+    E[0] = (int64_t)(X[2] - X[1]) * (cy - Y[1]) - (int64_t)(Y[2] - Y[1]) * (cx - X[1]);
+    E[1] = (int64_t)(X[0] - X[2]) * (cy - Y[2]) - (int64_t)(Y[0] - Y[2]) * (cx - X[2]);
+    E[2] = (int64_t)(X[1] - X[0]) * (cy - Y[0]) - (int64_t)(Y[1] - Y[0]) * (cx - X[0]);
+    *S = E[0] + E[1] + E[2];
+    const bool in = (E[0] >= 0 && E[1] >= 0 && E[2] >= 0) || (E[0] <= 0 && E[1] <= 0 && E[2] <= 0);
+    return in && *S != 0;
+}
+
+// Barycentric weights of corners 1 and 2.
+__device__ __forceinline__ void bary_of(const int64_t E[3], int64_t S, float* b1, float* b2) {
+    const float fs = (float)S;
+    *b1 = (float)E[1] / fs;
+    *b2 = (float)E[2] / fs;
+}
+
+// The weights of texel (i, j) in a face that covers it (face_uv: the snapped
+// corners).
+__device__ __forceinline__ void texel_weights(const int4* __restrict__ face_uv, int64_t fg, int32_t i, int32_t j,
+                                              float* b1, float* b2) {
+    const int4 p = face_uv[2 * fg], q = face_uv[2 * fg + 1];
+    const int32_t X[3] = {p.x, p.z, q.x}, Y[3] = {p.y, p.w, q.y};
+    int64_t E[3], S;
+    cover_at(X, Y, i, j, E, &S);
+    bary_of(E, S, b1, b2);
+}
+
 // Host description of a batch: asset table, grid prefix tables and the
 // workspace layout.
 struct Layout {
@@ -306,7 +344,8 @@ hipError_t launch_sort(const BatchHost& H, int which, int bits, bool* result_in_
                        hipEvent_t after_first = nullptr);
 
 hipError_t launch_lo_prep(const BatchHost& H, hipStream_t s);
-hipError_t launch_raster(const BatchHost& H, hipStream_t s);
+// emit: also write the ray lists (without: their counts and starts only)
+hipError_t launch_raster(const BatchHost& H, hipStream_t s, bool emit = true);
 hipError_t launch_fill_uncovered(const BatchHost& H, hipStream_t s);
 hipError_t launch_bvh_build(const BatchHost& H, hipStream_t s);
 hipError_t launch_traverse(const BatchHost& H, const TravConfig& cfg, hipStream_t s);
@@ -326,8 +365,8 @@ struct VisRun {
 };
 hipError_t launch_visibility_rays(const BatchHost& H, const VisRun& v, hipStream_t s);
 // Backprojection precompute (Sec. 7.4, TextureGen Postprocessing) for asset
-// 0's covered texels (its ray list and low-poly normals) against the depth
-// buffers of the views.
+// 0's texels (its face map and low-poly normals) against the depth buffers of
+// the views.
 struct MapRun {
     const float* eyes;  // device [n_views][3]
     float target[3];
@@ -335,8 +374,8 @@ struct MapRun {
     int32_t n_views, img_res;
     const float* depth;  // device [n_views][img_res^2]: first-hit distances along the pixel rays
     float tol;
-    float* uv_out;       // device [n_views][res^2][2], pre-filled with -1
-    float* inc_out;      // device [n_views][res^2], pre-filled with 0
+    float* uv_out;       // device [n_views][res^2][2]
+    float* inc_out;      // device [n_views][res^2]
 };
 hipError_t launch_view_maps(const BatchHost& H, const MapRun& m, hipStream_t s);
 // Vertex -> face lists and the normal-gated flood fill from `visible` ([n_f]

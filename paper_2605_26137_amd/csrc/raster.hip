@@ -192,18 +192,9 @@ __device__ __forceinline__ FaceBox load_face_box(const int4* __restrict__ face_u
     return fb;
 }
 
-// Edge functions of the edges opposite corners 0, 1, 2 at texel (i, j).
-__device__ __forceinline__ bool cover(const FaceBox& fb, int32_t i, int32_t j, int64_t E[3],
-                                      int64_t* S) {
-    int64_t cx = 256 * (int64_t)j + 128, cy = 256 * (int64_t)i + 128;
-    const int32_t* X = fb.X;
-    const int32_t* Y = fb.Y;
-    E[0] = (int64_t)(X[2] - X[1]) * (cy - Y[1]) - (int64_t)(Y[2] - Y[1]) * (cx - X[1]);
-    E[1] = (int64_t)(X[0] - X[2]) * (cy - Y[2]) - (int64_t)(Y[0] - Y[2]) * (cx - X[2]);
-    E[2] = (int64_t)(X[1] - X[0]) * (cy - Y[0]) - (int64_t)(Y[1] - Y[0]) * (cx - X[0]);
-    *S = E[0] + E[1] + E[2];
-    bool in = (E[0] >= 0 && E[1] >= 0 && E[2] >= 0) || (E[0] <= 0 && E[1] <= 0 && E[2] <= 0);
-    return in && *S != 0;
+// Edge functions at texel (i, j); true when the face covers it.
+__device__ __forceinline__ bool cover(const FaceBox& fb, int32_t i, int32_t j, int64_t E[3], int64_t* S) {
+    return cover_at(fb.X, fb.Y, i, j, E, S);
 }
 
 constexpr int kRasterBlock = 256;
@@ -292,9 +283,7 @@ __global__ __launch_bounds__(kRasterBlock) void raster_emit_kernel(Batch Bt, con
             Ray ray;
             ray.texel = i * res + j;
             ray.face = (int32_t)f;
-            float fs = (float)S;
-            ray.b1 = (float)E[1] / fs;
-            ray.b2 = (float)E[2] / fs;
+            bary_of(E, S, &ray.b1, &ray.b2);
             rays[r] = ray;
         }
         run += (uint32_t)__popcll(m);
@@ -311,7 +300,7 @@ __global__ __launch_bounds__(256) void fill_uncovered_kernel(Batch Bt, const uin
     const AssetDev& As = Bt.A[block_asset(Bt, kGTex, blockIdx.x, &lb)];
     const int64_t t = lb * 256 + threadIdx.x;
     if (t >= (int64_t)As.res * As.res) return;
-    bool cov = facemap[As.tex + t] != 0x7FFFFFFFu;
+    bool cov = facemap[As.tex + t] != kNoFace;
     level[As.tex + t] = cov ? 0 : 255;
     if (!cov) {
         As.out_map[3 * t] = 0.f;
@@ -326,7 +315,7 @@ __global__ __launch_bounds__(256) void uncovered_kernel(Batch Bt, const uint32_t
     int64_t lb;
     const AssetDev& As = Bt.A[block_asset(Bt, kGTex, blockIdx.x, &lb)];
     const int64_t t = lb * 256 + threadIdx.x;
-    if (t >= (int64_t)As.res * As.res || facemap[As.tex + t] != 0x7FFFFFFFu) return;
+    if (t >= (int64_t)As.res * As.res || facemap[As.tex + t] != kNoFace) return;
     As.out_map[3 * t] = 0.f;
     As.out_map[3 * t + 1] = 0.f;
     As.out_map[3 * t + 2] = 1.f;
@@ -416,7 +405,7 @@ __global__ __launch_bounds__(kFinishBlock) void finish_kernel(Batch Bt, const ui
         const int32_t i = oi + r;
         const bool in = r < R && col_in && i >= 0 && i < res;
         t[u] = in ? i * res + j : -1;
-        cov[u] = in && facemap[t[u]] != 0x7FFFFFFFu;
+        cov[u] = in && facemap[t[u]] != kNoFace;
     }
     float m0[kRows], m1[kRows], m2[kRows];
 #pragma unroll
@@ -547,7 +536,7 @@ hipError_t launch_lo_prep(const BatchHost& H, hipStream_t s) {
     return hipSuccess;
 }
 
-hipError_t launch_raster(const BatchHost& H, hipStream_t s) {
+hipError_t launch_raster(const BatchHost& H, hipStream_t s, bool emit) {
     const Layout& L = H.L;
     char* ws = H.ws;
     uint32_t* facemap = (uint32_t*)(ws + L.facemap);
@@ -555,7 +544,7 @@ hipError_t launch_raster(const BatchHost& H, hipStream_t s) {
     uint32_t* off = (uint32_t*)(ws + L.face_off);
     const int4* fuv = (const int4*)(ws + L.face_uv);
     hipError_t e;
-    if ((e = fill_u32(facemap, 0x7FFFFFFFu, L.t_tex, s)) != hipSuccess) return e;
+    if ((e = fill_u32(facemap, kNoFace, L.t_tex, s)) != hipSuccess) return e;
     const unsigned g = (unsigned)H.blocks(kGLoFWave);
     if (g > 0) {
         hipLaunchKernelGGL(raster_claim_kernel, dim3(g), dim3(kRasterBlock), 0, s, H.dev, fuv, facemap);
@@ -568,7 +557,7 @@ hipError_t launch_raster(const BatchHost& H, hipStream_t s) {
         hipSuccess)
         return e;
     if ((e = launch_ray_spaces(H, s)) != hipSuccess) return e;
-    if (g > 0) {
+    if (g > 0 && emit) {
         hipLaunchKernelGGL(raster_emit_kernel, dim3(g), dim3(kRasterBlock), 0, s, H.dev, fuv,
                            (const uint32_t*)facemap, (const uint32_t*)off, (Ray*)(ws + L.rays));
     }
