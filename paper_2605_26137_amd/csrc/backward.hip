@@ -361,9 +361,14 @@ __device__ __forceinline__ float3 hiN_term(const uint32_t* __restrict__ vals, co
 // forms its pair's term, a segmented scan over the wave adds the terms of
 // each vertex's run (items ascending within a run: the sort is stable) in a
 // fixed tree order, and the lane at the run's end writes the sum.  A run
-// that goes on past the wave's 64 pairs is finished by that lane, adding the
-// rest in pair order; the waves holding the rest skip it.  Waves take
-// (asset, 64-ray batch) items: 192 pairs each.
+// that goes on past the wave's 64 pairs is finished by the whole wave, the
+// next 256 pairs at a time (each 64 summed in a fixed tree, the four sums
+// added in pair order); the waves holding the rest skip it.  Bound by the
+// latency of the gathered terms, so a long run (many texels per high-poly
+// vertex) must not be one lane's chain: walked by its last lane alone, ten
+// uneven assets with up to some hundred pairs a vertex took 1,136 us, this way
+// 251 us; 1.08M rays on 655k vertices 48 -> 45 us.  Waves take (asset,
+// 64-ray batch) items: 192 pairs each.
 __global__ __launch_bounds__(256) void bwd_hiN_kernel(Batch B, const uint32_t* __restrict__ keys,
                                                       const uint32_t* __restrict__ vals,
                                                       const HiTerm* __restrict__ ht) {
@@ -419,12 +424,37 @@ __global__ __launch_bounds__(256) void bwd_hiN_kernel(Batch B, const uint32_t* _
                 }
             }
             const bool run_end = lane == 63 || next != key;
-            if (!in || key >= nhv || !run_end) continue;
-            if (lane < first_change && cont_in) continue;  // an earlier wave's run
-            if (lane == 63) {
-                for (int64_t j = i0 + 64; j < hi && keys[j] == key; ++j) g = add3(g, hiN_term(vals, ht, j));
+            const bool mine = !(lane < first_change && cont_in);  // else an earlier wave's run
+            // the last lane's run past the wave's pairs (wave-uniform loop)
+            const uint32_t last = (uint32_t)__builtin_amdgcn_readlane((int)key, 63);
+            bool more = i0 + 64 < hi && last < nhv && !(first_change == 64 && cont_in);
+            for (int64_t j0 = i0 + 64; more && j0 < hi; j0 += 256) {
+                uint32_t kj[4];
+                float3 t[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int64_t j = j0 + 64 * u + lane;
+                    kj[u] = j < hi ? keys[j] : 0xFFFFFFFFu;
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u)  // sorted: once a pair differs, so does every later one
+                    t[u] = kj[u] == last ? hiN_term(vals, ht, j0 + 64 * u + lane) : f3(0.f, 0.f, 0.f);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const uint64_t same = __ballot(kj[u] == last);
+                    if (same == 0) {
+                        more = false;
+                        break;
+                    }
+                    const float3 sum = f3(wave_sum(t[u].x), wave_sum(t[u].y), wave_sum(t[u].z));
+                    if (lane == 63) g = add3(g, sum);
+                    if (same != ~0ull) {
+                        more = false;
+                        break;
+                    }
+                }
             }
-            st3(grad_hi_N, key, g);
+            if (in && key < nhv && run_end && mine) st3(grad_hi_N, key, g);
         }
     }
 }
