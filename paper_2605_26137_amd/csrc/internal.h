@@ -392,9 +392,9 @@ hipError_t launch_flood_fill(const BatchHost& H, const FillRun& f, hipStream_t s
 // Quadric edge-collapse simplification (Sec. 6.1): workspace carving and the
 // two blocking drivers (they synchronise `s` to read the per-round counts).
 struct QemLayout {
-    int64_t nv, nf, edge_cap;
-    size_t cnt, hist, P, Q, P2, Q2, F, F2, keep, koff, deg, off, cur, adj, ncnt, noff, hcnt, eoff, bnd, nbr, keep_ring, E, bits, faces,
-        pl, m, M, partner, wflag, part, scan_tmp;
+    int64_t nv, nf, edge_cap, arena;
+    size_t cnt, hist, P, Q, P2, Q2, F, F2, keep, koff, num, off, cur, adj, ring, info, hcnt, eoff, part, sup, E, bits, faces,
+        pl, m, list, scan_tmp;
     size_t total;
 };
 size_t qem_layout(int64_t nv, int64_t nf, QemLayout* L);
