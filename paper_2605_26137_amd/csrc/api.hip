@@ -122,6 +122,11 @@ int64_t grid_blocks(int g, const Sizes& z) {
         case kGTex3: return cdiv(3 * tex, 256);
         case kGBwdSort: return cdiv(3 * tex, kSortTile);
         case kGTile: return cdiv(z.res, kFinishTile) * cdiv(z.res, kFinishTile);
+        case kGBuild: return cdiv(z.nhf, kBuildTile);
+    }
+    if (g >= kGJoin1 && g < kGJoin1 + kJoinLevels) {
+        const int level = g - kGJoin1 + 1;
+        return join_groups(z.nhf, level - 1, nullptr) > 1 ? join_groups(z.nhf, level, nullptr) : 0;
     }
     return 0;
 }
@@ -178,7 +183,7 @@ int32_t make_plan(const Sizes* z, int n, uint32_t flags, Plan* P) {
         L.t_tex += tex;
         L.t_stile += cdiv(z[a].nhf, kSortTile);
         L.t_btile += cdiv(3 * tex, kSortTile);
-        L.t_tl += treelet_cap(z[a].nhf);
+        L.t_tl += cdiv(z[a].nhf, kBuildTile);
         max_hv = std::max(max_hv, z[a].nhv);
         for (int g = 0; g < kGridCount; ++g) {
             P->gpf[(size_t)g * (n + 1) + a] = (int32_t)gsum[g];
@@ -222,7 +227,6 @@ int32_t make_plan(const Sizes* z, int n, uint32_t flags, Plan* P) {
     L.grads = take(sizeof(AssetGrad) * (size_t)n);
     L.ray_pf = take(4 * (size_t)(n + 1));
     L.rb_pf = take(4 * (size_t)(n + 1));
-    L.tl_pf = take(4 * (size_t)(n + 1));
     L.bt_pf = take(4 * (size_t)(n + 1));
     L.lo_n = take(16 * (size_t)L.t_lv);
     L.lo_deg = take(4 * (size_t)L.t_lv);
@@ -245,16 +249,12 @@ int32_t make_plan(const Sizes* z, int n, uint32_t flags, Plan* P) {
     L.keys1 = take(4 * (size_t)L.t_hf);
     L.vals1 = take(4 * (size_t)L.t_hf);
     L.hist = take(4 * 256 * (size_t)L.t_stile);
-    L.nodes = take(64 * (size_t)L.t_node);
     L.nodes_c = take(32 * (size_t)L.t_node);
     L.leaves = take(48 * (size_t)L.t_hf);
-    L.node_parent = take(4 * (size_t)L.t_node);
-    L.leaf_parent = take(4 * (size_t)L.t_hf);
-    L.refit_cnt = take(4 * (size_t)L.t_node);
-    L.frontier = take(4 * (size_t)L.t_tl);
-    L.treelets = take(16 * (size_t)L.t_tl);
-    L.top = take(8 * (size_t)L.t_tl);
-    L.child = take(4 * (size_t)L.t_node);
+    int64_t rows = 0;
+    for (int level = 0; level <= kJoinLevels; ++level) rows += join_rows(L.t_tl, n, level);
+    L.items = take(32 * (size_t)kSpine * (size_t)rows);
+    L.item_cnt = take(4 * (size_t)rows);
     L.spill = take(4 * (size_t)kMaxDepth * (size_t)L.spill_lanes);
     if (L.save) {
         const size_t items = 3 * (size_t)L.t_tex;
@@ -327,7 +327,6 @@ BatchHost host_view(const Plan& P, char* ws) {
     H.dev.gpf = (const int32_t*)(ws + L.gpf);
     H.dev.ray_pf = (const uint32_t*)(ws + L.ray_pf);
     H.dev.rb_pf = (const uint32_t*)(ws + L.rb_pf);
-    H.dev.tl_pf = (const uint32_t*)(ws + L.tl_pf);
     H.dev.bt_pf = (const uint32_t*)(ws + L.bt_pf);
     H.dev.cnt = (uint32_t*)(ws + L.counters);
     H.dev.gcnt = (uint32_t*)(ws + L.gcnt);

@@ -30,17 +30,6 @@ struct Hit {
 };
 static_assert(sizeof(Hit) == 16, "Hit is 16 B");
 
-// Full-precision box slots of a binary node, by child side (build scratch:
-// the refit hands the boxes of the top levels over through these):
-//   a = (L.lo.x, L.lo.y, L.lo.z, L.hi.x)
-//   b = (L.hi.y, L.hi.z, R.lo.x, R.lo.y)
-//   c = (R.lo.z, R.hi.x, R.hi.y, R.hi.z)
-struct alignas(16) BvhNode {
-    float4 a, b, c;
-    int4 unused;
-};
-static_assert(sizeof(BvhNode) == 64, "BvhNode is 64 B");
-
 // Binary BVH node as the traversal reads it (32 B, two 16-B loads per
 // visit): the boxes of both children quantised to 8 bits per plane in a
 // frame of the node's own.
@@ -114,7 +103,7 @@ struct AssetDev {
     int64_t tex;    // texels
     int64_t stile;  // sort tiles of the BVH keys
     int64_t btile;  // sort tiles of the backward pairs (capacity 3 res^2)
-    int64_t tl;     // treelet and frontier slots
+    int64_t tl;     // tiles of the tree build
 };
 
 // Inputs and outputs of the backward pass, one per asset.
@@ -136,6 +125,11 @@ enum GridId : int {
     kGTex3,     // texel channels, 256 per block
     kGBwdSort,  // backward sort tiles (capacity 3 res^2, kSortTile per block)
     kGTile,     // kFinishTile^2 texel tiles of the fused uncovered fill + dilation
+    kGBuild,    // tiles of the tree build (kBuildTile leaves per block)
+    kGJoin1,    // groups of kJoin tiles, of kJoin groups, ... (none once the asset is one group)
+    kGJoin2,
+    kGJoin3,
+    kGJoin4,
     kGridCount
 };
 
@@ -149,22 +143,36 @@ __host__ __device__ inline int64_t sort_super_rows(int64_t tiles, int64_t n) { r
 constexpr int kFinishTile = 56;  // texel tile side of the fused fill + dilation (tile + 2 halos <= 64)
 constexpr int kMaxFusedPasses = 4;  // more dilation passes run one launch per pass
 
-// Treelet and frontier capacity per asset.  Treelet roots are the small
-// children of the nodes with more than 2048 leaves ("big" nodes).  Big nodes
-// whose children are both small cover disjoint ranges of > 2048 leaves, so
-// there are fewer than n / 2048 of them, and every big node lies on the root
-// path (at most 62 nodes) of one of them: fewer than 62 n / 2048 + 62 big
-// nodes, one more treelet than big nodes.
-__host__ __device__ inline int64_t treelet_cap(int64_t n) { return n / 32 + 2 * kMaxDepth + 16; }
+// Tree build: leaves per tile, tiles (groups) per group and in the last group,
+// and the most subtrees that a tile or group leaves waiting: along each of its
+// two edges one per distinct prefix length (62).
+constexpr int kBuildTile = 1024, kJoin = 64, kJoinLast = 128, kSpine = 128;
+constexpr int kJoinLevels = 4;  // 2^30 leaves: 2^20 tiles, 16384, 256, 4, 1 groups
+static_assert(kSpine >= 2 * 62, "a list holds every waiting subtree");
+// Groups of a level of an asset with n leaves (level 0: tiles) and the leaves
+// that each covers; its rows in the level's lists: asset a's start at tile_base
+// / 64^level + a, which keeps assets apart.
+__host__ __device__ inline int64_t join_groups(int64_t n, int level, int64_t* span_out) {
+    int64_t span = kBuildTile, g = (n + span - 1) / span;
+    for (int l = 0; l < level; ++l) {
+        span *= g <= kJoinLast ? kJoinLast : kJoin;
+        g = (n + span - 1) / span;
+    }
+    if (span_out) *span_out = span;
+    return g;
+}
+__host__ __device__ inline int64_t join_row(int64_t tile_base, int64_t a, int level) {
+    return level == 0 ? tile_base : (tile_base >> (6 * level)) + a;
+}
+__host__ __device__ inline int64_t join_rows(int64_t tiles, int64_t n, int level) {
+    return level == 0 ? tiles : (tiles >> (6 * level)) + n + 1;
+}
 
 // Per-asset counter slots.
 constexpr int kCntRays = 0;      // covered texels (rays)
 constexpr int kCntBoxLo = 2;     // u64 box tests (FLAG_COUNT), slots 2-3
 constexpr int kCntTriLo = 4;     // u64 triangle tests (FLAG_COUNT), slots 4-5
-constexpr int kCntFrontier = 6;  // refit frontier length
-constexpr int kCntTreelets = 7;  // refit treelets
 constexpr int kCntIterLo = 8;    // u64 traversal loop trips of whole waves (FLAG_COUNT), slots 8-9
-constexpr int kCntTop = 10;      // refit top nodes (internal nodes above the treelets)
 constexpr int kCntSlots = 16;
 // Batch counter slots.
 constexpr int kGcQueue = 0;  // traversal work queue head
@@ -182,7 +190,6 @@ struct Batch {
     const int32_t* gpf;     // [kGridCount][n + 1] block prefix of each grid
     const uint32_t* ray_pf; // [n + 1] first ray of each asset (written after the raster)
     const uint32_t* rb_pf;  // [n + 1] 64-ray batches before each asset
-    const uint32_t* tl_pf;  // [n + 1] treelets before each asset
     const uint32_t* bt_pf;  // [n + 1] backward sort tiles holding pairs before each asset (after the raster)
     uint32_t* cnt;          // [n][kCntSlots]
     uint32_t* gcnt;         // [kGcSlots]
@@ -262,7 +269,7 @@ __device__ __forceinline__ void texel_weights(const int4* __restrict__ face_uv, 
 // Host description of a batch: asset table, grid prefix tables and the
 // workspace layout.
 struct Layout {
-    size_t status, counters, gcnt, table, grads, gpf, ray_pf, rb_pf, tl_pf, bt_pf;
+    size_t status, counters, gcnt, table, grads, gpf, ray_pf, rb_pf, bt_pf;
     size_t lo_n, lo_deg, lo_off, lo_cur, lo_adj;  // lo vertex normals + vertex->face CSR
     size_t face_t, face_uv, face_cnt, face_off;   // per lo face
     size_t scan_tmp;                              // block sums of the scans
@@ -270,7 +277,7 @@ struct Layout {
     size_t rays, hits;                            // per ray
     size_t bounds_part, bounds;                   // centroid bounds: per sort tile, per asset
     size_t keys0, keys1, vals0, vals1, hist, sup; // radix sort of the BVH keys
-    size_t nodes, nodes_c, leaves, node_parent, leaf_parent, refit_cnt, frontier, treelets, top, child;
+    size_t nodes_c, leaves, items, item_cnt;      // tree; lists of waiting subtrees
     size_t spill;                                 // traversal stack spill
     // backward scratch (BAKE_FLAG_SAVE only)
     size_t bwd_ray, bwd_hterm, bwd_k0, bwd_v0, bwd_k1, bwd_v1, bwd_hist, bwd_sup, bwd_face1, bwd_face2, bwd_sbar,
@@ -327,10 +334,8 @@ hipError_t write_table(void* dst, const void* src, size_t bytes, hipStream_t s, 
 int64_t bwd_sort_zero_words(const Layout& L);
 
 // Per-asset ray starts, 64-ray batch prefix and backward sort tile prefix
-// (after the raster); treelet prefix (after the hierarchy kernel has listed
-// the treelets).
+// (after the raster).
 hipError_t launch_ray_spaces(const BatchHost& H, hipStream_t s);
-hipError_t launch_treelet_space(const BatchHost& H, hipStream_t s);
 
 // Stable LSD radix sort of every asset's (key, value) pairs on the low `bits`
 // bits, 8 per pass, ping-ponging between the two buffers of the sort:

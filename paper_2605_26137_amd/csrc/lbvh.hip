@@ -5,14 +5,13 @@
 //   2. 30-bit Morton code of each centroid, value = original triangle index,
 //   3. stable LSD radix sort of (code, index), 8-bit digits, LDS-ranked with
 //      wave64 ballots, so equal codes keep ascending index order,
-//   4. Karras hierarchy: every internal node finds its key range and split
-//      from common-prefix lengths (code, extended by the index on equal codes);
-//      the same kernel packs the leaves (vertices copied bit-exactly, original
-//      index kept) and lists the refit's treelets and the nodes above them,
-//   5. bottom-up refit in LDS, treelet by treelet, then the nodes above the
-//      treelets: the second arriving child of a node unions both boxes and
-//      continues upward (min/max is exact, so the boxes do not depend on
-//      arrival order); the nodes are then written compressed (32 B each).
+//   4. hierarchy, boxes and compressed nodes in one pass, bottom-up: a subtree
+//      joins the neighbour it shares the longer common prefix with (code,
+//      extended by the index on equal codes), so the tree is the radix tree over
+//      the codes and every node is met with both child boxes in hand (after
+//      Apetrei 2014, with Karras's node numbering).  The same kernel packs the
+//      leaves (vertices copied bit-exactly, original index kept) and writes the
+//      nodes compressed (32 B each).
 // In a batch every asset gets its own tree over its own bounds; sort tiles
 // never straddle two assets, and each tile places its keys from its asset's
 // per-tile and per-super-tile digit counts (section 3).
@@ -456,228 +455,32 @@ __global__ __launch_bounds__(kSortBlock) void radix_scatter_kernel(Batch Bt, con
 }
 
 // ---------------------------------------------------------------------------
-// 4. Karras hierarchy
-// ---------------------------------------------------------------------------
-
-// Per-thread search reach: a node's range and split are searched by its own
-// thread in the wave's LDS window of sorted keys when the range spans at most
-// kKarrasReach keys; longer ranges (the few nodes near the top) are searched
-// by the whole wave together, 64 probes per step.
-constexpr int kKarrasReach = 64;
-// Leaves per refit treelet (section 5): the hierarchy kernel lists the treelets.
-constexpr int kTreelet = 2048;
-
-// The largest x in [lo, hi) with pred(x), given pred(lo) and not pred(hi)
-// (pred monotone: true up to some point, false after it); the wave searches
-// 64 candidates per step.  Wave-uniform arguments.
-template <typename Pred>
-__device__ __forceinline__ int64_t wave_last_true(int64_t lo, int64_t hi, int lane, Pred pred) {
-    while (hi - lo > 1) {
-        const int64_t step = (hi - lo + 63) / 64;
-        const int64_t x = lo + (int64_t)lane * step;
-        const bool ok = lane > 0 && x < hi && pred(x);
-        const uint64_t m = __ballot(ok) | 1ull;
-        const int last = 63 - __clzll((long long)m);
-        lo += (int64_t)last * step;
-        hi = min(hi, lo + step);
-    }
-    return lo;
-}
-
-// Appends, for every lane with want set, one slot of the per-asset list whose
-// length counter is *counter: one atomic per wave (the wave's asset is
-// uniform), slots in lane order.  Returns the lane's slot.
-__device__ __forceinline__ uint32_t wave_append(uint32_t* counter, bool want) {
-    const uint64_t m = __ballot(want);
-    if (m == 0) return 0;
-    const int lane = threadIdx.x & 63;
-    const int leader = __ffsll((long long)m) - 1;
-    uint32_t base = 0;
-    if (lane == leader) base = atomicAdd(counter, (uint32_t)__popcll(m));
-    base = __shfl(base, leader, 64);
-    return base + (uint32_t)__popcll(m & __lanemask_lt());
-}
-
-// Also packs leaf i (its triangle's corners and index, in sorted order: the
-// leaves are independent of the hierarchy) and lists the refit's work (see
-// section 5): a node of more than kTreelet
-// leaves is a top node, listed with its parent link (by its parent, or by
-// itself at the root); a child of at most kTreelet leaves of a top node, or
-// a root of at most kTreelet leaves, roots a treelet, listed with its range
-// and parent link.  Clears the arrival counters of the refit's fallback.
-__global__ __launch_bounds__(kBlock) void karras_kernel(Batch Bt, const uint32_t* __restrict__ keys_all,
-                                                        const uint32_t* __restrict__ sorted_idx,
-                                                        Leaf* __restrict__ leaves,
-                                                        uint32_t* __restrict__ child_all,
-                                                        int32_t* __restrict__ np_all,
-                                                        int32_t* __restrict__ lp_all,
-                                                        int4* __restrict__ list_all,
-                                                        int2* __restrict__ top_all,
-                                                        uint32_t* __restrict__ cnt_all) {
-    // each wave's window: keys [i0 - 64, i0 + 128) around its nodes [i0, i0 + 64)
-    __shared__ uint32_t s_win[kBlock / 64][3 * 64];
-    int64_t lb;
-    const int a = block_asset(Bt, kGHiF, blockIdx.x, &lb);
-    const AssetDev& As = Bt.A[a];
-    const int64_t n = As.nhf;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int64_t i0 = lb * kBlock + wave * 64;
-    const int64_t i = i0 + lane;
-    if (i < n) {
-        const uint32_t g = sorted_idx[As.hf + i];
-        bool bad;
-        const int3 t = tri_idx(As.hi_F, g, As.nhv, &bad);
-        const float3 va = ldv(As.hi_V, t.x), vb = ldv(As.hi_V, t.y), vc = ldv(As.hi_V, t.z);
-        Leaf lf;
-        lf.a = make_float4(va.x, va.y, va.z, vb.x);
-        lf.b = make_float4(vb.y, vb.z, vc.x, vc.y);
-        lf.c = make_float4(vc.z, __int_as_float((int32_t)g), 0.f, 0.f);
-        leaves[As.hf + i] = lf;
-    }
-    const uint32_t* __restrict__ keys = keys_all + As.hf;
-    uint32_t* win = s_win[wave];
-#pragma unroll
-    for (int r = 0; r < 3; ++r) {
-        const int64_t q = i0 - 64 + 64 * r + lane;
-        if (q >= 0 && q < n) win[64 * r + lane] = keys[q];
-    }
-    __syncthreads();
-    if (i0 >= n - 1) return;  // the whole wave is past the asset's nodes
-    // common-prefix length of keys a and b (b within the window of a's wave;
-    // extended by the indices on equal keys), -1 outside [0, n)
-    auto cpw = [&](int64_t a, int64_t b) -> int {
-        if (b < 0 || b >= n) return -1;
-        const uint32_t x = win[a - i0 + 64], y = win[b - i0 + 64];
-        return x == y ? 32 + __clz((uint32_t)a ^ (uint32_t)b) : __clz(x ^ y);
-    };
-    const bool live = i < n - 1;
-    int d = 1, dmin = 0, dnode = 0;
-    int64_t l = 0, sp = 0;
-    bool big = false;
-    if (live) {
-        d = (cpw(i, i + 1) - cpw(i, i - 1)) >= 0 ? 1 : -1;
-        dmin = cpw(i, i - d);
-        int64_t lmax = 2;
-        while (lmax <= kKarrasReach && cpw(i, i + lmax * d) > dmin) lmax <<= 1;
-        if (lmax > kKarrasReach) {
-            big = true;
-        } else {
-            for (int64_t t = lmax >> 1; t >= 1; t >>= 1)
-                if (cpw(i, i + (l + t) * d) > dmin) l += t;
-            dnode = cpw(i, i + l * d);
-            int64_t t = l;
-            do {
-                t = (t + 1) >> 1;
-                if (cpw(i, i + (sp + t) * d) > dnode) sp += t;
-            } while (t > 1);
-        }
-    }
-    // the wave's long ranges, one at a time: range end by probing the powers
-    // of two, then 64-way refinement; the split likewise
-    uint64_t bm = __ballot(big);
-    while (bm) {
-        const int src = __ffsll((long long)bm) - 1;
-        bm &= bm - 1;
-        const int64_t bi = __shfl(i, src, 64);
-        const int bd = __shfl(d, src, 64), bdmin = __shfl(dmin, src, 64);
-        const uint32_t kb = keys[bi];
-        auto cpg = [&](int64_t b) -> int {
-            if (b < 0 || b >= n) return -1;
-            const uint32_t y = keys[b];
-            return kb == y ? 32 + __clz((uint32_t)bi ^ (uint32_t)b) : __clz(kb ^ y);
-        };
-        // 2^k for k <= 6 is known to lie in the range (the per-thread search
-        // found 64 in it); lanes 7..40 probe 2^lane
-        const bool okp = lane > 6 && lane <= 40 && cpg(bi + ((int64_t)1 << lane) * bd) > bdmin;
-        const uint64_t m = __ballot(okp) | 0x7Full;
-        const int K = 63 - __clzll((long long)m);
-        const int64_t L = wave_last_true((int64_t)1 << K, (int64_t)1 << (K + 1), lane,
-                                         [&](int64_t x) { return cpg(bi + x * bd) > bdmin; });
-        const int bdnode = cpg(bi + L * bd);
-        const int64_t S = wave_last_true(0, L, lane, [&](int64_t x) { return cpg(bi + x * bd) > bdnode; });
-        if (lane == src) {
-            l = L;
-            dnode = bdnode;
-            sp = S;
-        }
-    }
-    if (!live) return;
-    int32_t* __restrict__ node_parent = np_all + As.node;
-    int32_t* __restrict__ leaf_parent = lp_all + As.hf;
-    const int64_t j = i + l * d;
-    (void)dnode;
-    const int64_t gamma = i + sp * d + (d < 0 ? -1 : 0);
-    const int64_t lo = i < j ? i : j, hi = i < j ? j : i;
-    const int32_t left = lo == gamma ? ~(int32_t)gamma : (int32_t)gamma;
-    const int32_t right = hi == gamma + 1 ? ~(int32_t)(gamma + 1) : (int32_t)(gamma + 1);
-    child_all[As.node + i] = (uint32_t)gamma | (left < 0 ? kChildLeafL : 0u) | (right < 0 ? kChildLeafR : 0u);
-    if (left < 0) leaf_parent[gamma] = (int32_t)(i << 1);
-    else node_parent[gamma] = (int32_t)(i << 1);
-    if (right < 0) leaf_parent[gamma + 1] = (int32_t)((i << 1) | 1);
-    else node_parent[gamma + 1] = (int32_t)((i << 1) | 1);
-    if (i == 0) node_parent[0] = -1;
-    // the refit's lists
-    cnt_all[As.node + i] = 0u;
-    const bool top = hi - lo + 1 > kTreelet;
-    const uint32_t cap = (uint32_t)treelet_cap(n);
-    uint32_t* ntop = &Bt.cnt[(int64_t)a * kCntSlots + kCntTop];
-    uint32_t* ntl = &Bt.cnt[(int64_t)a * kCntSlots + kCntTreelets];
-    const int32_t cref[2] = {left, right};
-    const int32_t clo[2] = {(int32_t)lo, (int32_t)(gamma + 1)}, chi[2] = {(int32_t)gamma, (int32_t)hi};
-#pragma unroll
-    for (int side = 0; side < 2; ++side) {
-        const int32_t pp = (int32_t)((i << 1) | side);
-        const bool cbig = chi[side] - clo[side] + 1 > kTreelet;
-        const uint32_t et = wave_append(ntop, cbig);
-        if (cbig) {
-            if (et < cap) top_all[As.tl + et] = make_int2(cref[side], pp);
-            else set_status(Bt, kStInternal);
-        }
-        const bool root = top && !cbig;
-        const uint32_t e = wave_append(ntl, root);
-        if (root) {
-            if (e < cap) list_all[As.tl + e] = make_int4(cref[side], clo[side], chi[side], pp);
-            else set_status(Bt, kStInternal);
-        }
-    }
-    const uint32_t er = wave_append(top ? ntop : ntl, i == 0);
-    if (i == 0) {
-        if (er >= cap) set_status(Bt, kStInternal);
-        else if (top) top_all[As.tl + er] = make_int2(0, -1);
-        else list_all[As.tl + er] = make_int4(0, 0, (int32_t)(n - 1), -1);
-    }
-}
-
-// ---------------------------------------------------------------------------
-// 5. leaves + refit
+// 4. hierarchy + leaves + nodes
 // ---------------------------------------------------------------------------
 //
-// The refit avoids device-scope ordering per node (an acquire/release at
-// device scope costs an L2 write-back and invalidation across the XCDs, and
-// chains of them serialise the upper levels):
-//  a. treelets: the maximal subtrees with at most kTreelet leaves (listed by
-//     the hierarchy kernel).  A Karras node covers a contiguous leaf range
-//     [lo, hi] and its index lies in that range, so a treelet's internal
-//     nodes have indices in [lo, hi] too;
-//  b. one workgroup per treelet loads the parent links of [lo, hi] into LDS
-//     and refits bottom-up: each child leaves its box in its own LDS slot of
-//     the parent (one slot per side) and counts its arrival in LDS; the second
-//     arrival reads the sibling's slot and continues.  The treelet root's box
-//     goes to its parent's slot and the parent is appended to a frontier; the
-//     workgroup then writes the treelet's nodes compressed, in parallel;
-//  c. one workgroup per asset finishes the nodes above the treelets from the
-//     frontier: in LDS when there are at most kTopLds of them, else with
-//     global counters that only this workgroup touches.
-
-constexpr int kRefitBlock = 1024;  // 16 waves: the LDS footprint allows one workgroup per CU
-constexpr int kTopBlock = 1024;
-constexpr int kTopList = 8192;
-
-__device__ __forceinline__ void put_slot(BvhNode* node, int side, const float b[6]) {
-    float* f = reinterpret_cast<float*>(node) + 6 * side;
-#pragma unroll
-    for (int k = 0; k < 6; ++k) f[k] = b[k];
-}
+// The radix tree over the sorted codes, from its leaves up.  A subtree covers
+// a leaf range [l, r]; its parent's split lies at r when the prefix common to
+// leaves r and r + 1 is longer than that common to l - 1 and l (it is then the
+// left child), else at l - 1 (the right child).  Both children leave their box
+// at the split; the one that comes second has both boxes and goes on as the
+// parent.  A node's index is that of the end of its range towards its sibling
+// (Karras: the left child of a node with split s is node or leaf s, the right
+// one s + 1; the root is 0), so a node's children and its own index are known as
+// it forms, without searches, parent links or a separate refit.
+//
+// One workgroup does this in LDS for a tile of kBuildTile consecutive leaves.
+// The subtrees whose sibling lies in another tile (at most 62 along each edge
+// of the tile, about twenty in all) go to the tile's list in order, and a join
+// launch does the same over the lists of kJoin tiles, with list entries in place
+// of leaves, then over those of kJoin joined groups, until one group is the whole
+// asset (the last one takes up to kJoinLast: two joins do for 8M faces).
+//
+// Bound by the gather of the leaves' corners and the latency of the climb (a
+// dozen LDS round trips).  Two workgroups fit a CU.  Before, a hierarchy kernel
+// searched every node's range and scattered parent links, a treelet refit read
+// them back and climbed with one workgroup per CU, and one workgroup per asset
+// finished the top: 1.31M faces 164 -> 104 us, 5.24M 654 -> 246 us, 5,120
+// 39 -> 27 us.
 
 __device__ __forceinline__ float pow2f(uint32_t e) { return __uint_as_float(e << 23); }  // 2^(e - 127)
 
@@ -758,284 +561,272 @@ __device__ __forceinline__ void leaf_box(const Leaf& L, float box[6]) {
     }
 }
 
-// Workgroups take the batch's treelets in turn (the treelet prefix over the
-// assets is known on the device only).
-__global__ __launch_bounds__(kRefitBlock) void treelet_refit_kernel(
-    Batch Bt, const Leaf* __restrict__ leaves_all, BvhNode* nodes_all, BvhNodeC* __restrict__ nodes_c_all,
-    const uint32_t* __restrict__ child_all,
-    const int32_t* __restrict__ np_all,
-    const int32_t* __restrict__ lp_all, const int4* __restrict__ list_all, int32_t* __restrict__ frontier_all) {
-    __shared__ int32_t s_np[kTreelet];      // parent link of internal node lo + i
-    __shared__ int32_t s_lp[kTreelet];      // parent link of leaf lo + i
-    __shared__ uint32_t s_cnt[kTreelet];    // arrivals at internal node lo + i
-    __shared__ float s_box[kTreelet][2][6]; // child boxes of internal node lo + i, by side
-    const uint32_t total = Bt.tl_pf[Bt.n];
-    for (uint32_t g = blockIdx.x; g < total; g += gridDim.x) {
-        const int a = upper_asset(Bt.tl_pf, Bt.n, g);
-        const AssetDev& As = Bt.A[a];
-        const int64_t n = As.nhf;
-        const Leaf* __restrict__ leaves = leaves_all + As.hf;
-        BvhNode* nodes = nodes_all + As.node;
-        BvhNodeC* __restrict__ nodes_c = nodes_c_all + As.node;
-        const uint32_t* __restrict__ child = child_all + As.node;
-        const int32_t* __restrict__ node_parent = np_all + As.node;
-        const int32_t* __restrict__ leaf_parent = lp_all + As.hf;
-        uint32_t* nfront = &Bt.cnt[(int64_t)a * kCntSlots + kCntFrontier];
-        const uint32_t front_cap = (uint32_t)treelet_cap(n);
-        const int4 T = list_all[As.tl + (g - Bt.tl_pf[a])];
-        const int32_t ref = T.x, lo = T.y, hi = T.z, rootpp = T.w;
-        const int32_t sz = hi - lo + 1;
-        for (int i = threadIdx.x; i < sz; i += kRefitBlock) {
-            s_np[i] = (lo + i < n - 1) ? node_parent[lo + i] : -1;
-            s_lp[i] = n > 1 ? leaf_parent[lo + i] : -1;
-            s_cnt[i] = 0;
-        }
-        __syncthreads();
-        for (int i = threadIdx.x; i < sz; i += kRefitBlock) {
-            float box[6];
-            leaf_box(leaves[lo + i], box);
-            int32_t cur = ~(lo + i);   // node whose box is in `box`
-            int32_t pp = s_lp[i];
-            for (int level = 0;; ++level) {
-                if (cur == ref) {
-                    // treelet complete: hand its box to the node above
-                    if (rootpp >= 0) {
-                        put_slot(&nodes[rootpp >> 1], rootpp & 1, box);
-                        uint32_t e = atomicAdd(nfront, 1u);
-                        if (e < front_cap) frontier_all[As.tl + e] = rootpp;
-                        else set_status(Bt, kStInternal);
-                    }
-                    break;
-                }
-                if (level > 2 * kMaxDepth || pp < 0) {  // only a malformed hierarchy gets here
-                    set_status(Bt, kStInternal);
-                    break;
-                }
-                const int32_t p = pp >> 1, side = pp & 1, li = p - lo;
-                if (li < 0 || li >= sz) {  // only a malformed hierarchy gets here
-                    set_status(Bt, kStInternal);
-                    break;
-                }
-                // each child leaves its box in its own LDS slot of p and
-                // counts its arrival; the second arrival (workgroup-scope
-                // acquire) reads the other slot and writes the node out
-#pragma unroll
-                for (int q = 0; q < 6; ++q) s_box[li][side][q] = box[q];
-                uint32_t old = __hip_atomic_fetch_add(&s_cnt[li], 1u, __ATOMIC_ACQ_REL,
-                                                      __HIP_MEMORY_SCOPE_WORKGROUP);
-                if (old == 0) break;
-                float sib[6];
-#pragma unroll
-                for (int q = 0; q < 6; ++q) sib[q] = s_box[li][1 - side][q];
+// A subtree that waits for a sibling in another tile or group: its first leaf,
+// the prefix length before that, and its box (its last leaf is the one before
+// the next entry's first).
+struct alignas(16) BuildItem {
+    float box[6];
+    int32_t l, cpl;
+};
+static_assert(sizeof(BuildItem) == 32, "BuildItem is 32 B");
 
-#pragma unroll
-                for (int q = 0; q < 3; ++q) box[q] = fminf(box[q], sib[q]);
-#pragma unroll
-                for (int q = 3; q < 6; ++q) box[q] = fmaxf(box[q], sib[q]);
-                cur = p;
-                pp = s_np[li];
-            }
-        }
-        __syncthreads();
-        // the treelet's internal nodes (both children arrived) from their LDS
-        // slots, in parallel
-        for (int i = threadIdx.x; i < sz; i += kRefitBlock)
-            if (s_cnt[i] == 2u) write_compressed(&nodes_c[lo + i], child[lo + i], s_box[i][0], s_box[i][1]);
-        __syncthreads();
-    }
+constexpr int kBuildBlock = 1024;
+constexpr int kJoinUnits = 2 * kBuildBlock;  // list entries a join holds at a time
+static_assert(kJoinUnits >= 4 * kSpine, "every batch of a join takes some lists");
+constexpr uint32_t kNoNode = 0xFFFFFFFFu;
+
+// Common-prefix length of leaves a and a + 1 of an asset of n leaves (-1 past
+// its ends).
+__device__ __forceinline__ int prefix_len(uint32_t ka, uint32_t kb, int64_t a) {
+    return ka == kb ? 32 + __clz((uint32_t)a ^ (uint32_t)(a + 1)) : __clz(ka ^ kb);
 }
 
-// Top pass: one workgroup per asset climbs from its frontier through the nodes
-// above the treelets.  Each frontier entry says: child `side` of node p is
-// complete and its box is in p's slot.
-//
-// When the asset has at most kTopLds top nodes, the climb runs in LDS: the
-// top nodes (listed by karras_kernel) get LDS slots through an LDS
-// hash of their indices, each learns its parent's slot, the frontier's boxes
-// are copied into their parents' LDS box slots, and the climb's arrival
-// counters, parent links and boxes are LDS accesses only.  Otherwise the
-// nodes' global box slots and counters serve.
-constexpr int kTopLds = 2048;
-constexpr int kTopHash = 4096;  // open addressing, linear probing (load <= 1/2)
-
-__device__ __forceinline__ uint32_t top_hash(int32_t p) { return ((uint32_t)p * 2654435761u) >> 20; }
-
-__device__ __forceinline__ int top_slot(const int32_t* hkey, const int16_t* hval, int32_t p) {
-    uint32_t h = top_hash(p) & (kTopHash - 1);
-    for (int probe = 0; probe < kTopHash; ++probe) {
-        const int32_t k = hkey[h];
-        if (k == p) return hval[h];
-        if (k == -1) return -1;
-        h = (h + 1) & (kTopHash - 1);
-    }
-    return -1;
-}
-
-struct TopLds {
-    int32_t hkey[kTopHash];
-    int16_t hval[kTopHash];
-    int32_t node[kTopLds];      // top node of slot e
-    int32_t up[kTopLds];        // parent slot link (slot << 1 | side), -1 at the root
-    uint32_t cnt[kTopLds];      // arrivals
-    float box[kTopLds][2][6];   // child boxes, by side
+// The climb's state over UNITS leaves or list entries ("units"); slot k is the
+// split before unit k, slot m that after the last one of m.
+template <int UNITS>
+struct ClimbLds {
+    float box[12][UNITS + 1];   // child boxes waiting at a split: left 0-5, right 6-11
+    int32_t end[UNITS + 1];     // far end of the child that came first | side << 30, -1: none yet
+    uint32_t dest[UNITS + 1];   // node at the split: its index | leaf flags of its children
+    int8_t cpl[UNITS + 2];      // prefix common to the leaves before and after a split
+    uint16_t item[UNITS];       // slot + 1 where the waiting subtree that starts here left its box
+    uint32_t wave_sum[kBuildBlock / 64];
 };
 
-__device__ void refit_top_lds(Batch Bt, const AssetDev& As, BvhNode* nodes, BvhNodeC* __restrict__ nodes_c,
-                              const uint32_t* __restrict__ child, const int32_t* __restrict__ frontier, uint32_t nf,
-                              const int2* __restrict__ top, uint32_t nt, TopLds& S) {
-    int32_t* s_hkey = S.hkey;
-    int16_t* s_hval = S.hval;
-    int32_t* s_node = S.node;
-    int32_t* s_up = S.up;
-    uint32_t* s_cnt = S.cnt;
-    float(*s_box)[2][6] = S.box;
-    const int tid = threadIdx.x;
-    for (int h = tid; h < kTopHash; h += kTopBlock) s_hkey[h] = -1;
-    __syncthreads();
-    for (uint32_t e = tid; e < nt; e += kTopBlock) {
-        const int2 t = top[e];
-        s_node[e] = t.x;
-        s_cnt[e] = 0;
-        uint32_t h = top_hash(t.x) & (kTopHash - 1);
-        for (int probe = 0; probe < kTopHash; ++probe) {
-            if (atomicCAS(&s_hkey[h], -1, t.x) == -1) {
-                s_hval[h] = (int16_t)e;
-                break;
-            }
-            h = (h + 1) & (kTopHash - 1);
+// first(k): first leaf of unit k (k = m: one past the last leaf).
+template <int UNITS, typename First>
+__device__ __forceinline__ void climb(ClimbLds<UNITS>& S, int u, float box[6], First first) {
+    int a = u, b = u, slot = -1;
+    uint32_t flags = 0;
+    for (;;) {
+        const int cl = S.cpl[a], cr = S.cpl[b + 1];
+        if (cl < 0 && cr < 0) {  // the whole asset
+            if (slot >= 0) S.dest[slot] = flags;
+            return;
         }
-    }
-    __syncthreads();
-    for (uint32_t e = tid; e < nt; e += kTopBlock) {
-        const int32_t pp = top[e].y;
-        int32_t up = -1;
-        if (pp >= 0) {
-            const int ps = top_slot(s_hkey, s_hval, pp >> 1);
-            if (ps < 0) set_status(Bt, kStInternal);  // a top node's parent is a top node
-            else up = (ps << 1) | (pp & 1);
-        }
-        s_up[e] = up;
-    }
-    // the treelet roots' boxes, from their parents' global slots
-    for (uint32_t f = tid; f < nf; f += kTopBlock) {
-        const int32_t pp = frontier[f];
-        const int ps = top_slot(s_hkey, s_hval, pp >> 1);
-        if (ps < 0) {
-            set_status(Bt, kStInternal);
-            continue;
-        }
-        const float* g = reinterpret_cast<const float*>(&nodes[pp >> 1]) + 6 * (pp & 1);
+        const bool left = cr > cl;
+        if (slot >= 0) S.dest[slot] = (uint32_t)(left ? first(b + 1) - 1 : first(a)) | flags;
+        const int si = left ? b + 1 : a;
+        const int side = left ? 0 : 6;
 #pragma unroll
-        for (int q = 0; q < 6; ++q) s_box[ps][pp & 1][q] = g[q];
-    }
-    __syncthreads();
-    for (uint32_t f = tid; f < nf; f += kTopBlock) {
-        const int32_t pp0 = frontier[f];
-        int e = top_slot(s_hkey, s_hval, pp0 >> 1);
-        for (int level = 0; e >= 0; ++level) {
-            if (level > 2 * kMaxDepth) {  // only a malformed hierarchy gets here
-                set_status(Bt, kStInternal);
-                break;
-            }
-            const uint32_t old = __hip_atomic_fetch_add(&s_cnt[e], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
-            if (old == 0) break;
-            float box[6];
+        for (int q = 0; q < 6; ++q) S.box[side + q][si] = box[q];
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        const int32_t old = __hip_atomic_exchange(&S.end[si], (left ? a : b) | (left ? 0 : 1 << 30), __ATOMIC_RELAXED,
+                                                  __HIP_MEMORY_SCOPE_WORKGROUP);
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+        if (old == -1) return;  // the sibling goes on
 #pragma unroll
-            for (int q = 0; q < 3; ++q) box[q] = fminf(s_box[e][0][q], s_box[e][1][q]);
+        for (int q = 0; q < 3; ++q) box[q] = fminf(box[q], S.box[6 - side + q][si]);
 #pragma unroll
-            for (int q = 3; q < 6; ++q) box[q] = fmaxf(s_box[e][0][q], s_box[e][1][q]);
-            const int32_t up = s_up[e];
-            if (up < 0) break;
-#pragma unroll
-            for (int q = 0; q < 6; ++q) s_box[up >> 1][up & 1][q] = box[q];
-            e = up >> 1;
-        }
-    }
-    __syncthreads();
-    for (uint32_t e = tid; e < nt; e += kTopBlock) {
-        if (s_cnt[e] == 2u) write_compressed(&nodes_c[s_node[e]], child[s_node[e]], s_box[e][0], s_box[e][1]);
-        else set_status(Bt, kStInternal);
+        for (int q = 3; q < 6; ++q) box[q] = fmaxf(box[q], S.box[6 - side + q][si]);
+        const int far = old & ~(1 << 30);
+        if (left) b = far;
+        else a = far;
+        slot = si;
+        // a child is a leaf when it is one unit of one leaf
+        flags = (a == si - 1 && first(si) - first(si - 1) == 1 ? kChildLeafL : 0u) |
+                (b == si && first(si + 1) - first(si) == 1 ? kChildLeafR : 0u);
     }
 }
 
-__global__ __launch_bounds__(kTopBlock) void refit_top_kernel(Batch Bt, BvhNode* nodes_all,
-                                                             BvhNodeC* __restrict__ nodes_c_all,
-                                                             const uint32_t* __restrict__ child_all,
-                                                             const int32_t* __restrict__ np_all,
-                                                             const int32_t* __restrict__ frontier_all,
-                                                             const int2* __restrict__ top_all,
-                                                             uint32_t* cnt_all) {
-    // global path: nodes completed by the climb, compressed in parallel after
-    // it (beyond the list's capacity a node is compressed where it completes)
-    union TopMem {
-        TopLds lds;
-        int32_t done[kTopList];
-    };
-    __shared__ TopMem s_mem;
-    __shared__ uint32_t s_ndone;
-    int32_t* s_done = s_mem.done;
-    const int a = blockIdx.x;
-    const AssetDev& As = Bt.A[a];
-    if (As.nhf <= 1) return;
-    BvhNode* nodes = nodes_all + As.node;
-    BvhNodeC* __restrict__ nodes_c = nodes_c_all + As.node;
-    const uint32_t* __restrict__ child = child_all + As.node;
-    const int32_t* __restrict__ node_parent = np_all + As.node;
-    const int32_t* __restrict__ frontier = frontier_all + As.tl;
-    uint32_t* cnt = cnt_all + As.node;
-    const uint32_t m = min(Bt.cnt[(int64_t)a * kCntSlots + kCntFrontier], (uint32_t)treelet_cap(As.nhf));
-    const uint32_t nt = Bt.cnt[(int64_t)a * kCntSlots + kCntTop];
-    if (nt > 0 && nt <= min((uint32_t)kTopLds, (uint32_t)treelet_cap(As.nhf))) {
-        refit_top_lds(Bt, As, nodes, nodes_c, child, frontier, m, top_all + As.tl, nt, s_mem.lds);
-        return;
-    }
-    if (threadIdx.x == 0) s_ndone = 0;
+// After every unit has climbed: writes the nodes formed, and the subtrees left
+// waiting in order; returns their number.
+template <int UNITS, typename First>
+__device__ uint32_t climb_out(Batch& Bt, ClimbLds<UNITS>& S, int m, BvhNodeC* __restrict__ nodes, BuildItem* items,
+                              First first) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int k = tid; k < m; k += kBuildBlock) S.item[k] = 0;
     __syncthreads();
-    for (uint32_t e = threadIdx.x; e < m; e += kTopBlock) {
-        int32_t pp = frontier[e];
-        for (int level = 0; pp >= 0; ++level) {
-            if (level > 2 * kMaxDepth) {
-                set_status(Bt, kStInternal);
-                break;
-            }
-            int32_t p = pp >> 1;
-            uint32_t old = __hip_atomic_fetch_add(&cnt[p], 1u, __ATOMIC_ACQ_REL,
-                                                  __HIP_MEMORY_SCOPE_WORKGROUP);
-            if (old == 0) break;
-            float box[6], bl[6], br[6];
-            const float* f = reinterpret_cast<const float*>(&nodes[p]);
+    for (int k = tid; k <= m; k += kBuildBlock) {
+        const uint32_t d = S.dest[k];
+        if (d != kNoNode) {
+            float L[6], R[6];
 #pragma unroll
             for (int q = 0; q < 6; ++q) {
-                bl[q] = f[q];
-                br[q] = f[6 + q];
+                L[q] = S.box[q][k];
+                R[q] = S.box[6 + q][k];
             }
-            const uint32_t slot = atomicAdd(&s_ndone, 1u);
-            if (slot < (uint32_t)kTopList) s_done[slot] = p;
-            else write_compressed(&nodes_c[p], child[p], bl, br);
-#pragma unroll
-            for (int q = 0; q < 3; ++q) box[q] = fminf(bl[q], br[q]);
-#pragma unroll
-            for (int q = 3; q < 6; ++q) box[q] = fmaxf(bl[q], br[q]);
-            pp = node_parent[p];
-            if (pp >= 0) put_slot(&nodes[pp >> 1], pp & 1, box);
+            write_compressed(&nodes[d & kChildIndex], (uint32_t)(first(k) - 1) | (d & ~kChildIndex), L, R);
+        } else if (S.end[k] != -1) {  // one child waits
+            S.item[S.end[k] & (1 << 30) ? k : S.end[k]] = (uint16_t)(k + 1);
         }
     }
     __syncthreads();
-    const uint32_t nd = min(s_ndone, (uint32_t)kTopList);
-    for (uint32_t i = threadIdx.x; i < nd; i += kTopBlock) {
-        const int32_t p = s_done[i];
-        const float* f = reinterpret_cast<const float*>(&nodes[p]);
-        float bl[6], br[6];
-#pragma unroll
-        for (int q = 0; q < 6; ++q) {
-            bl[q] = f[q];
-            br[q] = f[6 + q];
+    uint32_t base = 0;
+    for (int k0 = 0; k0 < m; k0 += kBuildBlock) {
+        const int k = k0 + tid;
+        const uint32_t it = k < m ? S.item[k] : 0u;
+        const uint64_t bal = __ballot(it != 0);
+        if (lane == 0) S.wave_sum[wave] = (uint32_t)__popcll(bal);
+        __syncthreads();
+        uint32_t at = base + (uint32_t)__popcll(bal & __lanemask_lt());
+        for (int w = 0; w < kBuildBlock / 64; ++w) {
+            const uint32_t c = S.wave_sum[w];
+            if (w < wave) at += c;
+            base += c;
         }
-        write_compressed(&nodes_c[p], child[p], bl, br);
+        if (it != 0) {
+            if (at < (uint32_t)kSpine) {
+                const int si = (int)it - 1, side = S.end[si] & (1 << 30) ? 6 : 0;
+                BuildItem o;
+#pragma unroll
+                for (int q = 0; q < 6; ++q) o.box[q] = S.box[side + q][si];
+                o.l = (int32_t)first(k);
+                o.cpl = S.cpl[k];
+                items[at] = o;
+            } else {
+                set_status(Bt, kStInternal);  // the depth bound rules it out
+            }
+        }
+        __syncthreads();
     }
+    return min(base, (uint32_t)kSpine);
 }
 
-inline unsigned blocks_for(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
+__global__ __launch_bounds__(kBuildBlock) __attribute__((amdgpu_waves_per_eu(8))) void build_tile_kernel(
+    Batch Bt, const uint32_t* __restrict__ keys_all, const uint32_t* __restrict__ sorted_idx, Leaf* __restrict__ leaves,
+    BvhNodeC* __restrict__ nodes_all, BuildItem* __restrict__ items, uint32_t* __restrict__ counts) {
+    static_assert(kBuildTile == kBuildBlock, "a thread per leaf");
+    __shared__ ClimbLds<kBuildTile> S;
+    int64_t lt;
+    const int a = block_asset(Bt, kGBuild, blockIdx.x, &lt);
+    const AssetDev& As = Bt.A[a];
+    const int64_t n = As.nhf, t0 = lt * kBuildTile;
+    const int m = (int)min((int64_t)kBuildTile, n - t0);
+    const int tid = threadIdx.x;
+    const int64_t i = t0 + tid;
+    const uint32_t* __restrict__ keys = keys_all + As.hf;
+    const bool on = tid < m;
+    float box[6];
+    if (on) {
+        const uint32_t g = sorted_idx[As.hf + i];
+        const uint32_t k0 = keys[i], kl = i > 0 ? keys[i - 1] : 0u;
+        bool bad;
+        const int3 t = tri_idx(As.hi_F, g, As.nhv, &bad);
+        const float3 va = ldv(As.hi_V, t.x), vb = ldv(As.hi_V, t.y), vc = ldv(As.hi_V, t.z);
+        Leaf lf;
+        lf.a = make_float4(va.x, va.y, va.z, vb.x);
+        lf.b = make_float4(vb.y, vb.z, vc.x, vc.y);
+        lf.c = make_float4(vc.z, __int_as_float((int32_t)g), 0.f, 0.f);
+        leaves[As.hf + i] = lf;
+        leaf_box(lf, box);
+        S.cpl[tid] = (int8_t)(i > 0 ? prefix_len(kl, k0, i - 1) : -1);
+        if (tid == m - 1) S.cpl[m] = (int8_t)(i + 1 < n ? prefix_len(k0, keys[i + 1], i) : -1);
+    }
+    S.end[tid] = -1;
+    S.dest[tid] = kNoNode;
+    if (tid == 0) {
+        S.end[kBuildTile] = -1;
+        S.dest[kBuildTile] = kNoNode;
+    }
+    __syncthreads();
+    auto first = [&](int k) { return (int32_t)t0 + k; };
+    if (on) climb(S, tid, box, first);
+    __syncthreads();
+    const int64_t row = As.tl + lt;
+    const uint32_t left = climb_out(Bt, S, m, nodes_all + As.node, items + row * kSpine, first);
+    if (tid == 0) counts[row] = left;
+}
+
+// Joins the lists of up to kJoinLast tiles (level 1) or groups (higher levels),
+// as many at a time as fit the workgroup's LDS (mostly all of them); what a
+// batch leaves waiting goes before the next one.
+struct JoinArgs {
+    Batch B;
+    const uint32_t* keys;
+    BvhNodeC* nodes;
+    const BuildItem* in;
+    const uint32_t* in_count;
+    BuildItem* out;
+    uint32_t* out_count;
+    int level;
+};
+
+__global__ __launch_bounds__(kBuildBlock) void build_join_kernel(JoinArgs p) {
+    __shared__ ClimbLds<kJoinUnits> S;
+    __shared__ int32_t s_first[kJoinUnits + 1];
+    __shared__ int32_t s_at[kJoinLast + 1];  // entries before each list
+    __shared__ int s_take, s_carry;
+    Batch& Bt = p.B;
+    int64_t lg;
+    const int a = block_asset(Bt, kGJoin1 + p.level - 1, blockIdx.x, &lg);
+    const AssetDev& As = Bt.A[a];
+    const int64_t n = As.nhf;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const uint32_t* __restrict__ keys = p.keys + As.hf;
+    int64_t span;  // leaves of a list
+    const int64_t lists = join_groups(n, p.level - 1, &span), groups = join_groups(n, p.level, nullptr);
+    const int64_t c0 = groups == 1 ? 0 : lg * kJoin;
+    const int nc = (int)min((int64_t)(groups == 1 ? kJoinLast : kJoin), lists - c0);
+    const int64_t row_in = join_row(As.tl, a, p.level - 1) + c0, row = join_row(As.tl, a, p.level) + lg;
+    static_assert(kJoinLast == 128, "two waves sum the list lengths");
+    if (tid < 128) {
+        int x = tid < nc ? (int)min(p.in_count[row_in + tid], (uint32_t)kSpine) : 0;
+        for (int o = 1; o < 64; o <<= 1) {
+            const int y = __shfl_up(x, o, 64);
+            if (lane >= o) x += y;
+        }
+        s_at[tid + 1] = x;
+    }
+    if (tid == 0) {
+        s_at[0] = 0;
+        s_carry = 0;
+    }
+    __syncthreads();
+    if (tid >= 64 && tid < 128) s_at[tid + 1] += s_at[64];
+    BuildItem* out = p.out + row * kSpine;
+    auto first = [&](int k) { return s_first[k]; };
+    for (int c = 0; c < nc;) {
+        if (tid == 0) s_take = c;
+        __syncthreads();
+        const int carry = s_carry, before = s_at[c];
+        if (tid >= c && tid < nc && carry + s_at[tid + 1] - before <= kJoinUnits) atomicMax(&s_take, tid + 1);
+        __syncthreads();
+        const int c2 = s_take, m = carry + s_at[c2] - before;
+        const int64_t end = min(n, (c0 + c2) * span);  // the batch's last leaf + 1
+        float box[kJoinUnits / kBuildBlock][6];
+#pragma unroll
+        for (int h = 0; h < kJoinUnits / kBuildBlock; ++h) {
+            const int u = tid + h * kBuildBlock;
+            S.end[u] = -1;
+            S.dest[u] = kNoNode;
+            if (u < m) {
+                const BuildItem* src = out + u;
+                if (u >= carry) {
+                    const int at = u - carry + before;
+                    int lo = c, hi = c2 - 1;  // last list that starts at or before the entry
+                    while (lo < hi) {
+                        const int mid = (lo + hi + 1) >> 1;
+                        if (s_at[mid] <= at) lo = mid;
+                        else hi = mid - 1;
+                    }
+                    src = p.in + (row_in + lo) * kSpine + (at - s_at[lo]);
+                }
+                const BuildItem it = *src;
+#pragma unroll
+                for (int q = 0; q < 6; ++q) box[h][q] = it.box[q];
+                s_first[u] = it.l;
+                S.cpl[u] = (int8_t)it.cpl;
+            }
+        }
+        if (tid == 0) {
+            S.end[kJoinUnits] = -1;
+            S.dest[kJoinUnits] = kNoNode;
+            s_first[m] = (int32_t)end;
+            S.cpl[m] = (int8_t)(end < n ? prefix_len(keys[end - 1], keys[end], end - 1) : -1);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int h = 0; h < kJoinUnits / kBuildBlock; ++h)
+            if (tid + h * kBuildBlock < m) climb(S, tid + h * kBuildBlock, box[h], first);
+        __syncthreads();
+        const uint32_t left = climb_out(Bt, S, m, p.nodes + As.node, out, first);
+        if (tid == 0) s_carry = (int)left;
+        c = c2;
+        __syncthreads();
+    }
+    if (tid == 0) p.out_count[row] = (uint32_t)s_carry;
+}
 
 }  // namespace
 
@@ -1097,16 +888,8 @@ hipError_t launch_bvh_build(const BatchHost& H, hipStream_t s) {
     float* bounds = (float*)(ws + L.bounds);
     uint32_t* k0 = (uint32_t*)(ws + L.keys0);
     uint32_t* v0 = (uint32_t*)(ws + L.vals0);
-    BvhNode* nodes = (BvhNode*)(ws + L.nodes);
     BvhNodeC* nodes_c = (BvhNodeC*)(ws + L.nodes_c);
     Leaf* leaves = (Leaf*)(ws + L.leaves);
-    int32_t* np = (int32_t*)(ws + L.node_parent);
-    int32_t* lp = (int32_t*)(ws + L.leaf_parent);
-    uint32_t* cnt = (uint32_t*)(ws + L.refit_cnt);
-    int32_t* frontier = (int32_t*)(ws + L.frontier);
-    int4* tlist = (int4*)(ws + L.treelets);
-    int2* top = (int2*)(ws + L.top);
-    uint32_t* child = (uint32_t*)(ws + L.child);
 
     hipLaunchKernelGGL(bounds_part_kernel, dim3((unsigned)(H.blocks(kGSort) * kBoundsSplit)), dim3(kBlock), 0, s,
                        H.dev, part);
@@ -1119,25 +902,28 @@ hipError_t launch_bvh_build(const BatchHost& H, hipStream_t s) {
     bool in1 = false;
     if ((e = launch_sort(H, kSortBvh, 30, &in1, s)) != hipSuccess) return e;
     // 30-bit keys take four 8-bit passes: the sorted arrays are back in keys0 / vals0
-    if (H.blocks(kGHiF) > 0) {
-        hipLaunchKernelGGL(karras_kernel, dim3((unsigned)H.blocks(kGHiF)), dim3(kBlock), 0, s, H.dev,
-                           (const uint32_t*)k0, (const uint32_t*)v0, leaves, child, np, lp, tlist, top, cnt);
-    }
+    BuildItem* items = (BuildItem*)(ws + L.items);
+    uint32_t* counts = (uint32_t*)(ws + L.item_cnt);
+    hipLaunchKernelGGL(build_tile_kernel, dim3((unsigned)H.blocks(kGBuild)), dim3(kBuildBlock), 0, s, H.dev,
+                       (const uint32_t*)k0, (const uint32_t*)v0, leaves, nodes_c, items, counts);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    if (L.t_node > 0) {
-        if ((e = launch_treelet_space(H, s)) != hipSuccess) return e;
-        // enough workgroups for the treelets of every asset (at least one per
-        // kTreelet / 2 leaves), capped
-        int64_t grid = 0;
-        for (int a = 0; a < L.n; ++a) grid += H.A[a].nhf / (kTreelet / 2) + 1;
-        grid = std::min<int64_t>(grid, 2048);
-        hipLaunchKernelGGL(treelet_refit_kernel, dim3((unsigned)grid), dim3(kRefitBlock), 0, s, H.dev,
-                           (const Leaf*)leaves, nodes, nodes_c, (const uint32_t*)child, (const int32_t*)np,
-                           (const int32_t*)lp,
-                           (const int4*)tlist, frontier);
-        hipLaunchKernelGGL(refit_top_kernel, dim3((unsigned)L.n), dim3(kTopBlock), 0, s, H.dev, nodes, nodes_c,
-                           (const uint32_t*)child, (const int32_t*)np, (const int32_t*)frontier, (const int2*)top,
-                           cnt);
+    int64_t row = 0;  // first row of the level below
+    for (int level = 1; level <= kJoinLevels; ++level) {
+        const int64_t blocks = H.blocks(kGJoin1 + level - 1);
+        if (blocks == 0) break;  // every asset is whole
+        const int64_t next = row + join_rows(L.t_tl, L.n, level - 1);
+        JoinArgs j;
+        j.B = H.dev;
+        j.keys = k0;
+        j.nodes = nodes_c;
+        j.in = items + row * kSpine;
+        j.in_count = counts + row;
+        j.out = items + next * kSpine;
+        j.out_count = counts + next;
+        j.level = level;
+        hipLaunchKernelGGL(build_join_kernel, dim3((unsigned)blocks), dim3(kBuildBlock), 0, s, j);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        row = next;
     }
     return hipGetLastError();
 }

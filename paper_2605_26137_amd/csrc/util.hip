@@ -239,24 +239,6 @@ __global__ __launch_bounds__(kPrefixBlock) void ray_spaces_kernel(Batch B, const
     }
 }
 
-__global__ __launch_bounds__(kPrefixBlock) void treelet_space_kernel(Batch B, uint32_t* tl_pf) {
-    __shared__ uint32_t lw[kPrefixBlock / 64];
-    __shared__ uint32_t carry;
-    if (threadIdx.x == 0) carry = 0;
-    __syncthreads();
-    for (int c = 0; c < B.n; c += kPrefixBlock) {
-        const int a = c + threadIdx.x;
-        uint32_t m = 0;
-        if (a < B.n) {
-            const uint32_t cap = (uint32_t)treelet_cap(B.A[a].nhf);
-            m = min(B.cnt[(int64_t)a * kCntSlots + kCntTreelets], cap);
-            if (B.A[a].nhf <= 1) m = 0;  // nothing to refit
-        }
-        asset_prefix(m, a, B.n, tl_pf, &carry, lw);
-    }
-    if (threadIdx.x == 0) tl_pf[B.n] = carry;
-}
-
 int grid_for(int64_t n, int block) {
     int64_t g = (n + block - 1) / block;
     if (g < 1) g = 1;
@@ -325,12 +307,6 @@ hipError_t launch_ray_spaces(const BatchHost& H, hipStream_t s) {
     hipLaunchKernelGGL(ray_spaces_kernel, dim3(1), dim3(kPrefixBlock), 0, s, H.dev,
                        (const uint32_t*)(H.ws + L.face_off), L.t_lf, (uint32_t*)(H.ws + L.ray_pf),
                        (uint32_t*)(H.ws + L.rb_pf), (uint32_t*)(H.ws + L.bt_pf));
-    return hipGetLastError();
-}
-
-hipError_t launch_treelet_space(const BatchHost& H, hipStream_t s) {
-    hipLaunchKernelGGL(treelet_space_kernel, dim3(1), dim3(kPrefixBlock), 0, s, H.dev,
-                       (uint32_t*)(H.ws + H.L.tl_pf));
     return hipGetLastError();
 }
 
