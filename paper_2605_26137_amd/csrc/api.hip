@@ -121,7 +121,7 @@ int64_t grid_blocks(int g, const Sizes& z) {
         case kGTex: return cdiv(tex, 256);
         case kGTex3: return cdiv(3 * tex, 256);
         case kGBwdSort: return cdiv(3 * tex, kSortTile);
-        case kGTile: return cdiv(z.res, kFinishTile) * cdiv(z.res, kFinishTile);
+        case kGTile: return cdiv(z.res, kFinishCols) * cdiv(z.res, kFinishRows);
         case kGBuild: return cdiv(z.nhf, kBuildTile);
     }
     if (g >= kGJoin1 && g < kGJoin1 + kJoinLevels) {
@@ -548,7 +548,8 @@ int32_t run_forward(Plan& P, const Opts& o, void* workspace, hipStream_t s) {
     HIP_OR_FAIL(launch_dilate(H, o.dilate, s));
     bool any_rgb8 = false;
     for (int a = 0; a < L.n; ++a) any_rgb8 = any_rgb8 || P.A[a].out_rgb8 != nullptr;
-    if (any_rgb8) HIP_OR_FAIL(launch_rgb8(H, s));
+    // the fused fill writes the bytes as well
+    if (any_rgb8 && (o.dilate == 0 || o.dilate > kMaxFusedPasses)) HIP_OR_FAIL(launch_rgb8(H, s));
     if (save) remember_saved(workspace, P.sig, one_stream, nonce);
     else forget_saved(workspace);
     HIP_OR_FAIL(tim_record(tim, 5, s));

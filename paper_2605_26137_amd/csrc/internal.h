@@ -81,16 +81,35 @@ constexpr int32_t kMiss = -1, kUnreliable = -2, kUncovered = -3;
 // through exactly the arithmetic of a single bake.
 // ---------------------------------------------------------------------------
 
+// A pointer to device memory held in memory.  Read there by a kernel, a plain
+// pointer could as well point to LDS for all the compiler knows: its accesses
+// become flat ones, which every wait for LDS waits for and the other way round,
+// and loads meant to be in flight together go one after the other.
+#if defined(__HIP_DEVICE_COMPILE__)
+#define BAKE_IN_GLOBAL __attribute__((address_space(1)))
+#else
+#define BAKE_IN_GLOBAL
+#endif
+template <typename T>
+struct DevPtr {
+    BAKE_IN_GLOBAL T* p;
+    DevPtr() = default;
+    __host__ __device__ DevPtr(T* q) : p((BAKE_IN_GLOBAL T*)q) {}
+    __host__ __device__ operator T*() const { return (T*)p; }
+};
+#undef BAKE_IN_GLOBAL
+static_assert(sizeof(DevPtr<float>) == sizeof(float*), "a pointer either way");
+
 struct AssetDev {
-    const float* hi_V;
-    const int32_t* hi_F;
-    const float* hi_N;
-    const float* lo_V;
-    const int32_t* lo_F;
-    const float* lo_UV;
-    float* out_map;
-    int32_t* out_hit;
-    uint8_t* out_rgb8;  // may be null
+    DevPtr<const float> hi_V;
+    DevPtr<const int32_t> hi_F;
+    DevPtr<const float> hi_N;
+    DevPtr<const float> lo_V;
+    DevPtr<const int32_t> lo_F;
+    DevPtr<const float> lo_UV;
+    DevPtr<float> out_map;
+    DevPtr<int32_t> out_hit;
+    DevPtr<uint8_t> out_rgb8;  // may be null
     int32_t nhv, nhf, nlv, nlf;
     int32_t res, log2res;
     float max_dist;
@@ -108,9 +127,9 @@ struct AssetDev {
 
 // Inputs and outputs of the backward pass, one per asset.
 struct AssetGrad {
-    const float* grad_map;  // [res, res, 3]
-    float* grad_lo_V;       // [nlv, 3] or null
-    float* grad_hi_N;       // [nhv, 3] or null
+    DevPtr<const float> grad_map;  // [res, res, 3]
+    DevPtr<float> grad_lo_V;       // [nlv, 3] or null
+    DevPtr<float> grad_hi_N;       // [nhv, 3] or null
 };
 
 // Grids: per-asset block counts of the launches, as prefix tables.
@@ -124,7 +143,7 @@ enum GridId : int {
     kGTex,      // texels, 256 per block
     kGTex3,     // texel channels, 256 per block
     kGBwdSort,  // backward sort tiles (capacity 3 res^2, kSortTile per block)
-    kGTile,     // kFinishTile^2 texel tiles of the fused uncovered fill + dilation
+    kGTile,     // kFinishCols x kFinishRows texel tiles of the fused uncovered fill + dilation
     kGBuild,    // tiles of the tree build (kBuildTile leaves per block)
     kGJoin1,    // groups of kJoin tiles, of kJoin groups, ... (none once the asset is one group)
     kGJoin2,
@@ -140,7 +159,7 @@ constexpr int kSuper = 32;       // sort tiles per super-tile (digit counts summ
 // Super-tile rows of a sort over `tiles` tiles of `n` assets (asset a's rows
 // start at its first tile / kSuper + a).
 __host__ __device__ inline int64_t sort_super_rows(int64_t tiles, int64_t n) { return tiles / kSuper + n + 1; }
-constexpr int kFinishTile = 56;  // texel tile side of the fused fill + dilation (tile + 2 halos <= 64)
+constexpr int kFinishCols = 56, kFinishRows = 28;  // texel tile of the fused fill + dilation (columns + 2 halos <= 64)
 constexpr int kMaxFusedPasses = 4;  // more dilation passes run one launch per pass
 
 // Tree build: leaves per tile, tiles (groups) per group and in the last group,

@@ -322,6 +322,9 @@ __global__ __launch_bounds__(256) void uncovered_kernel(Batch Bt, const uint32_t
     As.out_hit[t] = kUncovered;
 }
 
+// Written out, so that the fused and the per-pass fill round alike.
+__device__ __forceinline__ float sumsq(float x, float y, float z) { return fmaf(z, z, fmaf(y, y, x * x)); }
+
 // Pass k: a still-empty texel takes the normalised sum of its 8 neighbours
 // that had a value before this pass (level < k).  Texels written in this pass
 // are never read in it, so the map is updated in place.
@@ -354,7 +357,7 @@ __global__ __launch_bounds__(256) void dilate_kernel(Batch Bt, int pass, uint8_t
         }
     }
     if (cnt == 0) return;
-    float l2 = sx * sx + sy * sy + sz * sz;
+    float l2 = sumsq(sx, sy, sz);
     if (!(l2 > 0.f)) return;
     float r = 1.0f / sqrtf(l2);
     map[3 * t] = sx * r;
@@ -363,41 +366,61 @@ __global__ __launch_bounds__(256) void dilate_kernel(Batch Bt, int pass, uint8_t
     level[t] = (uint8_t)pass;
 }
 
-// Uncovered fill and 1 <= k <= kMaxFusedPasses dilation passes in one launch.
-// A workgroup takes a kFinishTile^2 texel tile plus a k-texel halo, R = tile
-// + 2k <= 64 texels a side: one wave per region row at a time, one lane per
-// column.  The region's values go to LDS (covered texels with their traced
-// value, uncovered ones as (0,0,1)) and its rows to 64-bit masks: inside the
-// image, and has a value before the pass (covered, or filled in an earlier
-// pass).  A pass fills, with the pass rule of dilate_kernel, only the empty
-// texels that the masks show to have a valued neighbour; the others read
-// nothing.  A value at distance d from the region's edge is exact through
-// pass d, so the tile (d >= k) is exact after k passes: the result is bitwise
-// that of the fill + per-pass launches (same neighbours, same order of sums).
+__device__ __forceinline__ uint8_t rgb8_of(float v) {
+    float c = floorf((v + 1.0f) * 127.5f + 0.5f);
+    c = fminf(fmaxf(c, 0.0f), 255.0f);
+    return (uint8_t)c;
+}
+
+// Uncovered fill, 1 <= k <= kMaxFusedPasses dilation passes and the 8-bit map in
+// one launch.  A workgroup takes a tile of kFinishCols x kFinishRows texels plus a
+// k-texel halo; a region row is a wave's, a lane per column.  Its rows become
+// 64-bit masks: inside the image, and has a value before the pass (covered, or
+// filled in an earlier pass).  Covered texels beside an uncovered one go to
+// LDS with their traced value (all of them where the 8-bit map is written),
+// uncovered ones as (0,0,1).  A pass fills, with the pass rule of dilate_kernel,
+// only the empty texels that the masks show to have a valued neighbour: they go to
+// a list that the workgroup shares out.  A texel's twenty-four neighbour values
+// are read whether valued or not and selected, so that they arrive together
+// instead of one after the other behind eight branches (adding the +0 of an
+// unvalued one changes no sum that starts at +0).  A value at distance d from the
+// region's edge is exact through pass d, so the tile (d >= k) is exact after k
+// passes: the result is bitwise that of the fill + per-pass launches (same
+// neighbours, same order of sums).
+//
+// Bound by latency: coverage, values, then k passes of two LDS trips each.  A
+// tile of 28 rows gives a small image workgroups enough and a wave four rows.
+// 128^2 with 2 passes 16.7 -> 8.8 us, 512^2 with 4 and the bytes 34 -> 16, 2048^2
+// 53 -> 46, 4096^2 176 -> 158 (before: 56 rows, a coverage load awaited per row,
+// every covered value read, a separate launch for the bytes).  12 rows: 6.7, 14, 55
+// and 196 us; 56 rows: 13, 24, 56 and 179.
 constexpr int kFinishBlock = 512;
 constexpr int kFinishWaves = kFinishBlock / 64;
-static_assert(kFinishTile + 2 * kMaxFusedPasses <= 64, "a region row fits one wave");
+static_assert(kFinishCols + 2 * kMaxFusedPasses <= 64, "a region row fits one wave");
 
 template <int PASSES>
 __global__ __launch_bounds__(kFinishBlock) void finish_kernel(Batch Bt, const uint32_t* __restrict__ facemap_all) {
     static_assert(PASSES >= 1 && PASSES <= kMaxFusedPasses, "fused pass count");
-    constexpr int R = kFinishTile + 2 * PASSES;                // region side
+    constexpr int R = kFinishRows + 2 * PASSES;                   // region rows
     constexpr int kRows = (R + kFinishWaves - 1) / kFinishWaves;  // region rows per wave
-    __shared__ float s_map[R][64][3];
+    __shared__ float s_map[R][3][64];
     __shared__ uint64_t s_in[R], s_val[2][R];
+    __shared__ uint16_t s_list[R * 64];
+    __shared__ int s_n[2];
     int64_t lt;
     const AssetDev& As = Bt.A[block_asset(Bt, kGTile, blockIdx.x, &lt)];
     const int32_t res = As.res;
-    const int32_t tiles_x = (res + kFinishTile - 1) / kFinishTile;
-    const int32_t oi = (int32_t)(lt / tiles_x) * kFinishTile - PASSES;  // region origin
-    const int32_t oj = (int32_t)(lt % tiles_x) * kFinishTile - PASSES;
+    const int32_t tiles_x = (res + kFinishCols - 1) / kFinishCols;
+    const int32_t oi = (int32_t)(lt / tiles_x) * kFinishRows - PASSES;  // region origin
+    const int32_t oj = (int32_t)(lt % tiles_x) * kFinishCols - PASSES;
     const uint32_t* __restrict__ facemap = facemap_all + As.tex;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int32_t j = oj + lane;
-    const bool col_in = lane < R && j >= 0 && j < res;
-    // Loads of all the wave's rows first: coverage, then the map values of
-    // the covered texels (two load latencies per wave).
+    const bool col_in = lane < kFinishCols + 2 * PASSES && j >= 0 && j < res;
+    uint8_t* const rgb8 = As.out_rgb8;
+    if (threadIdx.x < 2) s_n[threadIdx.x] = 0;
     int32_t t[kRows];
+    uint32_t f[kRows];
     bool cov[kRows];
 #pragma unroll
     for (int u = 0; u < kRows; ++u) {
@@ -405,32 +428,47 @@ __global__ __launch_bounds__(kFinishBlock) void finish_kernel(Batch Bt, const ui
         const int32_t i = oi + r;
         const bool in = r < R && col_in && i >= 0 && i < res;
         t[u] = in ? i * res + j : -1;
-        cov[u] = in && facemap[t[u]] != kNoFace;
-    }
-    float m0[kRows], m1[kRows], m2[kRows];
-#pragma unroll
-    for (int u = 0; u < kRows; ++u) {
-        m0[u] = 0.f;
-        m1[u] = 0.f;
-        m2[u] = 1.f;
-        if (cov[u]) {
-            m0[u] = As.out_map[3 * t[u]];
-            m1[u] = As.out_map[3 * t[u] + 1];
-            m2[u] = As.out_map[3 * t[u] + 2];
-        }
+        f[u] = facemap[max(t[u], 0)];  // no branch: the rows' loads go out together
     }
 #pragma unroll
     for (int u = 0; u < kRows; ++u) {
+        cov[u] = t[u] >= 0 && f[u] != kNoFace;
         const int r = wave + u * kFinishWaves;
         if (r >= R) break;  // wave-uniform
-        s_map[r][lane][0] = m0[u];
-        s_map[r][lane][1] = m1[u];
-        s_map[r][lane][2] = m2[u];
         const uint64_t bin = __ballot(t[u] >= 0), bcov = __ballot(cov[u]);
         if (lane == 0) {
             s_in[r] = bin;
             s_val[0][r] = bcov;
         }
+    }
+    __syncthreads();
+    float m[kRows][3];
+#pragma unroll
+    for (int u = 0; u < kRows; ++u) {
+        const int r = wave + u * kFinishWaves;
+        m[u][0] = 0.f;
+        m[u][1] = 0.f;
+        m[u][2] = 1.f;
+        if (r >= R) break;
+        uint64_t near = 0;  // uncovered texels, then their neighbours
+#pragma unroll
+        for (int d = -1; d <= 1; ++d) {
+            const int rr = min(max(r + d, 0), R - 1);
+            near |= s_in[rr] & ~s_val[0][rr];
+        }
+        near |= (near << 1) | (near >> 1);
+        if (cov[u] && (rgb8 || ((near >> lane) & 1ull))) {
+            m[u][0] = As.out_map[3 * t[u]];
+            m[u][1] = As.out_map[3 * t[u] + 1];
+            m[u][2] = As.out_map[3 * t[u] + 2];
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < kRows; ++u) {
+        const int r = wave + u * kFinishWaves;
+        if (r >= R) break;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) s_map[r][q][lane] = m[u][q];
     }
     __syncthreads();
     for (int pass = 1; pass <= PASSES; ++pass) {
@@ -443,51 +481,69 @@ __global__ __launch_bounds__(kFinishBlock) void finish_kernel(Batch Bt, const ui
             const uint64_t vu = r > 0 ? cur[r - 1] : 0ull, vc = cur[r], vd = r + 1 < R ? cur[r + 1] : 0ull;
             const uint64_t vm = vu | vc | vd;
             const uint64_t cand = (vm | (vm << 1) | (vm >> 1)) & s_in[r] & ~vc;
-            bool filled = false;
-            if ((cand >> lane) & 1ull) {
-                float sx = 0.f, sy = 0.f, sz = 0.f;
+            int at = 0;
+            if (lane == 0) {
+                nxt[r] = vc;
+                if (cand) at = atomicAdd(&s_n[pass & 1], __popcll(cand));
+            }
+            at = __builtin_amdgcn_readfirstlane(at);
+            if ((cand >> lane) & 1ull)
+                s_list[at + __popcll(cand & ((1ull << lane) - 1ull))] = (uint16_t)(r * 64 + lane);
+        }
+        __syncthreads();
+        const int todo = s_n[pass & 1];
+        if (threadIdx.x == 0) s_n[(pass & 1) ^ 1] = 0;  // read before the barrier that opened this pass
+        for (int e = threadIdx.x; e < todo; e += kFinishBlock) {
+            const int r = s_list[e] >> 6, c = s_list[e] & 63;
+            float sx = 0.f, sy = 0.f, sz = 0.f;
 #pragma unroll
-                for (int di = -1; di <= 1; ++di) {
-                    const uint64_t row = di < 0 ? vu : (di == 0 ? vc : vd);
+            for (int di = -1; di <= 1; ++di) {
+                const int ii = min(max(r + di, 0), R - 1);
+                const uint32_t has = ii == r + di ? (uint32_t)(c > 0 ? cur[ii] >> (c - 1) : cur[ii] << 1) & 7u : 0u;
 #pragma unroll
-                    for (int dj = -1; dj <= 1; ++dj) {
-                        if (di == 0 && dj == 0) continue;
-                        const int ii = r + di, jj = lane + dj;
-                        if (ii < 0 || jj < 0 || ii >= R || jj >= R) continue;
-                        if ((row >> jj) & 1ull) {
-                            sx += s_map[ii][jj][0];
-                            sy += s_map[ii][jj][1];
-                            sz += s_map[ii][jj][2];
-                        }
-                    }
-                }
-                // at least one neighbour had a value (the candidate mask)
-                const float l2 = sx * sx + sy * sy + sz * sz;
-                if (l2 > 0.f) {
-                    const float inv = 1.0f / sqrtf(l2);
-                    s_map[r][lane][0] = sx * inv;
-                    s_map[r][lane][1] = sy * inv;
-                    s_map[r][lane][2] = sz * inv;
-                    filled = true;
+                for (int dj = -1; dj <= 1; ++dj) {
+                    if (di == 0 && dj == 0) continue;
+                    const int jj = min(max(c + dj, 0), 63);
+                    const bool on = (has >> (dj + 1)) & 1u;
+                    const float x = s_map[ii][0][jj], y = s_map[ii][1][jj], z = s_map[ii][2][jj];
+                    sx += on ? x : 0.f;
+                    sy += on ? y : 0.f;
+                    sz += on ? z : 0.f;
                 }
             }
-            // texels filled in this pass are read by no one in it: the pass
-            // reads the masks of `cur` and writes those of `nxt`
-            const uint64_t bf = __ballot(filled);
-            if (lane == 0) nxt[r] = vc | bf;
+            // at least one neighbour had a value (the candidate mask)
+            const float l2 = sumsq(sx, sy, sz);
+            if (l2 > 0.f) {
+                // texels filled in this pass are read by no one in it: the
+                // pass reads the masks of `cur` and writes those of `nxt`
+                const float inv = 1.0f / sqrtf(l2);
+                s_map[r][0][c] = sx * inv;
+                s_map[r][1][c] = sy * inv;
+                s_map[r][2][c] = sz * inv;
+                atomicOr((unsigned long long*)&nxt[r], 1ull << c);
+            }
         }
         __syncthreads();
     }
-    // the tile's uncovered texels, filled or (0,0,1)
-    const bool col_tile = lane >= PASSES && lane < PASSES + kFinishTile;
+    // the tile's uncovered texels, filled or (0,0,1); every texel's bytes
+    const bool col_tile = lane >= PASSES && lane < PASSES + kFinishCols;
 #pragma unroll
     for (int u = 0; u < kRows; ++u) {
         const int r = wave + u * kFinishWaves;
-        if (r < PASSES || r >= PASSES + kFinishTile || !col_tile || t[u] < 0 || cov[u]) continue;
-        As.out_map[3 * t[u]] = s_map[r][lane][0];
-        As.out_map[3 * t[u] + 1] = s_map[r][lane][1];
-        As.out_map[3 * t[u] + 2] = s_map[r][lane][2];
-        As.out_hit[t[u]] = kUncovered;
+        if (r < PASSES || r >= PASSES + kFinishRows || !col_tile || t[u] < 0) continue;
+        const float x = s_map[r][0][lane], y = s_map[r][1][lane], z = s_map[r][2][lane];
+        if (!cov[u]) {
+            As.out_map[3 * t[u]] = x;
+            As.out_map[3 * t[u] + 1] = y;
+            As.out_map[3 * t[u] + 2] = z;
+            As.out_hit[t[u]] = kUncovered;
+        }
+        if (rgb8) {
+            const int64_t at = 3 * (int64_t)t[u];
+            rgb8[at] = rgb8_of(x);
+            rgb8[at + 1] = rgb8_of(y);
+            rgb8[at + 2] = rgb8_of(z);
+        }
     }
 }
 
@@ -496,9 +552,7 @@ __global__ __launch_bounds__(256) void rgb8_kernel(Batch Bt) {
     const AssetDev& As = Bt.A[block_asset(Bt, kGTex3, blockIdx.x, &lb)];
     const int64_t k = lb * 256 + threadIdx.x;
     if (!As.out_rgb8 || k >= 3 * (int64_t)As.res * As.res) return;
-    float c = floorf((As.out_map[k] + 1.0f) * 127.5f + 0.5f);
-    c = fminf(fmaxf(c, 0.0f), 255.0f);
-    As.out_rgb8[k] = (uint8_t)c;
+    As.out_rgb8[k] = rgb8_of(As.out_map[k]);
 }
 
 inline unsigned blocks_for(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
