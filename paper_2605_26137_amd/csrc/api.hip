@@ -203,7 +203,7 @@ int32_t make_plan(const Sizes* z, int n, uint32_t flags, Plan* P) {
         L.t_lf >= ((int64_t)1 << 31))
         return fail(BAKE_E_UNSUPPORTED, "batch too large: needs sum(n_hi_f) < 2^31 and 3 sum(res^2) < 2^32");
     L.max_hv_bits = 1;
-    while (L.max_hv_bits < 32 && ((int64_t)1 << L.max_hv_bits) <= max_hv) ++L.max_hv_bits;  // keys in [0, nhv]
+    while (L.max_hv_bits < 32 && ((int64_t)1 << L.max_hv_bits) < max_hv) ++L.max_hv_bits;  // keys in [0, nhv)
     P->sig = sig ^ (L.save ? 0x5A5Aull : 0ull);
 
     size_t off = 0;
@@ -259,13 +259,18 @@ int32_t make_plan(const Sizes* z, int n, uint32_t flags, Plan* P) {
     if (L.save) {
         const size_t items = 3 * (size_t)L.t_tex;
         L.bwd_ray = take(36 * (size_t)L.t_tex);
-        L.bwd_hterm = take(32 * (size_t)L.t_tex);
+        L.bwd_term = take(12 * items);
+        const size_t batches = (size_t)(L.t_tex / 64 + n);
+        L.bwd_pairs = take(4 * batches);
         L.bwd_k0 = take(4 * items);
         L.bwd_v0 = take(4 * items);
         L.bwd_k1 = take(4 * items);
         L.bwd_v1 = take(4 * items);
         L.bwd_hist = take(4 * 256 * (size_t)L.t_btile);
         L.bwd_sup = take(4 * 256 * (size_t)kSortPasses * (size_t)sort_super_rows(L.t_btile, n));
+        const size_t buckets = (size_t)pair_bucket((int64_t)batches, n) + 1;
+        L.bwd_bucket = take(4 * kBucketStride * buckets);  // zeroed with the rows before it
+        L.bwd_bucket_pf = take(4 * buckets);
         L.bwd_face1 = take(72 * (size_t)L.t_lf);
         L.bwd_face2 = take(36 * (size_t)L.t_lf);
         L.bwd_sbar = take(12 * (size_t)L.t_lv);

@@ -15,8 +15,9 @@
 //     normalisation and the face cross products are differentiated, and a
 //     second gather finishes dL/dlo_V;
 //   * high-poly: each hit ray contributes beta_k h_bar to the three vertices
-//     of its triangle; the (vertex, ray*3 + corner) pairs are radix-sorted
-//     stably and each vertex sums its run in ray order.
+//     of its triangle; a wave adds the terms its 64 rays have for a vertex, the
+//     (vertex, place of the sum) pairs are radix-sorted stably and each vertex
+//     adds its run in ray order.
 // No floating-point atomics: the result is bitwise reproducible.  In a batch
 // the per-ray kernels take (asset, 64-ray batch) items like the traversal,
 // and the reductions stay inside each asset's ranges.
@@ -53,14 +54,6 @@ struct RayGrad {  // 36 B per ray: what the low-poly chain needs
     float3 pb, mb, tfb;
 };
 
-// What the high-poly sums need of a ray, in one 32-B record: h_bar and the
-// hit weights beta1, beta2 (beta0 = 1 - beta1 - beta2).
-struct alignas(16) HiTerm {
-    float4 a;  // h_bar.xyz, beta1
-    float4 b;  // beta2, -, -, -
-};
-static_assert(sizeof(HiTerm) == 32, "HiTerm is 32 B");
-
 // The (asset, 64-ray batch) item q: the asset and the wave's global ray
 // (invalid when past the asset's rays).
 struct RayItem {
@@ -82,36 +75,148 @@ __device__ __forceinline__ RayItem ray_item(const Batch& B, uint32_t q, int lane
     return it;
 }
 
-// Per-ray adjoint.  Also emits the three (hi vertex, item) sort pairs of the
-// ray; rays without a hit emit the out-of-range key nhv.
-__global__ __launch_bounds__(256) void bwd_ray_kernel(Batch B, const Ray* __restrict__ rays,
-                                                      const Hit* __restrict__ hits,
-                                                      const float4* __restrict__ lo_n_all,
-                                                      const float4* __restrict__ face_t_all,
-                                                      RayGrad* __restrict__ rg, HiTerm* __restrict__ ht,
-                                                      uint32_t* __restrict__ keys, uint32_t* __restrict__ vals) {
+// A wave's rays meet a high-poly vertex several times: its 192 (vertex, ray)
+// terms go to a table in LDS, and each vertex leaves as one pair of its index and
+// its sum.
+constexpr int kMergeSlots = 256;
+constexpr uint32_t kNoVertex = 0xFFFFFFFFu;
+struct MergeLds {
+    float4 rec[64][2];             // h_bar.xyz, beta1 | corners 0-2, beta2
+    uint64_t rays[kMergeSlots];    // the slot's rays, a bit each
+    uint32_t vertex[kMergeSlots];
+    uint8_t list[192];             // slots in use
+};
+
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Which vertex a slot holds depends on the order of the insertions, the sums do
+// not: a vertex's rays are added in ascending order, those of a slot that more
+// than one lane shares (few vertices) by stride and then in a fixed tree.
+// Returns the number of pairs; the table is left empty.
+__device__ __forceinline__ int merge_pairs(MergeLds& S, int lane, bool hit, const int32_t j[3], float3 hb, float be1,
+                                           float be2, uint32_t* __restrict__ keys, float* __restrict__ terms) {
+    if (hit) {
+        S.rec[lane][0] = make_float4(hb.x, hb.y, hb.z, be1);
+        S.rec[lane][1] = make_float4(__int_as_float(j[0]), __int_as_float(j[1]), __int_as_float(j[2]), be2);
+        uint32_t slot[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) slot[k] = ((uint32_t)j[k] * 2654435761u) >> 24;
+        bool more = true;
+        while (more) {  // at most 192 vertices: there is a free slot.  A settled corner finds its own
+            uint32_t was[3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) was[k] = atomicCAS(&S.vertex[slot[k]], kNoVertex, (uint32_t)j[k]);
+            more = false;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const bool taken = was[k] != kNoVertex && was[k] != (uint32_t)j[k];
+                slot[k] = (slot[k] + (taken ? 1u : 0u)) & (kMergeSlots - 1);
+                more = more || taken;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) atomicOr((unsigned long long*)&S.rays[slot[k]], 1ull << lane);
+    }
+    wave_sync();
+    int n = 0;
+#pragma unroll
+    for (int c = 0; c < kMergeSlots; c += 64) {
+        const uint64_t used = __ballot(S.vertex[c + lane] != kNoVertex);
+        if ((used >> lane) & 1ull) S.list[n + __popcll(used & __lanemask_lt())] = (uint8_t)(c + lane);
+        n += __popcll(used);
+    }
+    wave_sync();
+    const int l2 = n > 32 ? 0 : (n > 16 ? 1 : (n > 8 ? 2 : (n > 4 ? 3 : (n > 2 ? 4 : (n > 1 ? 5 : 6)))));  // lanes a slot
+    const uint64_t every[7] = {~0ull,                  0x5555555555555555ull, 0x1111111111111111ull, 0x0101010101010101ull,
+                               0x0001000100010001ull, 0x0000000100000001ull, 1ull};
+    uint64_t mine = 0;
+#pragma unroll
+    for (int k = 0; k < 7; ++k)
+        if (l2 == k) mine = every[k];
+    const int part = lane & ((1 << l2) - 1);
+    mine <<= part;
+    for (int s0 = 0; s0 < n; s0 += 64 >> l2) {
+        const int s = s0 + (lane >> l2);
+        const bool on = s < n;
+        const int slot = on ? S.list[s] : 0;
+        const uint32_t v = S.vertex[slot];
+        uint64_t m = on ? S.rays[slot] & mine : 0ull;
+        float3 g = f3(0.f, 0.f, 0.f);
+        while (m) {
+            const int r = __ffsll((long long)m) - 1;
+            m &= m - 1;
+            const float4 a = S.rec[r][0], b = S.rec[r][1];
+            // a corner's weight (a face may name a vertex twice)
+            const float w = (__float_as_uint(b.x) == v ? 1.0f - a.w - b.w : 0.f) +
+                            (__float_as_uint(b.y) == v ? a.w : 0.f) + (__float_as_uint(b.z) == v ? b.w : 0.f);
+            g = add3(g, mul3(f3(a.x, a.y, a.z), w));
+        }
+        for (int o = 1; o < 1 << l2; o <<= 1)
+            g = add3(g, f3(__shfl_xor(g.x, o, 64), __shfl_xor(g.y, o, 64), __shfl_xor(g.z, o, 64)));
+        if (on && part == 0) {
+            keys[s] = v;
+            st3(terms, s, g);
+            S.vertex[slot] = kNoVertex;
+            S.rays[slot] = 0;
+        }
+    }
+    wave_sync();
+    return n;
+}
+
+// Per-ray adjoint.  A batch's merged (high-poly vertex, sum) pairs go to keys and
+// terms from three times its first ray on, their number to pairs[batch] and into
+// its bucket's.
+//
+// Bound by memory (rays, hits and the gathered corners in, 36 B of low-poly
+// terms out), which hides the merging.  A dense mesh has some forty vertices
+// under a wave's rays, so that a fifth of the pairs is left to sort and to add
+// up: at 1.9M rays on 655k vertices the sort 139 -> 85 us, bwd_hiN_kernel
+// 44 -> 20 and this kernel 50 -> 48 (it wrote 56 B per ray for the pairs), at 7.8M
+// rays on 2.6M vertices this kernel 202 -> 179 and bwd_hiN_kernel 169 -> 61.
+struct RayArgs {
+    Batch B;
+    const Ray* rays;
+    const Hit* hits;
+    const float4 *lo_n, *face_t;
+    RayGrad* rg;
+    float* terms;
+    uint32_t *keys, *pairs, *bucket;
+};
+
+__global__ __launch_bounds__(256) void bwd_ray_kernel(RayArgs p) {
+    __shared__ MergeLds lds[4];
+    const Batch& B = p.B;
     if (!sealed(B)) return;
     const int lane = threadIdx.x & 63;
+    MergeLds& S = lds[threadIdx.x >> 6];
+    for (int c = lane; c < kMergeSlots; c += 64) {
+        S.vertex[c] = kNoVertex;
+        S.rays[c] = 0;
+    }
+    wave_sync();
     const uint32_t nb = B.rb_pf[B.n];
     const uint32_t waves = gridDim.x * 4u;
     for (uint32_t q = __builtin_amdgcn_readfirstlane(blockIdx.x * 4u + (threadIdx.x >> 6)); q < nb;
          q += waves) {
         const RayItem it = ray_item(B, q, lane);
-        if (!it.valid) continue;
         const AssetDev& As = B.A[it.a];
         const int64_t r = it.r;
-        const int64_t nhv = As.nhv;
-        const Ray ray = rays[r];
-        const Hit hit = hits[r];
+        const int64_t first = it.begin + 64 * (int64_t)(q - B.rb_pf[it.a]);
+        const Ray ray = p.rays[it.valid ? r : first];
+        const Hit hit = p.hits[it.valid ? r : first];
         RayGrad g;
         g.pb = g.mb = g.tfb = f3(0.f, 0.f, 0.f);
-        HiTerm term;
-        term.a = make_float4(0.f, 0.f, 0.f, 0.f);
-        term.b = make_float4(0.f, 0.f, 0.f, 0.f);
-        uint32_t kv[3] = {(uint32_t)nhv, (uint32_t)nhv, (uint32_t)nhv};
+        float3 hb = f3(0.f, 0.f, 0.f);
+        int32_t jv[3] = {0, 0, 0};
         const float* grad_map = B.G[it.a].grad_map;  // NULL: the asset wants no gradient
-        if (hit.id >= 0 && grad_map) {
-            const float4* lo_n = lo_n_all + As.lv;
+        const bool on = it.valid && hit.id >= 0 && grad_map;
+        if (on) {
+            const float4* lo_n = p.lo_n + As.lv;
             const int32_t* lo_F = As.lo_F;
             const int32_t* hi_F = As.hi_F;
             const float* hi_V = As.hi_V;
@@ -124,7 +229,7 @@ __global__ __launch_bounds__(256) void bwd_ray_kernel(Batch B, const Ray* __rest
                                 b0 * n0.z + b1 * n1.z + b2 * n2.z);
             const float lm = sqrtf(dot3(m, m));
             const float3 d = mul3(m, 1.0f / lm);
-            const float4 T4 = face_t_all[As.lf + f];
+            const float4 T4 = p.face_t[As.lf + f];
             const float3 Tf = f3(T4.x, T4.y, T4.z);
             const float H = T4.w;
             const float3 Tt = sub3(Tf, mul3(d, dot3(d, Tf)));
@@ -149,7 +254,7 @@ __global__ __launch_bounds__(256) void bwd_ray_kernel(Batch B, const Ray* __rest
             const float3 Tfb = sub3(Ttb, mul3(d, dot3(d, Ttb)));
             db = sub3(db, add3(mul3(Ttb, dot3(d, Tf)), mul3(Tf, dot3(d, Ttb))));
             // n = h/|h|; h = sum beta_k N_k
-            const float3 hb = unit_adj(nb3, n, lh);
+            hb = unit_adj(nb3, n, lh);
             const float bb1 = dot3(hb, sub3(N1, N0)), bb2 = dot3(hb, sub3(N2, N0));
             // M (t, beta1, beta2) = p - A with M = [-d | e1 | e2]:  w = M^-T (0, bb1, bb2),
             // by Cramer on M^T (columns = the rows of M)
@@ -164,18 +269,18 @@ __global__ __launch_bounds__(256) void bwd_ray_kernel(Batch B, const Ray* __rest
             g.pb = w;
             g.mb = unit_adj(db, d, lm);
             g.tfb = Tfb;
-            term.a = make_float4(hb.x, hb.y, hb.z, be1);
-            term.b = make_float4(be2, 0.f, 0.f, 0.f);
-            kv[0] = (uint32_t)j0;
-            kv[1] = (uint32_t)j1;
-            kv[2] = (uint32_t)j2;
+            jv[0] = j0;
+            jv[1] = j1;
+            jv[2] = j2;
         }
-        rg[r] = g;
-        ht[r] = term;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            keys[3 * r + k] = kv[k];
-            vals[3 * r + k] = (uint32_t)(3 * r + k);
+        if (it.valid) p.rg[r] = g;
+        int n = 0;
+        if (B.G[it.a].grad_hi_N)
+            n = merge_pairs(S, lane, on, jv, hb, hit.beta1, hit.beta2, p.keys + 3 * first, p.terms + 9 * first);
+        if (lane == 0) {
+            p.pairs[q] = (uint32_t)n;
+            const uint32_t q0 = B.rb_pf[it.a];
+            if (n && p.bucket) atomicAdd(&p.bucket[kBucketStride * (pair_bucket(q0, it.a) + (q - q0) / kPairBucket)], (uint32_t)n);
         }
     }
 }
@@ -346,60 +451,60 @@ __global__ __launch_bounds__(256) void zero_grad_hi_kernel(Batch B) {
     st3(out, v, f3(0.f, 0.f, 0.f));
 }
 
-// The term of sorted pair j: the hit's barycentric weight of corner k times
-// the ray's adjoint of the interpolated high-poly normal (item = 3 ray + k).
-__device__ __forceinline__ float3 hiN_term(const uint32_t* __restrict__ vals, const HiTerm* __restrict__ ht,
-                                           int64_t j) {
-    const uint32_t item = vals[j];
-    const uint32_t r = item / 3, k = item - 3 * r;
-    const HiTerm h = ht[r];
-    const float beta = k == 0 ? 1.0f - h.a.w - h.b.x : (k == 1 ? h.a.w : h.b.x);
-    return mul3(f3(h.a.x, h.a.y, h.a.z), beta);
-}
-
-// Sorted (vertex, item) pairs of an asset, 64 at a time per wave: each lane
-// forms its pair's term, a segmented scan over the wave adds the terms of
-// each vertex's run (items ascending within a run: the sort is stable) in a
-// fixed tree order, and the lane at the run's end writes the sum.  A run
+// Sorted (vertex, place of its sum) pairs of an asset, 64 at a time per wave:
+// each lane takes its pair's sum, a segmented scan over the wave adds those of
+// each vertex's run (places ascending within a run: the sort is stable) in a
+// fixed tree order, and the lane at the run's end writes the total.  A run
 // that goes on past the wave's 64 pairs is finished by the whole wave, the
 // next 256 pairs at a time (each 64 summed in a fixed tree, the four sums
 // added in pair order); the waves holding the rest skip it.  Bound by the
-// latency of the gathered terms, so a long run (many texels per high-poly
-// vertex) must not be one lane's chain: walked by its last lane alone, ten
-// uneven assets with up to some hundred pairs a vertex took 1,136 us, this way
-// 251 us; 1.08M rays on 655k vertices 48 -> 45 us.  Waves take (asset,
-// 64-ray batch) items: 192 pairs each.
+// latency of the gathered sums.  A run walked by its last lane alone, with up to
+// some hundred terms a vertex, took 1,136 us over ten uneven assets; by the whole
+// wave 249, with the terms of a wave's rays merged before the sort 49.  Waves take
+// 256 pairs at a time.
+constexpr int kHiGroups = 4;
 __global__ __launch_bounds__(256) void bwd_hiN_kernel(Batch B, const uint32_t* __restrict__ keys,
                                                       const uint32_t* __restrict__ vals,
-                                                      const HiTerm* __restrict__ ht) {
+                                                      const float* __restrict__ terms) {
     if (!sealed(B)) return;
     const int lane = threadIdx.x & 63;
-    const uint32_t nb = B.rb_pf[B.n];
+    constexpr uint32_t kPer = kSortTile / (64 * kHiGroups);  // items of a sort tile
+    const uint32_t nb = kPer * B.gcnt[kGcBwdTiles];
     const uint32_t waves = gridDim.x * 4u;
     for (uint32_t q = __builtin_amdgcn_readfirstlane(blockIdx.x * 4u + (threadIdx.x >> 6)); q < nb;
          q += waves) {
-        const RayItem it = ray_item(B, q, 0);
-        float* grad_hi_N = B.G[it.a].grad_hi_N;
+        const int a = upper_asset(B.bt_pf, B.n, q / kPer);
+        float* grad_hi_N = B.G[a].grad_hi_N;
         if (!grad_hi_N) continue;
-        const uint32_t nhv = (uint32_t)B.A[it.a].nhv;
-        const int64_t lo = 3 * it.begin, hi = 3 * it.end;
-        // the three 64-pair groups' loads first (keys, items, then each
-        // item's hit and ray gradient), so their latencies overlap; the
-        // scans below are unchanged
-        uint32_t keyv[3];
-        float3 gv[3];
-        bool contv[3];
+        const uint32_t nhv = (uint32_t)B.A[a].nhv;
+        const int64_t lo = 3 * (int64_t)B.ray_pf[a], hi = lo + B.cnt[(int64_t)a * kCntSlots + kCntPairs];
+        const int64_t first = lo + 64 * kHiGroups * (int64_t)(q - kPer * B.bt_pf[a]);
+        if (first >= hi) continue;
+        // the groups' loads first (keys and places, then the sums), so their
+        // latencies overlap
+        uint32_t keyv[kHiGroups], place[kHiGroups];
+        float3 gv[kHiGroups];
+        bool contv[kHiGroups];
 #pragma unroll
-        for (int k3 = 0; k3 < 3; ++k3) {
-            const int64_t i0 = 3 * it.r + 64 * k3;
-            const int64_t i = i0 + lane;
-            const bool in = i < hi;  // false for every lane past the batch's pairs
-            keyv[k3] = in ? keys[i] : 0xFFFFFFFFu;  // past the end: a run of its own
-            gv[k3] = in ? hiN_term(vals, ht, i) : f3(0.f, 0.f, 0.f);
-            contv[k3] = i0 < hi && i0 > lo && keys[i0 - 1] == keys[i0];
+        for (int k = 0; k < kHiGroups; ++k) {
+            const int64_t i = min(first + 64 * k + lane, hi - 1);
+            keyv[k] = keys[i];
+            place[k] = vals[i];
         }
-        for (int k3 = 0; k3 < 3; ++k3) {
-            const int64_t i0 = 3 * it.r + 64 * k3;  // the wave's first pair
+        const uint32_t before = first > lo ? keys[first - 1] : kNoVertex;
+#pragma unroll
+        for (int k = 0; k < kHiGroups; ++k) {
+            gv[k] = ld3(terms, place[k]);
+            if (first + 64 * k + lane >= hi) keyv[k] = kNoVertex;  // past the end: a run of its own
+        }
+#pragma unroll
+        for (int k = 0; k < kHiGroups; ++k) {
+            const uint32_t last = k > 0 ? (uint32_t)__builtin_amdgcn_readlane((int)keyv[k > 0 ? k - 1 : 0], 63) : before;
+            contv[k] = last == (uint32_t)__builtin_amdgcn_readfirstlane((int)keyv[k]);
+        }
+#pragma unroll
+        for (int k3 = 0; k3 < kHiGroups; ++k3) {
+            const int64_t i0 = first + 64 * k3;  // the wave's first pair
             if (i0 >= hi) break;
             const int64_t i = i0 + lane;
             const bool in = i < hi;
@@ -438,7 +543,7 @@ __global__ __launch_bounds__(256) void bwd_hiN_kernel(Batch B, const uint32_t* _
                 }
 #pragma unroll
                 for (int u = 0; u < 4; ++u)  // sorted: once a pair differs, so does every later one
-                    t[u] = kj[u] == last ? hiN_term(vals, ht, j0 + 64 * u + lane) : f3(0.f, 0.f, 0.f);
+                    t[u] = kj[u] == last ? ld3(terms, vals[j0 + 64 * u + lane]) : f3(0.f, 0.f, 0.f);
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     const uint64_t same = __ballot(kj[u] == last);
@@ -553,16 +658,18 @@ hipError_t launch_backward(const BatchHost& H, bool any_lo, bool any_hi, hipStre
     const Ray* rays = (const Ray*)(ws + L.rays);
     const Hit* hits = (const Hit*)(ws + L.hits);
     RayGrad* rg = (RayGrad*)(ws + L.bwd_ray);
-    HiTerm* ht = (HiTerm*)(ws + L.bwd_hterm);
+    float* terms = (float*)(ws + L.bwd_term);
     // persistent waves over the (asset, 64-ray batch) items: enough for the
     // largest possible ray count, capped
     int64_t cap_batches = 0;
     for (int a = 0; a < L.n; ++a) cap_batches += ((int64_t)H.A[a].res * H.A[a].res + 63) / 64;
     const unsigned ray_grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((cap_batches + 3) / 4, 4096));
     if (L.t_tex > 0) {
-        hipLaunchKernelGGL(bwd_ray_kernel, dim3(ray_grid), dim3(256), 0, s, H.dev, rays, hits,
-                           (const float4*)(ws + L.lo_n), (const float4*)(ws + L.face_t), rg, ht,
-                           (uint32_t*)(ws + L.bwd_k0), (uint32_t*)(ws + L.bwd_v0));
+        RayArgs r = {H.dev, rays, hits, (const float4*)(ws + L.lo_n), (const float4*)(ws + L.face_t), rg, terms,
+                     (uint32_t*)(ws + L.bwd_k1), (uint32_t*)(ws + L.bwd_pairs),
+                     pairs_in_one(H) ? nullptr : (uint32_t*)(ws + L.bwd_bucket)};
+        hipLaunchKernelGGL(bwd_ray_kernel, dim3(ray_grid), dim3(256), 0, s, r);
+        if (any_hi && !pairs_in_one(H) && (e = launch_pair_table(H, s)) != hipSuccess) return e;
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     // the low-poly and high-poly gradients only share the per-ray adjoint:
@@ -620,7 +727,7 @@ hipError_t launch_backward(const BatchHost& H, bool any_lo, bool any_hi, hipStre
             if (beside && (e = hipStreamWaitEvent(s, join, 0)) != hipSuccess) return e;
             hipLaunchKernelGGL(bwd_hiN_kernel, dim3(ray_grid), dim3(256), 0, s, H.dev,
                                (const uint32_t*)(ws + (in1 ? L.bwd_k1 : L.bwd_k0)),
-                               (const uint32_t*)(ws + (in1 ? L.bwd_v1 : L.bwd_v0)), (const HiTerm*)ht);
+                               (const uint32_t*)(ws + (in1 ? L.bwd_v1 : L.bwd_v0)), (const float*)terms);
             if ((e = hipGetLastError()) != hipSuccess) return e;
         }
     }

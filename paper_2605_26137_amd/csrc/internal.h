@@ -189,6 +189,7 @@ __host__ __device__ inline int64_t join_rows(int64_t tiles, int64_t n, int level
 
 // Per-asset counter slots.
 constexpr int kCntRays = 0;      // covered texels (rays)
+constexpr int kCntPairs = 1;     // backward: merged (vertex, sum) pairs
 constexpr int kCntBoxLo = 2;     // u64 box tests (FLAG_COUNT), slots 2-3
 constexpr int kCntTriLo = 4;     // u64 triangle tests (FLAG_COUNT), slots 4-5
 constexpr int kCntIterLo = 8;    // u64 traversal loop trips of whole waves (FLAG_COUNT), slots 8-9
@@ -196,7 +197,7 @@ constexpr int kCntSlots = 16;
 // Batch counter slots.
 constexpr int kGcQueue = 0;  // traversal work queue head
 constexpr int kGcSeal = 1;   // nonce of the last forward with BAKE_FLAG_SAVE (written as it starts; 0 after one without)
-constexpr int kGcBwdTiles = 2;  // backward sort tiles that hold pairs, over the batch (written after the raster)
+constexpr int kGcBwdTiles = 2;  // backward sort tiles that hold pairs, over the batch (written by the backward)
 constexpr int kXcds = 8;         // XCDs of an MI355X: each has its own L2
 constexpr int kXcdStride = 32;   // one 128-byte line per XCD queue head
 constexpr int kGcXcdQueue = 32;  // kXcds traversal queue heads, kXcdStride apart
@@ -209,13 +210,21 @@ struct Batch {
     const int32_t* gpf;     // [kGridCount][n + 1] block prefix of each grid
     const uint32_t* ray_pf; // [n + 1] first ray of each asset (written after the raster)
     const uint32_t* rb_pf;  // [n + 1] 64-ray batches before each asset
-    const uint32_t* bt_pf;  // [n + 1] backward sort tiles holding pairs before each asset (after the raster)
+    const uint32_t* bt_pf;  // [n + 1] backward sort tiles holding pairs before each asset (written by the backward)
     uint32_t* cnt;          // [n][kCntSlots]
     uint32_t* gcnt;         // [kGcSlots]
     uint32_t* status;       // status word, OR over the batch
     int n;
     uint32_t seal;          // backward: the nonce the saved forward left in gcnt[kGcSeal]
 };
+
+// Merged pairs of the backward, per 64-ray batch and in sums over kPairBucket
+// of an asset's batches (asset a's sums start at pair_bucket(rb_pf[a], a)).  A sum
+// has a cache line to itself: 30,000 waves adding into 120 sums of one word each
+// took 85 us.
+constexpr int kPairBucket = 256;
+constexpr int kBucketStride = 32;
+__host__ __device__ inline int64_t pair_bucket(int64_t batch, int64_t a) { return batch / kPairBucket + a; }
 
 // Backward kernels run only on the state of the forward they were planned
 // for: anything else (a workspace reused since) makes them do nothing.
@@ -299,7 +308,7 @@ struct Layout {
     size_t nodes_c, leaves, items, item_cnt;      // tree; lists of waiting subtrees
     size_t spill;                                 // traversal stack spill
     // backward scratch (BAKE_FLAG_SAVE only)
-    size_t bwd_ray, bwd_hterm, bwd_k0, bwd_v0, bwd_k1, bwd_v1, bwd_hist, bwd_sup, bwd_face1, bwd_face2, bwd_sbar,
+    size_t bwd_ray, bwd_term, bwd_pairs, bwd_bucket, bwd_bucket_pf, bwd_k0, bwd_v0, bwd_k1, bwd_v1, bwd_hist, bwd_sup, bwd_face1, bwd_face2, bwd_sbar,
         bwd_vbar;
     size_t total;
     // batch totals
@@ -351,6 +360,8 @@ hipError_t write_table(void* dst, const void* src, size_t bytes, hipStream_t s, 
                        int64_t zero_words = 0, int64_t set_idx = -1, uint32_t set_val = 0);
 // The backward sort's super-tile rows, which its caller zeroes before the sort.
 int64_t bwd_sort_zero_words(const Layout& L);
+bool pairs_in_one(const BatchHost& H);
+hipError_t launch_pair_table(const BatchHost& H, hipStream_t s);
 
 // Per-asset ray starts, 64-ray batch prefix and backward sort tile prefix
 // (after the raster).
@@ -359,7 +370,8 @@ hipError_t launch_ray_spaces(const BatchHost& H, hipStream_t s);
 // Stable LSD radix sort of every asset's (key, value) pairs on the low `bits`
 // bits, 8 per pass, ping-ponging between the two buffers of the sort:
 // kSortBvh: the Morton keys (keys0/vals0 <-> keys1/vals1); kSortBwd: the
-// backward pairs (bwd_k0/bwd_v0 <-> bwd_k1/bwd_v1), three per ray.
+// merged backward pairs (bwd_k0/bwd_v0 <-> bwd_k1/bwd_v1; the keys that bwd_ray
+// left in bwd_k1, batch by batch, are drawn together by the first pass).
 // *result_in_1 tells which buffer holds the result (the same for all assets).
 enum SortWhich : int { kSortBvh = 0, kSortBwd = 1 };
 // after_first: if not null, recorded on s once the first pass's histogram is

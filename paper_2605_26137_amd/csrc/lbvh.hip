@@ -28,6 +28,7 @@ constexpr int kBlock = 256;
 constexpr int kSortBlock = 1024;                     // sort workgroups: 16 waves
 constexpr int kSortRounds = kSortTile / kSortBlock;  // 4 keys per thread and pass
 constexpr int kSortWaves = kSortBlock / 64;
+constexpr int kBwdSortGrid = 1024;                   // two workgroups a CU, twice
 constexpr float kLeafEps = 1.0f / 16384.0f;  // edge tolerance of the hit rule (traverse.hip)
 
 __device__ __forceinline__ int3 tri_idx(const int32_t* __restrict__ F, int64_t g, int64_t nv,
@@ -199,16 +200,14 @@ __global__ __launch_bounds__(kBlock) void morton_kernel(Batch Bt, const float* _
 // The tile of a sort block: its asset's keys [start, start + count) in the
 // concatenated arrays, its count row (hbase + 256 lt), its super-tile rows
 // (from sbase; an asset's super-tiles start at tile_base / kSuper + asset,
-// which keeps assets apart) and its local tile lt.  BWD: the backward pairs,
-// whose count lives on the device (three per ray), with tiles sized for the
-// capacity 3 res^2.
+// which keeps assets apart) and its local tile lt.  BWD: the backward's merged
+// pairs, whose count lives on the device, with rows sized for the capacity
+// 3 res^2.
 struct SortTile {
     int64_t start, count, hbase, sbase, lt;
 };
 
-// BWD blocks map onto the tiles that hold pairs (the prefix the forward wrote
-// after its raster); the grid covers the capacity, and its blocks past the
-// pairs' tiles have exited already (bwd_block_idle).
+// BWD blocks share out the tiles that hold pairs.
 template <bool BWD>
 __device__ __forceinline__ SortTile sort_tile(const Batch& Bt, int64_t blk) {
     SortTile T;
@@ -223,7 +222,7 @@ __device__ __forceinline__ SortTile sort_tile(const Batch& Bt, int64_t blk) {
     const int64_t tile_base = BWD ? As.btile : As.stile;
     if (BWD) {
         T.start = 3 * (int64_t)Bt.ray_pf[a];
-        T.count = 3 * (int64_t)Bt.cnt[(int64_t)a * kCntSlots + kCntRays];
+        T.count = Bt.cnt[(int64_t)a * kCntSlots + kCntPairs];
     } else {
         T.start = As.hf;
         T.count = As.nhf;
@@ -233,40 +232,178 @@ __device__ __forceinline__ SortTile sort_tile(const Batch& Bt, int64_t blk) {
     return T;
 }
 
-// A backward sort block with nothing to do: a workspace no longer holding the
-// saved forward, or a block past the tiles that hold pairs.  Both words lie
-// in one line of the batch counters, so an idle block exits after one load
-// latency.
-__device__ __forceinline__ bool bwd_block_idle(const Batch& Bt) {
-    return !sealed(Bt) || blockIdx.x >= Bt.gcnt[kGcBwdTiles];
+// Tiles of a launch: block b takes b, b + gridDim.x, ...  The backward's are known
+// on the device only, and a workspace that no longer holds the saved forward has
+// none.
+template <bool BWD>
+__device__ __forceinline__ int64_t sort_tiles(const Batch& Bt) {
+    if (!BWD) return gridDim.x;
+    return sealed(Bt) ? Bt.gcnt[kGcBwdTiles] : 0;
 }
 
+// The thread's index, formed anew for each tile: what follows from it is not worth
+// the registers from one tile to the next (two workgroups a CU leave 64).
 template <bool BWD>
-__global__ __launch_bounds__(kSortBlock) void radix_hist_kernel(Batch Bt, const uint32_t* __restrict__ keys,
-                                                                int shift, uint32_t* __restrict__ hist,
-                                                                uint32_t* __restrict__ sup) {
-    __shared__ uint32_t h[256];
-    if (BWD && bwd_block_idle(Bt)) return;
-    const SortTile T = sort_tile<BWD>(Bt, blockIdx.x);
-    if (T.lt * kSortTile >= T.count) return;  // an empty capacity tile (uniform)
-    if (threadIdx.x < 256) h[threadIdx.x] = 0;
-    __syncthreads();
-    const int64_t base = T.lt * kSortTile;
-    // all rounds' keys are loaded before the first count (one load latency)
-    uint32_t k[kSortRounds];
-#pragma unroll
-    for (int r = 0; r < kSortRounds; ++r) {
-        const int64_t i = base + (int64_t)r * kSortBlock + threadIdx.x;
-        k[r] = i < T.count ? keys[T.start + i] : 0u;
+__device__ __forceinline__ int tile_thread() {
+    int t = threadIdx.x;
+    if (BWD) asm volatile("" : "+v"(t));
+    return t;
+}
+
+// The keys of the backward's first pass lie batch by batch, each batch's at three
+// times its first ray.  Draws tile T's together into kout, with their places as
+// values, and counts their digits in h.  A batch has some forty of 192: the
+// bucket that holds the tile's first pair comes from the buckets' prefix, the
+// batches from there on are summed 1,024 at a time, and a wave copies a batch.
+// ONE: an asset by itself of at most 1,024 batches, which this launch sums
+// without buckets; its first block writes what pair_table_kernel would.  Returns
+// whether the tile has pairs.
+template <bool ONE>
+__device__ __forceinline__ bool gather_pairs(const Batch& Bt, const SortTile& T, int a, int shift,
+                                             const uint32_t* __restrict__ sparse,
+                                             const uint32_t* __restrict__ pairs,
+                                             const uint32_t* __restrict__ bucket, uint32_t* __restrict__ kout,
+                                             uint32_t* __restrict__ vout, uint32_t* __restrict__ bt_pf,
+                                             uint32_t* h) {
+    __shared__ uint32_t s_at[kSortBlock], s_n[kSortBlock], s_w[kSortWaves];
+    const int tid = tile_thread<true>(), lane = tid & 63, wave = tid >> 6;
+    const int64_t q0 = Bt.rb_pf[a], nb = Bt.rb_pf[a + 1] - q0, nk = ceil_div(nb, kPairBucket);
+    const uint32_t* __restrict__ pre = bucket + pair_bucket(q0, a);
+    const uint32_t e0 = (uint32_t)(T.lt * kSortTile);
+    uint32_t e1 = ONE ? e0 + 1 : (uint32_t)min((int64_t)e0 + kSortTile, T.count);
+    int64_t k = -1;  // the last bucket that starts at or before e0
+    uint32_t base = 0;
+    if (ONE) {
+        k = 0;
+    } else {
+        const uint32_t zero = pre[0];
+        for (int64_t c = 0; c < nk; c += kSortBlock) {
+            const int m = __syncthreads_count(c + tid < nk && pre[min(c + tid, nk - 1)] - zero <= e0);
+            k += m;
+            if (m < kSortBlock) break;
+        }
+        base = pre[k] - zero;
     }
+    for (int64_t b0 = k * kPairBucket; base < e1 && b0 < nb; b0 += kSortBlock) {
+        const uint32_t n = b0 + tid < nb ? pairs[q0 + b0 + tid] : 0u;
+        uint32_t x = n;
 #pragma unroll
-    for (int r = 0; r < kSortRounds; ++r)
-        if (base + (int64_t)r * kSortBlock + threadIdx.x < T.count) atomicAdd(&h[(k[r] >> shift) & 255u], 1u);
-    __syncthreads();
-    if (threadIdx.x < 256) {
-        const uint32_t c = h[threadIdx.x];
-        hist[T.hbase + 256 * T.lt + threadIdx.x] = c;
-        if (c) atomicAdd(&sup[T.sbase + 256 * (T.lt / kSuper) + threadIdx.x], c);
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t y = __shfl_up(x, o, 64);
+            if (lane >= o) x += y;
+        }
+        __syncthreads();
+        if (lane == 63) s_w[wave] = x;
+        __syncthreads();
+        uint32_t all = 0;
+#pragma unroll 4
+        for (int w = 0; w < kSortWaves; ++w) {
+            const uint32_t y = s_w[w];
+            if (w < wave) x += y;
+            all += y;
+        }
+        if (ONE) {
+            if (T.lt == 0 && tid == 0) {
+                const uint32_t nt = (all + kSortTile - 1) / kSortTile;
+                Bt.cnt[kCntPairs] = all;
+                Bt.gcnt[kGcBwdTiles] = nt;
+                bt_pf[0] = 0;
+                bt_pf[1] = nt;
+            }
+            if (e0 >= all) return false;
+            e1 = min(e0 + kSortTile, all);
+        }
+        x += base - n;
+        s_at[tid] = x;
+        s_n[tid] = n;
+        const int j0 = __syncthreads_count(x + n <= e0), j1 = __syncthreads_count(x < e1);
+        constexpr int kU = 2;
+        for (int j = j0 + wave; j < j1; j += kU * kSortWaves) {
+            uint32_t key[kU];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                const int ju = min(j + u * kSortWaves, kSortBlock - 1);
+                const bool on = j + u * kSortWaves < j1 && lane < (int)s_n[ju];
+                key[u] = sparse[T.start + (on ? 192 * (b0 + ju) + lane : 0)];
+            }
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                const int ju = j + u * kSortWaves;
+                if (ju >= j1) break;
+                const uint32_t at = s_at[ju];
+                const int m = (int)s_n[ju];
+                const int64_t from = T.start + 192 * (b0 + ju);
+#pragma unroll 1
+                for (int i = lane; i < m; i += 64) {
+                    const uint32_t e = at + (uint32_t)i;
+                    if (e < e0 || e >= e1) continue;
+                    const uint32_t v = i < 64 ? key[u] : sparse[from + i];
+                    kout[T.start + e] = v;
+                    vout[T.start + e] = (uint32_t)(from + i);
+                    atomicAdd(&h[(v >> shift) & 255u], 1u);
+                }
+            }
+        }
+        base += all;
+        if (ONE) break;
+    }
+    return true;
+}
+
+enum SortKeys : int { kSortBvhKeys = 0, kSortPairs = 1, kSortPairsFirst = 2, kSortPairsOne = 3 };
+
+struct HistArgs {
+    Batch B;
+    const uint32_t* keys;
+    int shift;
+    uint32_t *hist, *sup;
+    // first pass of the backward: see gather_pairs
+    const uint32_t *pairs, *bucket;
+    uint32_t *kout, *vout, *bt_pf;
+};
+
+template <int WHICH>
+__global__ __launch_bounds__(kSortBlock) __attribute__((amdgpu_waves_per_eu(8))) void radix_hist_kernel(HistArgs p) {
+    constexpr bool BWD = WHICH != kSortBvhKeys;
+    __shared__ uint32_t h[256];
+    const Batch& Bt = p.B;
+    // ONE: a block per tile of the capacity
+    const int64_t tiles = WHICH == kSortPairsOne ? (sealed(Bt) ? gridDim.x : 0) : sort_tiles<BWD>(Bt);
+    for (int64_t blk = blockIdx.x; blk < tiles; blk += gridDim.x) {
+        SortTile T;
+        if constexpr (WHICH == kSortPairsOne) {
+            T = SortTile{3 * (int64_t)Bt.ray_pf[0], 0, 0, 0, blk};
+        } else {
+            T = sort_tile<BWD>(Bt, blk);
+        }
+        if (threadIdx.x < 256) h[threadIdx.x] = 0;
+        __syncthreads();
+        if constexpr (WHICH == kSortPairsFirst) {
+            gather_pairs<false>(Bt, T, upper_asset(Bt.bt_pf, Bt.n, blk), p.shift, p.keys, p.pairs, p.bucket, p.kout,
+                                p.vout, p.bt_pf, h);
+        } else if constexpr (WHICH == kSortPairsOne) {
+            if (!gather_pairs<true>(Bt, T, 0, p.shift, p.keys, p.pairs, p.bucket, p.kout, p.vout, p.bt_pf, h)) return;
+        } else {
+            const int64_t base = T.lt * kSortTile;
+            // all rounds' keys are loaded before the first count (one load latency)
+            uint32_t k[kSortRounds];
+#pragma unroll
+            for (int r = 0; r < kSortRounds; ++r) {
+                const int64_t i = base + (int64_t)r * kSortBlock + threadIdx.x;
+                k[r] = p.keys[T.start + min(i, T.count - 1)];
+            }
+#pragma unroll
+            for (int r = 0; r < kSortRounds; ++r)
+                if (base + (int64_t)r * kSortBlock + threadIdx.x < T.count)
+                    atomicAdd(&h[(k[r] >> p.shift) & 255u], 1u);
+        }
+        __syncthreads();
+        if (threadIdx.x < 256) {
+            const uint32_t c = h[threadIdx.x];
+            p.hist[T.hbase + 256 * T.lt + threadIdx.x] = c;
+            if (c) atomicAdd(&p.sup[T.sbase + 256 * (T.lt / kSuper) + threadIdx.x], c);
+        }
+        if (BWD) __syncthreads();
     }
 }
 
@@ -282,7 +419,7 @@ __global__ __launch_bounds__(kSortBlock) void radix_hist_kernel(Batch Bt, const 
 // order, then turns the counts into positions, so the whole tile is ranked
 // between two barriers.
 template <bool BWD>
-__global__ __launch_bounds__(kSortBlock) void radix_scatter_kernel(Batch Bt, const uint32_t* __restrict__ kin,
+__global__ __launch_bounds__(kSortBlock) __attribute__((amdgpu_waves_per_eu(8))) void radix_scatter_kernel(Batch Bt, const uint32_t* __restrict__ kin,
                                                                    const uint32_t* __restrict__ vin,
                                                                    uint32_t* __restrict__ kout,
                                                                    uint32_t* __restrict__ vout, int shift,
@@ -299,158 +436,160 @@ __global__ __launch_bounds__(kSortBlock) void radix_scatter_kernel(Batch Bt, con
     __shared__ uint16_t wcnt[kSortRounds][kSortWaves][256];
     static_assert(kSortTile <= 65535, "tile positions are kept in 16 bits");
     static_assert(kSortBlock == 4 * 256 && kSortRounds * kSortWaves == 64, "one scan thread per (round, digit)");
-    if (BWD && bwd_block_idle(Bt)) return;
-    const SortTile T = sort_tile<BWD>(Bt, blockIdx.x);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t base = T.lt * kSortTile;
-    const int64_t nvalid = min((int64_t)kSortTile, T.count - base);
-    if (nvalid <= 0) return;  // an empty capacity tile (uniform)
-    uint32_t key[kSortRounds], val[kSortRounds];
+    const int64_t tiles = sort_tiles<BWD>(Bt);
+    for (int64_t blk = blockIdx.x; blk < tiles; blk += gridDim.x) {
+        const int tid = tile_thread<BWD>(), lane = tid & 63, wave = tid >> 6;
+        const SortTile T = sort_tile<BWD>(Bt, blk);
+        const int64_t base = T.lt * kSortTile;
+        const int64_t nvalid = min((int64_t)kSortTile, T.count - base);
+        uint32_t key[kSortRounds], val[kSortRounds];
 #pragma unroll
-    for (int r = 0; r < kSortRounds; ++r) {
-        const int64_t i = (int64_t)r * kSortBlock + tid;
-        const bool valid = i < nvalid;
-        key[r] = valid ? kin[T.start + base + i] : 0u;
-        val[r] = valid ? vin[T.start + base + i] : 0u;
-    }
-    uint32_t(*scratch)[256] = reinterpret_cast<uint32_t(*)[256]>(s_key);
-    {
-        // per digit, in four parts: the asset's count (all super-tile rows)
-        // and the count before this tile (earlier super-tiles, then the
-        // earlier tiles of its own super-tile)
-        // (the loads of a group are all issued before their sums: one load
-        // latency per group instead of one per row)
-        const int d = tid & 255, part = tid >> 8;
-        const int64_t S = T.lt / kSuper, nS = ceil_div(ceil_div(T.count, kSortTile), kSuper);
+        for (int r = 0; r < kSortRounds; ++r) {
+            const int64_t i = (int64_t)r * kSortBlock + tid;
+            const bool valid = i < nvalid;
+            key[r] = valid ? kin[T.start + base + i] : 0u;
+            val[r] = valid ? vin[T.start + base + i] : 0u;
+        }
+        uint32_t(*scratch)[256] = reinterpret_cast<uint32_t(*)[256]>(s_key);
+        {
+            // per digit, in four parts: the asset's count (all super-tile rows)
+            // and the count before this tile (earlier super-tiles, then the
+            // earlier tiles of its own super-tile)
+            // (the loads of a group are all issued before their sums: one load
+            // latency per group instead of one per row)
+            const int d = tid & 255, part = tid >> 8;
+            const int64_t S = T.lt / kSuper, nS = ceil_div(ceil_div(T.count, kSortTile), kSuper);
+            uint32_t tot = 0, before = 0;
+            uint32_t hv[kSuper / 4];
+#pragma unroll
+            for (int j = 0; j < kSuper / 4; ++j) {
+                const int64_t t = S * kSuper + part + 4 * j;
+                hv[j] = t < T.lt ? hist[T.hbase + 256 * t + d] : 0u;
+            }
+            for (int64_t x0 = part; x0 < nS; x0 += 4 * 8) {
+                uint32_t v[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const int64_t x = x0 + 4 * j;
+                    v[j] = x < nS ? sup[T.sbase + 256 * x + d] : 0u;
+                }
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    tot += v[j];
+                    if (x0 + 4 * j < S) before += v[j];
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < kSuper / 4; ++j) before += hv[j];
+            scratch[part][d] = tot;
+            scratch[4 + part][d] = before;
+        }
+        __syncthreads();
         uint32_t tot = 0, before = 0;
-        uint32_t hv[kSuper / 4];
+        if (tid < 256) {
+            tot = (scratch[0][tid] + scratch[1][tid]) + (scratch[2][tid] + scratch[3][tid]);
+            before = (scratch[4][tid] + scratch[5][tid]) + (scratch[6][tid] + scratch[7][tid]);
+            // exclusive scan of the asset's digit counts (waves 0-3)
+            uint32_t x = tot;
 #pragma unroll
-        for (int j = 0; j < kSuper / 4; ++j) {
-            const int64_t t = S * kSuper + part + 4 * j;
-            hv[j] = t < T.lt ? hist[T.hbase + 256 * t + d] : 0u;
-        }
-        for (int64_t x0 = part; x0 < nS; x0 += 4 * 8) {
-            uint32_t v[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int64_t x = x0 + 4 * j;
-                v[j] = x < nS ? sup[T.sbase + 256 * x + d] : 0u;
+            for (int o = 1; o < 64; o <<= 1) {
+                const uint32_t y = __shfl_up(x, o, 64);
+                if (lane >= o) x += y;
             }
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                tot += v[j];
-                if (x0 + 4 * j < S) before += v[j];
-            }
+            if (lane == 63) s_wsum[wave] = x;
+            tot = x - tot;  // exclusive within the wave
         }
-#pragma unroll
-        for (int j = 0; j < kSuper / 4; ++j) before += hv[j];
-        scratch[part][d] = tot;
-        scratch[4 + part][d] = before;
-    }
-    __syncthreads();
-    uint32_t tot = 0, before = 0;
-    if (tid < 256) {
-        tot = (scratch[0][tid] + scratch[1][tid]) + (scratch[2][tid] + scratch[3][tid]);
-        before = (scratch[4][tid] + scratch[5][tid]) + (scratch[6][tid] + scratch[7][tid]);
-        // exclusive scan of the asset's digit counts (waves 0-3)
-        uint32_t x = tot;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t y = __shfl_up(x, o, 64);
-            if (lane >= o) x += y;
+        __syncthreads();
+        if (tid < 256) {
+            uint32_t w = 0;
+            for (int k = 0; k < wave; ++k) w += s_wsum[k];
+            s_glob[tid] = (uint32_t)T.start + w + tot + before;
+            s_run[tid] = 0;
         }
-        if (lane == 63) s_wsum[wave] = x;
-        tot = x - tot;  // exclusive within the wave
-    }
-    __syncthreads();
-    if (tid < 256) {
-        uint32_t w = 0;
-        for (int k = 0; k < wave; ++k) w += s_wsum[k];
-        s_glob[tid] = (uint32_t)T.start + w + tot + before;
-        s_run[tid] = 0;
-    }
-    for (int x = tid; x < kSortRounds * kSortWaves * 256 / 2; x += kSortBlock)
-        reinterpret_cast<uint32_t*>(&wcnt[0][0][0])[x] = 0;
-    __syncthreads();
-    // the tile's digit counts, and every wave's per-round digit counts
-    uint32_t rank[kSortRounds];
+        for (int x = tid; x < kSortRounds * kSortWaves * 256 / 2; x += kSortBlock)
+            reinterpret_cast<uint32_t*>(&wcnt[0][0][0])[x] = 0;
+        __syncthreads();
+        // the tile's digit counts, and every wave's per-round digit counts
+        uint32_t rank[kSortRounds];
 #pragma unroll
-    for (int r = 0; r < kSortRounds; ++r) {
-        const bool valid = (int64_t)r * kSortBlock + tid < nvalid;
-        const uint32_t dig = (key[r] >> shift) & 255u;
-        if (valid) atomicAdd(&s_run[dig], 1u);
-        uint64_t peers = __ballot(valid);
-#pragma unroll
-        for (int b = 0; b < 8; ++b) {
-            const bool bit = (dig >> b) & 1u;
-            const uint64_t m = __ballot(bit);
-            peers &= bit ? m : ~m;
-        }
-        rank[r] = (uint32_t)__popcll(peers & __lanemask_lt());
-        if (valid && rank[r] == 0) wcnt[r][wave][dig] = (uint16_t)__popcll(peers);
-    }
-    __syncthreads();
-    // thread (rr, d): exclusive scan of digit d's counts over the waves of
-    // round rr; waves 0-3 also scan the tile's digit counts
-    const int sd = tid & 255, rr = tid >> 8;
-    uint32_t ex[kSortWaves];
-    {
-        uint32_t acc = 0;
-#pragma unroll
-        for (int w = 0; w < kSortWaves; ++w) {
-            ex[w] = acc;
-            acc += wcnt[rr][w][sd];
-        }
-        s_part[rr][sd] = acc;
-    }
-    uint32_t c = 0, x = 0;
-    if (tid < 256) {
-        c = s_run[tid];
-        x = c;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t y = __shfl_up(x, o, 64);
-            if (lane >= o) x += y;
-        }
-        if (lane == 63) s_wsum[wave] = x;
-    }
-    __syncthreads();
-    if (tid < 256) {
-        uint32_t b = 0;
-        for (int w = 0; w < wave; ++w) b += s_wsum[w];
-        s_loc[tid] = b + x - c;
-    }
-    __syncthreads();
-    {
-        uint32_t p = s_loc[sd];
-        for (int r = 0; r < rr; ++r) p += s_part[r][sd];
-#pragma unroll
-        for (int w = 0; w < kSortWaves; ++w) wcnt[rr][w][sd] = (uint16_t)(p + ex[w]);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < kSortRounds; ++r) {
-        if ((int64_t)r * kSortBlock + tid < nvalid) {
+        for (int r = 0; r < kSortRounds; ++r) {
+            const bool valid = (int64_t)r * kSortBlock + tid < nvalid;
             const uint32_t dig = (key[r] >> shift) & 255u;
-            const uint32_t pos = (uint32_t)wcnt[r][wave][dig] + rank[r];
-            s_key[pos] = key[r];
-            s_val[pos] = val[r];
-        }
-    }
-    __syncthreads();
+            if (valid) atomicAdd(&s_run[dig], 1u);
+            uint64_t peers = __ballot(valid);
 #pragma unroll
-    for (int r = 0; r < kSortRounds; ++r) {
-        const int e = r * kSortBlock + tid;
-        if (e >= nvalid) break;
-        const uint32_t k = s_key[e];
-        const uint32_t d = (k >> shift) & 255u;
-        const uint32_t pos = s_glob[d] + ((uint32_t)e - s_loc[d]);
-        if ((int64_t)pos < T.start + T.count) {  // always, unless the counts were corrupted
-            kout[pos] = k;
-            vout[pos] = s_val[e];
-        } else {
-            set_status(Bt, kStInternal);
+            for (int b = 0; b < 8; ++b) {
+                const bool bit = (dig >> b) & 1u;
+                const uint64_t m = __ballot(bit);
+                peers &= bit ? m : ~m;
+            }
+            rank[r] = (uint32_t)__popcll(peers & __lanemask_lt());
+            if (valid && rank[r] == 0) wcnt[r][wave][dig] = (uint16_t)__popcll(peers);
         }
+        __syncthreads();
+        // thread (rr, d): exclusive scan of digit d's counts over the waves of
+        // round rr; waves 0-3 also scan the tile's digit counts
+        const int sd = tid & 255, rr = tid >> 8;
+        uint32_t ex[kSortWaves];
+        {
+            uint32_t acc = 0;
+#pragma unroll
+            for (int w = 0; w < kSortWaves; ++w) {
+                ex[w] = acc;
+                acc += wcnt[rr][w][sd];
+            }
+            s_part[rr][sd] = acc;
+        }
+        uint32_t c = 0, x = 0;
+        if (tid < 256) {
+            c = s_run[tid];
+            x = c;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const uint32_t y = __shfl_up(x, o, 64);
+                if (lane >= o) x += y;
+            }
+            if (lane == 63) s_wsum[wave] = x;
+        }
+        __syncthreads();
+        if (tid < 256) {
+            uint32_t b = 0;
+            for (int w = 0; w < wave; ++w) b += s_wsum[w];
+            s_loc[tid] = b + x - c;
+        }
+        __syncthreads();
+        {
+            uint32_t p = s_loc[sd];
+            for (int r = 0; r < rr; ++r) p += s_part[r][sd];
+#pragma unroll
+            for (int w = 0; w < kSortWaves; ++w) wcnt[rr][w][sd] = (uint16_t)(p + ex[w]);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kSortRounds; ++r) {
+            if ((int64_t)r * kSortBlock + tid < nvalid) {
+                const uint32_t dig = (key[r] >> shift) & 255u;
+                const uint32_t pos = (uint32_t)wcnt[r][wave][dig] + rank[r];
+                s_key[pos] = key[r];
+                s_val[pos] = val[r];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kSortRounds; ++r) {
+            const int e = r * kSortBlock + tid;
+            if (e >= nvalid) break;
+            const uint32_t k = s_key[e];
+            const uint32_t d = (k >> shift) & 255u;
+            const uint32_t pos = s_glob[d] + ((uint32_t)e - s_loc[d]);
+            if ((int64_t)pos < T.start + T.count) {  // always, unless the counts were corrupted
+                kout[pos] = k;
+                vout[pos] = s_val[e];
+            } else {
+                set_status(Bt, kStInternal);
+            }
+        }
+        if (BWD) __syncthreads();
     }
 }
 
@@ -831,8 +970,14 @@ __global__ __launch_bounds__(kBuildBlock) void build_join_kernel(JoinArgs p) {
 }  // namespace
 
 int64_t bwd_sort_zero_words(const Layout& L) {
-    return L.save ? sort_super_rows(L.t_btile, L.n) * 256 * (int64_t)kSortPasses : 0;
+    // the super-tile rows and, behind them, the pair buckets
+    return L.save ? (int64_t)(L.bwd_bucket_pf - L.bwd_sup) / 4 : 0;
 }
+
+// One asset whose 64-ray batches one workgroup sums at once: the tables of the
+// pairs come from the first pass itself, which costs a 256^2 training step 4 us
+// less than the launch.
+bool pairs_in_one(const BatchHost& H) { return H.L.n == 1 && H.L.t_tex <= 64 * (int64_t)kSortBlock; }
 
 hipError_t launch_sort(const BatchHost& H, int which, int bits, bool* result_in_1, hipStream_t s,
                        hipEvent_t after_first) {
@@ -850,6 +995,8 @@ hipError_t launch_sort(const BatchHost& H, int which, int bits, bool* result_in_
     uint32_t* sup = (uint32_t*)(H.ws + (bwd ? L.bwd_sup : L.sup));
     const int64_t sup_pass = sort_super_rows(bwd ? L.t_btile : L.t_stile, L.n) * 256;
     if (passes > kSortPasses) return hipErrorInvalidValue;
+    // the backward's tiles are known on the device: its blocks loop over them
+    const dim3 grid((unsigned)(bwd ? std::min<int64_t>(blocks, kBwdSortGrid) : blocks));
     // the super-tile rows start at zero: the BVH sort's lie in the region
     // every forward zeroes first, the backward's are zeroed with the
     // backward's gradient table (bwd_sort_zero_words)
@@ -857,21 +1004,32 @@ hipError_t launch_sort(const BatchHost& H, int which, int bits, bool* result_in_
     for (int p = 0; p < passes; ++p) {
         const int shift = 8 * p;
         uint32_t* sp = sup + sup_pass * p;
-        if (bwd) {
-            hipLaunchKernelGGL(radix_hist_kernel<true>, dim3((unsigned)blocks), dim3(kSortBlock), 0, s, H.dev,
-                               (const uint32_t*)kin, shift, hist, sp);
-            if (p == 0 && after_first && (e = hipEventRecord(after_first, s)) != hipSuccess) return e;
-            hipLaunchKernelGGL(radix_scatter_kernel<true>, dim3((unsigned)blocks), dim3(kSortBlock), 0, s, H.dev,
-                               (const uint32_t*)kin, (const uint32_t*)vin, kout, vout, shift,
-                               (const uint32_t*)hist, (const uint32_t*)sp);
+        HistArgs h = {H.dev, kin, shift, hist, sp, nullptr, nullptr, nullptr, nullptr, nullptr};
+        if (bwd && p == 0) {
+            h.keys = kout;
+            h.pairs = (const uint32_t*)(H.ws + L.bwd_pairs);
+            h.bucket = (const uint32_t*)(H.ws + L.bwd_bucket_pf);
+            h.kout = kin;
+            h.vout = vin;
+            h.bt_pf = (uint32_t*)(H.ws + H.L.bt_pf);
+            if (pairs_in_one(H))
+                hipLaunchKernelGGL(radix_hist_kernel<kSortPairsOne>, dim3((unsigned)blocks), dim3(kSortBlock), 0, s, h);
+            else
+                hipLaunchKernelGGL(radix_hist_kernel<kSortPairsFirst>, grid, dim3(kSortBlock), 0, s, h);
+        } else if (bwd) {
+            hipLaunchKernelGGL(radix_hist_kernel<kSortPairs>, grid, dim3(kSortBlock), 0, s, h);
         } else {
-            hipLaunchKernelGGL(radix_hist_kernel<false>, dim3((unsigned)blocks), dim3(kSortBlock), 0, s, H.dev,
-                               (const uint32_t*)kin, shift, hist, sp);
-            if (p == 0 && after_first && (e = hipEventRecord(after_first, s)) != hipSuccess) return e;
-            hipLaunchKernelGGL(radix_scatter_kernel<false>, dim3((unsigned)blocks), dim3(kSortBlock), 0, s, H.dev,
+            hipLaunchKernelGGL(radix_hist_kernel<kSortBvhKeys>, grid, dim3(kSortBlock), 0, s, h);
+        }
+        if (p == 0 && after_first && (e = hipEventRecord(after_first, s)) != hipSuccess) return e;
+        if (bwd)
+            hipLaunchKernelGGL(radix_scatter_kernel<true>, grid, dim3(kSortBlock), 0, s, H.dev,
                                (const uint32_t*)kin, (const uint32_t*)vin, kout, vout, shift,
                                (const uint32_t*)hist, (const uint32_t*)sp);
-        }
+        else
+            hipLaunchKernelGGL(radix_scatter_kernel<false>, grid, dim3(kSortBlock), 0, s, H.dev,
+                               (const uint32_t*)kin, (const uint32_t*)vin, kout, vout, shift,
+                               (const uint32_t*)hist, (const uint32_t*)sp);
         std::swap(kin, kout);
         std::swap(vin, vout);
         *result_in_1 = !*result_in_1;
