@@ -185,6 +185,7 @@ int32_t make_plan(const Sizes* z, int n, uint32_t flags, Plan* P) {
         L.t_btile += cdiv(3 * tex, kSortTile);
         L.t_tl += cdiv(z[a].nhf, kBuildTile);
         max_hv = std::max(max_hv, z[a].nhv);
+        L.max_hf = std::max(L.max_hf, (int64_t)z[a].nhf);
         for (int g = 0; g < kGridCount; ++g) {
             P->gpf[(size_t)g * (n + 1) + a] = (int32_t)gsum[g];
             gsum[g] += grid_blocks(g, z[a]);

@@ -159,6 +159,10 @@ constexpr int kSuper = 32;       // sort tiles per super-tile (digit counts summ
 // Super-tile rows of a sort over `tiles` tiles of `n` assets (asset a's rows
 // start at its first tile / kSuper + a).
 __host__ __device__ inline int64_t sort_super_rows(int64_t tiles, int64_t n) { return tiles / kSuper + n + 1; }
+// Assets whose triangles one workgroup sorts (front_kernel).  A bake of 128^2 by
+// it and by the launches over all CUs: 97 and 124 us at 320 triangles, 139 and 161
+// at 5,120, 149 and 163 at 8,192; 173 and 169 at 12,000, 183 and 169 at 16,384.
+constexpr int kFrontFaces = 8192;
 constexpr int kFinishCols = 56, kFinishRows = 28;  // texel tile of the fused fill + dilation (columns + 2 halos <= 64)
 constexpr int kMaxFusedPasses = 4;  // more dilation passes run one launch per pass
 
@@ -313,6 +317,7 @@ struct Layout {
     size_t total;
     // batch totals
     int n;
+    int64_t max_hf;  // largest asset
     int64_t t_lv, t_lf, t_hv, t_hf, t_node, t_tex, t_stile, t_btile, t_tl;
     int64_t spill_lanes, scan_tmp_n;
     int max_hv_bits;  // bit length of the largest nhv (backward sort keys lie in [0, nhv])

@@ -29,6 +29,13 @@ constexpr int kSortBlock = 1024;                     // sort workgroups: 16 wave
 constexpr int kSortRounds = kSortTile / kSortBlock;  // 4 keys per thread and pass
 constexpr int kSortWaves = kSortBlock / 64;
 constexpr int kBwdSortGrid = 1024;                   // two workgroups a CU, twice
+// LDS writes of a wave before its later reads
+__device__ __forceinline__ void wave_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 constexpr float kLeafEps = 1.0f / 16384.0f;  // edge tolerance of the hit rule (traverse.hip)
 
 __device__ __forceinline__ int3 tri_idx(const int32_t* __restrict__ F, int64_t g, int64_t nv,
@@ -162,6 +169,15 @@ __device__ __forceinline__ uint32_t quant10(float c, float lo, float inv) {
     return (uint32_t)q;
 }
 
+__device__ __forceinline__ uint32_t morton(float3 c, const float* bounds) {
+    float ex = bounds[3] - bounds[0], ey = bounds[4] - bounds[1], ez = bounds[5] - bounds[2];
+    float ix = ex > 0.f ? 1.0f / ex : 0.f, iy = ey > 0.f ? 1.0f / ey : 0.f,
+          iz = ez > 0.f ? 1.0f / ez : 0.f;
+    uint32_t x = quant10(c.x, bounds[0], ix), y = quant10(c.y, bounds[1], iy),
+             z = quant10(c.z, bounds[2], iz);
+    return (spread10(x) << 2) | (spread10(y) << 1) | spread10(z);
+}
+
 __global__ __launch_bounds__(kBlock) void morton_kernel(Batch Bt, const float* __restrict__ bounds_all,
                                                         uint32_t* __restrict__ keys,
                                                         uint32_t* __restrict__ vals) {
@@ -174,12 +190,7 @@ __global__ __launch_bounds__(kBlock) void morton_kernel(Batch Bt, const float* _
     bool bad;
     int3 t = tri_idx(As.hi_F, g, As.nhv, &bad);
     float3 c = centroid(As.hi_V, t);
-    float ex = bounds[3] - bounds[0], ey = bounds[4] - bounds[1], ez = bounds[5] - bounds[2];
-    float ix = ex > 0.f ? 1.0f / ex : 0.f, iy = ey > 0.f ? 1.0f / ey : 0.f,
-          iz = ez > 0.f ? 1.0f / ez : 0.f;
-    uint32_t x = quant10(c.x, bounds[0], ix), y = quant10(c.y, bounds[1], iy),
-             z = quant10(c.z, bounds[2], iz);
-    keys[As.hf + g] = (spread10(x) << 2) | (spread10(y) << 1) | spread10(z);
+    keys[As.hf + g] = morton(c, bounds);
     vals[As.hf + g] = (uint32_t)g;
 }
 
@@ -407,6 +418,20 @@ __global__ __launch_bounds__(kSortBlock) __attribute__((amdgpu_waves_per_eu(8)))
     }
 }
 
+// The wave's valid lanes whose digit is the lane's.
+template <int BITS>
+__device__ __forceinline__ uint64_t equal_lanes(uint32_t dig, bool valid) {
+    uint32_t lo = 0, hi = 0;  // lanes that differ in a bit
+#pragma unroll
+    for (int b = 0; b < BITS; ++b) {
+        const uint32_t mine = (uint32_t)((int32_t)(dig << (31 - b)) >> 31);
+        const uint64_t m = __ballot(mine != 0);
+        lo |= (uint32_t)m ^ mine;
+        hi |= (uint32_t)(m >> 32) ^ mine;
+    }
+    return ~((uint64_t)hi << 32 | lo) & __ballot(valid);
+}
+
 // Element r*1024 + tid of the block's tile is ranked among equal digits by
 // (earlier rounds, earlier waves, earlier lanes): a stable order.  The tile is
 // first placed in LDS in that order (digit runs contiguous), then written out
@@ -516,13 +541,7 @@ __global__ __launch_bounds__(kSortBlock) __attribute__((amdgpu_waves_per_eu(8)))
             const bool valid = (int64_t)r * kSortBlock + tid < nvalid;
             const uint32_t dig = (key[r] >> shift) & 255u;
             if (valid) atomicAdd(&s_run[dig], 1u);
-            uint64_t peers = __ballot(valid);
-#pragma unroll
-            for (int b = 0; b < 8; ++b) {
-                const bool bit = (dig >> b) & 1u;
-                const uint64_t m = __ballot(bit);
-                peers &= bit ? m : ~m;
-            }
+            const uint64_t peers = equal_lanes<8>(dig, valid);
             rank[r] = (uint32_t)__popcll(peers & __lanemask_lt());
             if (valid && rank[r] == 0) wcnt[r][wave][dig] = (uint16_t)__popcll(peers);
         }
@@ -590,6 +609,156 @@ __global__ __launch_bounds__(kSortBlock) __attribute__((amdgpu_waves_per_eu(8)))
             }
         }
         if (BWD) __syncthreads();
+    }
+}
+
+// Bounds, codes and sort of a small mesh in one workgroup: an asset of at most
+// kFrontFaces triangles whose keys and indices stay in LDS over the three passes.
+// Wave w holds elements [64 per w, 64 per (w + 1)) of the order before the pass,
+// 64 a round; a round's lanes of equal digit are found by ballots, the wave's
+// counts of earlier rounds give their rank in the wave, one scan over waves and
+// digits the rest: a stable order, as that of the passes over many tiles.
+// Bound by the issue rate of one CU (a pass at 5,120 elements is 80 wave-rounds of
+// some 80 instructions on four SIMDs) and by the gather of the corners: 28 us at
+// 5,120, where bounds, codes and four passes in eleven launches took 54 and
+// their gaps.
+constexpr int kFrontBlock = 1024;
+constexpr int kFrontWaves = kFrontBlock / 64;
+constexpr int kFrontBits = 10, kFrontDigits = 1 << kFrontBits;  // three passes over 30-bit codes
+constexpr int kFrontPer = kFrontFaces / kFrontBlock;
+static_assert(kFrontFaces % kFrontBlock == 0 && kFrontFaces <= 65536, "whole rounds, 16-bit indices");
+static_assert(kFrontDigits == kFrontBlock, "a thread per digit");
+
+__global__ __launch_bounds__(kFrontBlock) void front_kernel(Batch Bt, uint32_t* __restrict__ keys,
+                                                            uint32_t* __restrict__ vals) {
+    __shared__ uint32_t s_key[kFrontFaces];
+    __shared__ uint16_t s_idx[kFrontFaces];
+    __shared__ uint16_t s_cnt[kFrontWaves][kFrontDigits];
+    __shared__ uint32_t s_dig[kFrontDigits];
+    __shared__ uint32_t s_w[kFrontWaves];
+    __shared__ float s_red[kFrontWaves][6];
+    const int a = blockIdx.x;
+    const AssetDev& As = Bt.A[a];
+    const int n = As.nhf, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (n == 0) return;
+    const int per = (n + kFrontBlock - 1) / kFrontBlock;
+    const int e0 = wave * 64 * per + lane;  // element of round r: e0 + 64 r
+    float3 c[kFrontPer];
+    bool anybad = false, nonfin = false;
+    float v[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    {
+        const float* __restrict__ V = As.hi_V;
+        const int32_t* __restrict__ F = As.hi_F;
+        int3 t[kFrontPer];
+#pragma unroll
+        for (int r = 0; r < kFrontPer; ++r) {
+            bool bad = false;
+            const int e = e0 + 64 * r;
+            t[r] = r < per && e < n ? tri_idx(F, e, As.nhv, &bad) : make_int3(0, 0, 0);
+            anybad |= bad;
+        }
+#pragma unroll
+        for (int r = 0; r < kFrontPer; ++r) {
+            c[r] = make_float3(0.f, 0.f, 0.f);
+            if (r < per) c[r] = centroid(V, t[r]);
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < kFrontPer; ++r) {
+        if (r >= per || e0 + 64 * r >= n) continue;
+        if (!(isfinite(c[r].x) && isfinite(c[r].y) && isfinite(c[r].z))) {
+            nonfin = true;
+            continue;
+        }
+        v[0] = fminf(v[0], c[r].x); v[1] = fminf(v[1], c[r].y); v[2] = fminf(v[2], c[r].z);
+        v[3] = fmaxf(v[3], c[r].x); v[4] = fmaxf(v[4], c[r].y); v[5] = fmaxf(v[5], c[r].z);
+    }
+    if (anybad) set_status(Bt, kStHiIndex);
+    if (nonfin) set_status(Bt, kStNonFinite);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) v[k] = k < 3 ? wave_min(v[k]) : wave_max(v[k]);
+    if (lane == 0)
+#pragma unroll
+        for (int k = 0; k < 6; ++k) s_red[wave][k] = v[k];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        const float x = s_red[lane & (kFrontWaves - 1)][k];
+        v[k] = k < 3 ? wave_min(x) : wave_max(x);
+    }
+    uint32_t key[kFrontPer], idx[kFrontPer];
+#pragma unroll
+    for (int r = 0; r < kFrontPer; ++r) {
+        key[r] = morton(c[r], v);
+        idx[r] = (uint32_t)(e0 + 64 * r);
+    }
+    for (int shift = 0; shift < 30; shift += kFrontBits) {
+        for (int x = tid; x < kFrontWaves * kFrontDigits / 2; x += kFrontBlock)
+            reinterpret_cast<uint32_t*>(&s_cnt[0][0])[x] = 0;
+        __syncthreads();
+        uint32_t rank[kFrontPer];
+#pragma unroll
+        for (int r = 0; r < kFrontPer; ++r) {
+            if (r >= per) break;
+            const bool valid = e0 + 64 * r < n;
+            const uint32_t dig = (key[r] >> shift) & (kFrontDigits - 1);
+            const uint64_t peers = equal_lanes<kFrontBits>(dig, valid);
+            const uint32_t in = (uint32_t)__popcll(peers & __lanemask_lt());
+            const uint32_t was = s_cnt[wave][dig];
+            rank[r] = was + in;
+            wave_order();
+            if (valid && in == 0) s_cnt[wave][dig] = (uint16_t)(was + __popcll(peers));
+            wave_order();
+        }
+        __syncthreads();
+        uint32_t sum = 0;
+#pragma unroll
+        for (int w = 0; w < kFrontWaves; ++w) {  // exclusive over the waves
+            const uint32_t y = s_cnt[w][tid];
+            s_cnt[w][tid] = (uint16_t)sum;
+            sum += y;
+        }
+        uint32_t x = sum;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t y = __shfl_up(x, o, 64);
+            if (lane >= o) x += y;
+        }
+        if (lane == 63) s_w[wave] = x;
+        __syncthreads();
+        uint32_t before = s_w[lane & (kFrontWaves - 1)];
+#pragma unroll
+        for (int o = 1; o < kFrontWaves; o <<= 1) {
+            const uint32_t y = __shfl_up(before, o, 64);
+            if (lane >= o) before += y;
+        }
+        before = wave > 0 ? (uint32_t)__builtin_amdgcn_readlane((int)before, wave - 1) : 0u;
+        s_dig[tid] = before + x - sum;
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kFrontPer; ++r) {
+            if (r >= per) break;
+            if (e0 + 64 * r >= n) continue;
+            const uint32_t dig = (key[r] >> shift) & (kFrontDigits - 1);
+            const uint32_t at = s_dig[dig] + s_cnt[wave][dig] + rank[r];
+            s_key[at] = key[r];
+            s_idx[at] = (uint16_t)idx[r];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kFrontPer; ++r) {
+            const int e = min(e0 + 64 * r, n - 1);
+            key[r] = s_key[e];
+            idx[r] = s_idx[e];
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < kFrontPer; ++r) {
+        const int e = e0 + 64 * r;
+        if (r < per && e < n) {
+            keys[As.hf + e] = key[r];
+            vals[As.hf + e] = idx[r];
+        }
     }
 }
 
@@ -1049,16 +1218,21 @@ hipError_t launch_bvh_build(const BatchHost& H, hipStream_t s) {
     BvhNodeC* nodes_c = (BvhNodeC*)(ws + L.nodes_c);
     Leaf* leaves = (Leaf*)(ws + L.leaves);
 
-    hipLaunchKernelGGL(bounds_part_kernel, dim3((unsigned)(H.blocks(kGSort) * kBoundsSplit)), dim3(kBlock), 0, s,
-                       H.dev, part);
-    hipLaunchKernelGGL(bounds_final_kernel, dim3((unsigned)L.n), dim3(kBlock), 0, s, H.dev,
-                       (const float*)part, bounds);
-    hipLaunchKernelGGL(morton_kernel, dim3((unsigned)H.blocks(kGHiF)), dim3(kBlock), 0, s, H.dev,
-                       (const float*)bounds, k0, v0);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-
-    bool in1 = false;
-    if ((e = launch_sort(H, kSortBvh, 30, &in1, s)) != hipSuccess) return e;
+    if (L.max_hf <= kFrontFaces) {
+        hipLaunchKernelGGL(front_kernel, dim3((unsigned)L.n), dim3(kFrontBlock), 0, s, H.dev, k0, v0);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    } else {
+        hipLaunchKernelGGL(bounds_part_kernel, dim3((unsigned)(H.blocks(kGSort) * kBoundsSplit)), dim3(kBlock), 0, s,
+                           H.dev, part);
+        hipLaunchKernelGGL(bounds_final_kernel, dim3((unsigned)L.n), dim3(kBlock), 0, s, H.dev,
+                           (const float*)part, bounds);
+        hipLaunchKernelGGL(morton_kernel, dim3((unsigned)H.blocks(kGHiF)), dim3(kBlock), 0, s, H.dev,
+                           (const float*)bounds, k0, v0);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    
+        bool in1 = false;
+        if ((e = launch_sort(H, kSortBvh, 30, &in1, s)) != hipSuccess) return e;
+    }
     // 30-bit keys take four 8-bit passes: the sorted arrays are back in keys0 / vals0
     BuildItem* items = (BuildItem*)(ws + L.items);
     uint32_t* counts = (uint32_t*)(ws + L.item_cnt);
