@@ -223,6 +223,8 @@ int32_t make_plan(const Sizes* z, int n, uint32_t flags, Plan* P) {
     L.gcnt = take(4 * (size_t)kGcSlots);
     // the BVH sort's super-tile rows: zeroed with the counters before the table
     L.sup = take(4 * 256 * (size_t)kSortPasses * (size_t)sort_super_rows(L.t_stile, n));
+    L.lo_deg = take(4 * (size_t)L.t_lv);
+    L.lo_cur = take(4 * (size_t)L.t_lv);
     L.table = take(sizeof(AssetDev) * (size_t)n + 4 * (size_t)kGridCount * (n + 1));
     L.gpf = L.table + sizeof(AssetDev) * (size_t)n;
     L.grads = take(sizeof(AssetGrad) * (size_t)n);
@@ -230,9 +232,7 @@ int32_t make_plan(const Sizes* z, int n, uint32_t flags, Plan* P) {
     L.rb_pf = take(4 * (size_t)(n + 1));
     L.bt_pf = take(4 * (size_t)(n + 1));
     L.lo_n = take(16 * (size_t)L.t_lv);
-    L.lo_deg = take(4 * (size_t)L.t_lv);
     L.lo_off = take(4 * (size_t)(L.t_lv + 1));
-    L.lo_cur = take(4 * (size_t)L.t_lv);
     L.lo_adj = take(12 * (size_t)L.t_lf);
     L.face_t = take(16 * (size_t)L.t_lf);
     L.face_uv = take(32 * (size_t)L.t_lf);
@@ -244,7 +244,6 @@ int32_t make_plan(const Sizes* z, int n, uint32_t flags, Plan* P) {
     L.rays = take(16 * (size_t)L.t_tex);
     L.hits = L.save ? take(16 * (size_t)L.t_tex) : off;
     L.bounds_part = take(24 * (size_t)kBoundsSplit * (size_t)L.t_stile);
-    L.bounds = take(24 * (size_t)n);
     L.keys0 = take(4 * (size_t)L.t_hf);
     L.vals0 = take(4 * (size_t)L.t_hf);
     L.keys1 = take(4 * (size_t)L.t_hf);
@@ -509,7 +508,7 @@ int32_t run_forward(Plan& P, const Opts& o, void* workspace, hipStream_t s) {
     std::vector<char> blob(L.grads - L.table, 0);
     memcpy(blob.data(), P.A.data(), sizeof(AssetDev) * (size_t)L.n);
     memcpy(blob.data() + (L.gpf - L.table), P.gpf.data(), 4 * P.gpf.size());
-    // the table, and the status, counters and BVH sort rows before it zeroed;
+    // the table, and the status, counters, BVH sort rows and vertex degrees before it zeroed;
     // with BAKE_FLAG_SAVE the seal takes this forward's nonce in the same
     // launch (the backward checks it on the device: any later forward on the
     // workspace overwrites it, and the stream orders it before the backward)
@@ -996,7 +995,7 @@ int32_t bake_visibility(const float* V, const int32_t* F, int64_t n_v, int64_t n
     std::vector<char> blob(L.grads - L.table, 0);
     memcpy(blob.data(), P.A.data(), sizeof(AssetDev));
     memcpy(blob.data() + (L.gpf - L.table), P.gpf.data(), 4 * P.gpf.size());
-    // the table, and the status, counters and BVH sort rows before it zeroed
+    // the table, and the status, counters, BVH sort rows and vertex degrees before it zeroed
     HIP_OR_FAIL(write_table(ws + L.table, blob.data(), (L.gpf - L.table) + 4 * P.gpf.size(), s, (uint32_t*)ws,
                             (int64_t)(L.table / 4)));
     forget_saved(workspace);
@@ -1090,7 +1089,7 @@ int32_t bake_view_maps(const float* V, const int32_t* F, const float* UV, int64_
     std::vector<char> blob(L.grads - L.table, 0);
     memcpy(blob.data(), P.A.data(), sizeof(AssetDev));
     memcpy(blob.data() + (L.gpf - L.table), P.gpf.data(), 4 * P.gpf.size());
-    // the table, and the status, counters and BVH sort rows before it zeroed
+    // the table, and the status, counters, BVH sort rows and vertex degrees before it zeroed
     HIP_OR_FAIL(write_table(ws + L.table, blob.data(), (L.gpf - L.table) + 4 * P.gpf.size(), s, (uint32_t*)ws,
                             (int64_t)(L.table / 4)));
     forget_saved(workspace);

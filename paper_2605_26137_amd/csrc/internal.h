@@ -307,7 +307,7 @@ struct Layout {
     size_t scan_tmp;                              // block sums of the scans
     size_t facemap, level;                        // per texel
     size_t rays, hits;                            // per ray
-    size_t bounds_part, bounds;                   // centroid bounds: per sort tile, per asset
+    size_t bounds_part;                           // centroid bounds, parts of sort tiles
     size_t keys0, keys1, vals0, vals1, hist, sup; // radix sort of the BVH keys
     size_t nodes_c, leaves, items, item_cnt;      // tree; lists of waiting subtrees
     size_t spill;                                 // traversal stack spill

@@ -60,7 +60,7 @@ __device__ __forceinline__ float3 centroid(const float* __restrict__ V, int3 t) 
 __device__ __forceinline__ int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // ---------------------------------------------------------------------------
-// 1. centroid bounds: a partial per sort tile, then one workgroup per asset
+// 1. centroid bounds: partials per sort tile, which every code tile reduces
 // ---------------------------------------------------------------------------
 
 __device__ __forceinline__ float wave_min(float v) {
@@ -136,19 +136,6 @@ __global__ __launch_bounds__(kBlock) void bounds_part_kernel(Batch Bt, float* __
     block_minmax6(v, part + 6 * (kBoundsSplit * (As.stile + lt) + sub));
 }
 
-__global__ __launch_bounds__(kBlock) void bounds_final_kernel(Batch Bt, const float* __restrict__ part,
-                                                              float* __restrict__ bounds) {
-    const AssetDev& As = Bt.A[blockIdx.x];
-    const int64_t nparts = kBoundsSplit * ceil_div(As.nhf, kSortTile);
-    const float* p = part + 6 * kBoundsSplit * As.stile;
-    float v[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
-    for (int64_t i = threadIdx.x; i < nparts; i += kBlock) {
-        for (int k = 0; k < 3; ++k) v[k] = fminf(v[k], p[6 * i + k]);
-        for (int k = 3; k < 6; ++k) v[k] = fmaxf(v[k], p[6 * i + k]);
-    }
-    block_minmax6(v, bounds + 6 * (int64_t)blockIdx.x);
-}
-
 // ---------------------------------------------------------------------------
 // 2. Morton codes (value = asset-local triangle index)
 // ---------------------------------------------------------------------------
@@ -176,22 +163,6 @@ __device__ __forceinline__ uint32_t morton(float3 c, const float* bounds) {
     uint32_t x = quant10(c.x, bounds[0], ix), y = quant10(c.y, bounds[1], iy),
              z = quant10(c.z, bounds[2], iz);
     return (spread10(x) << 2) | (spread10(y) << 1) | spread10(z);
-}
-
-__global__ __launch_bounds__(kBlock) void morton_kernel(Batch Bt, const float* __restrict__ bounds_all,
-                                                        uint32_t* __restrict__ keys,
-                                                        uint32_t* __restrict__ vals) {
-    int64_t lb;
-    const int a = block_asset(Bt, kGHiF, blockIdx.x, &lb);
-    const AssetDev& As = Bt.A[a];
-    const int64_t g = lb * kBlock + threadIdx.x;
-    if (g >= As.nhf) return;
-    const float* bounds = bounds_all + 6 * (int64_t)a;
-    bool bad;
-    int3 t = tri_idx(As.hi_F, g, As.nhv, &bad);
-    float3 c = centroid(As.hi_V, t);
-    keys[As.hf + g] = morton(c, bounds);
-    vals[As.hf + g] = (uint32_t)g;
 }
 
 // ---------------------------------------------------------------------------
@@ -372,6 +343,66 @@ struct HistArgs {
     const uint32_t *pairs, *bucket;
     uint32_t *kout, *vout, *bt_pf;
 };
+
+// Codes of a sort tile, their indices and the first pass's digit counts.  Each
+// tile reduces its asset's partial bounds by itself (four per tile of the asset, from
+// L2), which a launch by one workgroup per asset did in 2.4 to 4.8 us, and counts
+// the digits that a histogram launch read the keys again for.
+__global__ __launch_bounds__(kSortBlock) __attribute__((amdgpu_waves_per_eu(8))) void code_kernel(
+    Batch Bt, const float* __restrict__ part, uint32_t* __restrict__ keys, uint32_t* __restrict__ vals,
+    uint32_t* __restrict__ hist, uint32_t* __restrict__ sup) {
+    __shared__ uint32_t h[256];
+    __shared__ float s_red[kSortWaves][6];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const SortTile T = sort_tile<false>(Bt, blockIdx.x);
+    int64_t lt;
+    const AssetDev& As = Bt.A[block_asset(Bt, kGSort, blockIdx.x, &lt)];
+    const float* __restrict__ V = As.hi_V;
+    const int32_t* __restrict__ F = As.hi_F;
+    const int64_t g0 = lt * kSortTile + tid;
+    int3 t[kSortRounds];
+#pragma unroll
+    for (int r = 0; r < kSortRounds; ++r) {
+        bool bad;
+        t[r] = tri_idx(F, min(g0 + (int64_t)r * kSortBlock, T.count - 1), As.nhv, &bad);
+    }
+    const int64_t nparts = kBoundsSplit * ceil_div(T.count, kSortTile);
+    const float* p = part + 6 * kBoundsSplit * As.stile;
+    float v[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    for (int64_t i = tid; i < nparts; i += kSortBlock)
+#pragma unroll
+        for (int k = 0; k < 6; ++k) v[k] = k < 3 ? fminf(v[k], p[6 * i + k]) : fmaxf(v[k], p[6 * i + k]);
+    float3 c[kSortRounds];
+#pragma unroll
+    for (int r = 0; r < kSortRounds; ++r) c[r] = centroid(V, t[r]);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) v[k] = k < 3 ? wave_min(v[k]) : wave_max(v[k]);
+    if (lane == 0)
+#pragma unroll
+        for (int k = 0; k < 6; ++k) s_red[wave][k] = v[k];
+    if (tid < 256) h[tid] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        const float x = s_red[lane & (kSortWaves - 1)][k];
+        v[k] = k < 3 ? wave_min(x) : wave_max(x);
+    }
+#pragma unroll
+    for (int r = 0; r < kSortRounds; ++r) {
+        const int64_t g = g0 + (int64_t)r * kSortBlock;
+        if (g >= T.count) break;
+        const uint32_t key = morton(c[r], v);
+        keys[T.start + g] = key;
+        vals[T.start + g] = (uint32_t)g;
+        atomicAdd(&h[key & 255u], 1u);
+    }
+    __syncthreads();
+    if (tid < 256) {
+        const uint32_t n = h[tid];
+        hist[T.hbase + 256 * T.lt + tid] = n;
+        if (n) atomicAdd(&sup[T.sbase + 256 * (T.lt / kSuper) + tid], n);
+    }
+}
 
 template <int WHICH>
 __global__ __launch_bounds__(kSortBlock) __attribute__((amdgpu_waves_per_eu(8))) void radix_hist_kernel(HistArgs p) {
@@ -1187,7 +1218,7 @@ hipError_t launch_sort(const BatchHost& H, int which, int bits, bool* result_in_
                 hipLaunchKernelGGL(radix_hist_kernel<kSortPairsFirst>, grid, dim3(kSortBlock), 0, s, h);
         } else if (bwd) {
             hipLaunchKernelGGL(radix_hist_kernel<kSortPairs>, grid, dim3(kSortBlock), 0, s, h);
-        } else {
+        } else if (p > 0) {  // code_kernel counted the first pass's digits
             hipLaunchKernelGGL(radix_hist_kernel<kSortBvhKeys>, grid, dim3(kSortBlock), 0, s, h);
         }
         if (p == 0 && after_first && (e = hipEventRecord(after_first, s)) != hipSuccess) return e;
@@ -1212,7 +1243,6 @@ hipError_t launch_bvh_build(const BatchHost& H, hipStream_t s) {
     char* ws = H.ws;
     hipError_t e;
     float* part = (float*)(ws + L.bounds_part);
-    float* bounds = (float*)(ws + L.bounds);
     uint32_t* k0 = (uint32_t*)(ws + L.keys0);
     uint32_t* v0 = (uint32_t*)(ws + L.vals0);
     BvhNodeC* nodes_c = (BvhNodeC*)(ws + L.nodes_c);
@@ -1224,10 +1254,8 @@ hipError_t launch_bvh_build(const BatchHost& H, hipStream_t s) {
     } else {
         hipLaunchKernelGGL(bounds_part_kernel, dim3((unsigned)(H.blocks(kGSort) * kBoundsSplit)), dim3(kBlock), 0, s,
                            H.dev, part);
-        hipLaunchKernelGGL(bounds_final_kernel, dim3((unsigned)L.n), dim3(kBlock), 0, s, H.dev,
-                           (const float*)part, bounds);
-        hipLaunchKernelGGL(morton_kernel, dim3((unsigned)H.blocks(kGHiF)), dim3(kBlock), 0, s, H.dev,
-                           (const float*)bounds, k0, v0);
+        hipLaunchKernelGGL(code_kernel, dim3((unsigned)H.blocks(kGSort)), dim3(kSortBlock), 0, s, H.dev,
+                           (const float*)part, k0, v0, (uint32_t*)(ws + L.hist), (uint32_t*)(ws + L.sup));
         if ((e = hipGetLastError()) != hipSuccess) return e;
     
         bool in1 = false;

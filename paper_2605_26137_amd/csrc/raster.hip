@@ -121,10 +121,23 @@ __global__ __launch_bounds__(256) void lo_adj_kernel(Batch Bt, const uint32_t* _
 
 // Per vertex: sort its incident faces ascending (fixed summation order, so the
 // result does not depend on the order the adjacency was filled in), then
-// n_v = normalise(sum (V1 - V0) x (V2 - V0)).
-__global__ __launch_bounds__(256) void lo_normal_kernel(Batch Bt, const uint32_t* __restrict__ off,
-                                                        int32_t* __restrict__ adj,
-                                                        float4* __restrict__ lo_n) {
+// n_v = normalise(sum (V1 - V0) x (V2 - V0)).  The blocks past the vertices' clear
+// the face map, which the next launch claims texels in: a launch of its own took
+// 1.6 us at 128^2 and the gap before it; from the first low-poly launch the 67 MB
+// of 4096^2 held up the bounds on the other stream.
+constexpr int kFillPer = 4 * 256 * 4;  // texels a block and trip
+__global__ __launch_bounds__(256) void lo_normal_kernel(Batch Bt, int32_t vertex_blocks,
+                                                        const uint32_t* __restrict__ off, int32_t* __restrict__ adj,
+                                                        float4* __restrict__ lo_n, uint4* __restrict__ facemap,
+                                                        int64_t texels) {
+    if ((int32_t)blockIdx.x >= vertex_blocks) {
+        const uint4 none = make_uint4(kNoFace, kNoFace, kNoFace, kNoFace);
+        const int64_t step = (int64_t)(gridDim.x - vertex_blocks) * 256, quads = texels / 4;
+        const int64_t i0 = (int64_t)(blockIdx.x - vertex_blocks) * 256 + threadIdx.x;
+        for (int64_t i = i0; i < quads; i += step) facemap[i] = none;
+        if (i0 < texels - 4 * quads) reinterpret_cast<uint32_t*>(facemap)[4 * quads + i0] = kNoFace;
+        return;
+    }
     int64_t lb;
     const AssetDev& As = Bt.A[block_asset(Bt, kGLoV, blockIdx.x, &lb)];
     const int64_t v = lb * 256 + threadIdx.x;
@@ -566,8 +579,6 @@ hipError_t launch_lo_prep(const BatchHost& H, hipStream_t s) {
     uint32_t* off = (uint32_t*)(ws + L.lo_off);
     uint32_t* cur = (uint32_t*)(ws + L.lo_cur);
     hipError_t e;
-    if ((e = fill_u32(deg, 0, L.t_lv, s)) != hipSuccess) return e;
-    if ((e = fill_u32(cur, 0, L.t_lv, s)) != hipSuccess) return e;
     if (H.blocks(kGLoF) > 0) {
         hipLaunchKernelGGL(lo_face_kernel, dim3((unsigned)H.blocks(kGLoF)), dim3(256), 0, s, H.dev,
                            (float4*)(ws + L.face_t), (int4*)(ws + L.face_uv), deg);
@@ -582,9 +593,11 @@ hipError_t launch_lo_prep(const BatchHost& H, hipStream_t s) {
                            (const uint32_t*)off, cur, (int32_t*)(ws + L.lo_adj));
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    if (H.blocks(kGLoV) > 0) {
-        hipLaunchKernelGGL(lo_normal_kernel, dim3((unsigned)H.blocks(kGLoV)), dim3(256), 0, s, H.dev,
-                           (const uint32_t*)off, (int32_t*)(ws + L.lo_adj), (float4*)(ws + L.lo_n));
+    const int64_t vertices = H.blocks(kGLoV), fill = std::min<int64_t>((L.t_tex + kFillPer - 1) / kFillPer, 2048);
+    if (vertices + fill > 0) {
+        hipLaunchKernelGGL(lo_normal_kernel, dim3((unsigned)(vertices + fill)), dim3(256), 0, s, H.dev,
+                           (int32_t)vertices, (const uint32_t*)off, (int32_t*)(ws + L.lo_adj), (float4*)(ws + L.lo_n),
+                           (uint4*)(ws + L.facemap), L.t_tex);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return hipSuccess;
@@ -598,7 +611,6 @@ hipError_t launch_raster(const BatchHost& H, hipStream_t s, bool emit) {
     uint32_t* off = (uint32_t*)(ws + L.face_off);
     const int4* fuv = (const int4*)(ws + L.face_uv);
     hipError_t e;
-    if ((e = fill_u32(facemap, kNoFace, L.t_tex, s)) != hipSuccess) return e;
     const unsigned g = (unsigned)H.blocks(kGLoFWave);
     if (g > 0) {
         hipLaunchKernelGGL(raster_claim_kernel, dim3(g), dim3(kRasterBlock), 0, s, H.dev, fuv, facemap);
@@ -607,9 +619,6 @@ hipError_t launch_raster(const BatchHost& H, hipStream_t s, bool emit) {
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     // batch-wide scan: the face-ordered ray lists of the assets, concatenated
-    if ((e = exclusive_scan_u32(cnt, off, L.t_lf, (uint32_t*)(ws + L.scan_tmp), off + L.t_lf, s)) !=
-        hipSuccess)
-        return e;
     if ((e = launch_ray_spaces(H, s)) != hipSuccess) return e;
     if (g > 0 && emit) {
         hipLaunchKernelGGL(raster_emit_kernel, dim3(g), dim3(kRasterBlock), 0, s, H.dev, fuv,

@@ -113,8 +113,7 @@ __global__ __launch_bounds__(kScanBlock) void scan_down_kernel(const uint32_t* i
 // LDS, with a running carry between tiles.
 constexpr int kSmallBlock = 1024;
 constexpr int kSmallItems = 8;
-__global__ __launch_bounds__(kSmallBlock) void scan_small_kernel(const uint32_t* in, uint32_t* out,
-                                                                 int64_t n, uint32_t* total) {
+__device__ void scan_small(const uint32_t* in, uint32_t* out, int64_t n, uint32_t* total) {
     __shared__ uint32_t lw[kSmallBlock / 64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     uint32_t carry = 0;
@@ -152,6 +151,11 @@ __global__ __launch_bounds__(kSmallBlock) void scan_small_kernel(const uint32_t*
         carry += tot;
     }
     if (threadIdx.x == 0 && total) *total = carry;
+}
+
+__global__ __launch_bounds__(kSmallBlock) void scan_small_kernel(const uint32_t* in, uint32_t* out,
+                                                                 int64_t n, uint32_t* total) {
+    scan_small(in, out, n, total);
 }
 
 // Table writer: one chunk of host bytes travels as a by-value kernel
@@ -206,9 +210,7 @@ __device__ void asset_prefix(uint32_t v, int a, int n, uint32_t* out, uint32_t* 
 // After the raster: the ray list is the concatenation of the assets' face-
 // ordered lists, and the exclusive scan of the per-face counts (total at
 // index t_lf) gives every face's first ray.
-__global__ __launch_bounds__(kPrefixBlock) void ray_spaces_kernel(Batch B, const uint32_t* face_off,
-                                                                 int64_t t_lf, uint32_t* ray_pf,
-                                                                 uint32_t* rb_pf) {
+__device__ void ray_spaces(const Batch& B, const uint32_t* face_off, int64_t t_lf, uint32_t* ray_pf, uint32_t* rb_pf) {
     __shared__ uint32_t lw[kPrefixBlock / 64];
     __shared__ uint32_t carry;
     if (threadIdx.x == 0) carry = 0;
@@ -229,6 +231,21 @@ __global__ __launch_bounds__(kPrefixBlock) void ray_spaces_kernel(Batch B, const
         ray_pf[B.n] = face_off[t_lf];
         rb_pf[B.n] = carry;
     }
+}
+
+__global__ __launch_bounds__(kPrefixBlock) void ray_spaces_kernel(Batch B, const uint32_t* face_off,
+                                                                 int64_t t_lf, uint32_t* ray_pf,
+                                                                 uint32_t* rb_pf) {
+    ray_spaces(B, face_off, t_lf, ray_pf, rb_pf);
+}
+
+// The scan before it and the spaces in one launch, where one workgroup scans.
+__global__ __launch_bounds__(kPrefixBlock) void ray_scan_kernel(Batch B, const uint32_t* cnt, uint32_t* face_off,
+                                                               int64_t t_lf, uint32_t* ray_pf, uint32_t* rb_pf) {
+    static_assert(kPrefixBlock == kSmallBlock, "one workgroup size");
+    scan_small(cnt, face_off, t_lf, face_off + t_lf);
+    __syncthreads();
+    ray_spaces(B, face_off, t_lf, ray_pf, rb_pf);
 }
 
 // After the backward's rays: the prefix of the merged pairs' bucket sums over the
@@ -328,9 +345,19 @@ hipError_t write_table(void* dst, const void* src, size_t bytes, hipStream_t s, 
 
 hipError_t launch_ray_spaces(const BatchHost& H, hipStream_t s) {
     const Layout& L = H.L;
-    hipLaunchKernelGGL(ray_spaces_kernel, dim3(1), dim3(kPrefixBlock), 0, s, H.dev,
-                       (const uint32_t*)(H.ws + L.face_off), L.t_lf, (uint32_t*)(H.ws + L.ray_pf),
-                       (uint32_t*)(H.ws + L.rb_pf));
+    uint32_t* cnt = (uint32_t*)(H.ws + L.face_cnt);
+    uint32_t* off = (uint32_t*)(H.ws + L.face_off);
+    uint32_t* ray_pf = (uint32_t*)(H.ws + L.ray_pf);
+    uint32_t* rb_pf = (uint32_t*)(H.ws + L.rb_pf);
+    if (L.t_lf > 0 && L.t_lf <= (int64_t)kSmallBlock * kSmallItems) {
+        hipLaunchKernelGGL(ray_scan_kernel, dim3(1), dim3(kPrefixBlock), 0, s, H.dev, (const uint32_t*)cnt, off, L.t_lf,
+                           ray_pf, rb_pf);
+        return hipGetLastError();
+    }
+    const hipError_t e = exclusive_scan_u32(cnt, off, L.t_lf, (uint32_t*)(H.ws + L.scan_tmp), off + L.t_lf, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(ray_spaces_kernel, dim3(1), dim3(kPrefixBlock), 0, s, H.dev, (const uint32_t*)off, L.t_lf, ray_pf,
+                       rb_pf);
     return hipGetLastError();
 }
 
