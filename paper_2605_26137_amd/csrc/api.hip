@@ -466,10 +466,17 @@ int32_t check_workspace(const void* ws, size_t bytes, const Layout& L) {
 // the caller's stream).  Default priority.  The fork-join enqueue is
 // serialised so that concurrent callers never see each other's event records.
 constexpr int kMaxDevices = 64;
-constexpr int64_t kSideMinFaces = 1 << 16;  // high-poly faces of a batch below which one stream is used
+// High-poly faces of a batch from which the second stream is used.  A forward that
+// saves for a backward is one of a training step's many launches, which wait for
+// the host below this: the fork and join cost a 256^2 step at 20,000 faces more of it
+// than the 6 us they save the device.  A bake or view maps alone: 129 -> 110 us at 5,120 faces and 128^2,
+// 115 -> 97 at 2,000, 210 -> 184 at 20,000 and 512^2, 630 -> 587 for ten views
+// at 20,480; 115 -> 119 at 1,000.
+constexpr int64_t kSideMinFaces = 1 << 16, kSideMinFacesAlone = 1 << 11;
 struct Side {
     hipStream_t s = nullptr;
     hipEvent_t fork = nullptr, join = nullptr;
+    hipStream_t caller = nullptr;  // stream of the last call of few faces (compared only)
 };
 Side g_side[kMaxDevices];
 std::mutex g_side_mu;
@@ -496,6 +503,23 @@ Side* side_stream(hipStream_t s) {
     return &d;
 }
 
+// The second stream for a call on s over `faces` faces, null to do without.  Bakes
+// of few faces on several streams overlap each other better than their own two
+// chains, which would all meet in this one stream (four streams of 5,120 faces: 79
+// us a bake against 40): below kSideMinFaces a call takes it only when the call
+// before it on the device came from the same stream.  Captured work runs with its
+// graph.
+Side* side_for(hipStream_t s, int64_t faces, bool alone) {
+    Side* d = faces < (alone ? kSideMinFacesAlone : kSideMinFaces) ? nullptr : side_stream(s);
+    if (!d || faces >= kSideMinFaces) return d;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) return nullptr;
+    if (st != hipStreamCaptureStatusNone) return d;
+    const bool same = d->caller == s;
+    d->caller = s;
+    return same ? d : nullptr;
+}
+
 // The forward launch sequence of a planned batch.
 int32_t run_forward(Plan& P, const Opts& o, void* workspace, hipStream_t s) {
     char* ws = (char*)workspace;
@@ -516,11 +540,9 @@ int32_t run_forward(Plan& P, const Opts& o, void* workspace, hipStream_t s) {
     const uint32_t nonce = save ? reserve_nonce() : 0u;
     HIP_OR_FAIL(write_table(ws + L.table, blob.data(), (L.gpf - L.table) + 4 * P.gpf.size(), s, (uint32_t*)ws,
                             (int64_t)(L.table / 4), save ? (int64_t)(L.gcnt / 4 + kGcSeal) : -1, nonce));
-    // small bakes run on one stream: there the fork and join cost more than
-    // the overlap saves
     const bool one_stream = (o.flags & BAKE_FLAG_ONE_STREAM) != 0;
     std::unique_lock<std::mutex> side_lock(g_side_mu);
-    Side* side = L.t_hf >= kSideMinFaces && !one_stream ? side_stream(s) : nullptr;
+    Side* side = one_stream ? nullptr : side_for(s, L.t_hf, !save);
     if (side) {
         // the build, the longer chain, is enqueued first: kernels are handed
         // to the device one by one in the order they were enqueued (also on
@@ -576,7 +598,7 @@ int32_t run_backward(Plan& P, void* workspace, uint32_t nonce, bool one_stream, 
     HIP_OR_FAIL(write_table(ws + P.L.grads, P.G.data(), sizeof(AssetGrad) * (size_t)P.L.n, s,
                             (uint32_t*)(ws + P.L.bwd_sup), bwd_sort_zero_words(P.L)));
     std::lock_guard<std::mutex> side_lock(g_side_mu);
-    Side* side = P.L.t_hf >= kSideMinFaces && !one_stream ? side_stream(s) : nullptr;
+    Side* side = one_stream ? nullptr : side_for(s, P.L.t_hf, false);
     if (side) {
         HIP_OR_FAIL(launch_backward(H, any_lo, any_hi, s, side->s, side->fork, side->join));
     } else {
@@ -1093,10 +1115,26 @@ int32_t bake_view_maps(const float* V, const int32_t* F, const float* UV, int64_
     HIP_OR_FAIL(write_table(ws + L.table, blob.data(), (L.gpf - L.table) + 4 * P.gpf.size(), s, (uint32_t*)ws,
                             (int64_t)(L.table / 4)));
     forget_saved(workspace);
-    HIP_OR_FAIL(launch_lo_prep(H, s));
-    HIP_OR_FAIL(launch_raster(H, s, false));
-    HIP_OR_FAIL(tim_record(tim, 1, s));
-    HIP_OR_FAIL(launch_bvh_build(H, s));
+    {
+        std::unique_lock<std::mutex> side_lock(g_side_mu);
+        Side* side = side_for(s, L.t_hf, true);
+        if (side) {
+            HIP_OR_FAIL(hipEventRecord(side->fork, s));
+            HIP_OR_FAIL(launch_bvh_build(H, s));
+            HIP_OR_FAIL(hipStreamWaitEvent(side->s, side->fork, 0));
+            HIP_OR_FAIL(launch_lo_prep(H, side->s));
+            HIP_OR_FAIL(launch_raster(H, side->s, false));
+            HIP_OR_FAIL(tim_record(tim, 1, side->s));
+            HIP_OR_FAIL(hipEventRecord(side->join, side->s));
+            HIP_OR_FAIL(hipStreamWaitEvent(s, side->join, 0));
+        } else {
+            side_lock.unlock();
+            HIP_OR_FAIL(launch_lo_prep(H, s));
+            HIP_OR_FAIL(launch_raster(H, s, false));
+            HIP_OR_FAIL(tim_record(tim, 1, s));
+            HIP_OR_FAIL(launch_bvh_build(H, s));
+        }
+    }
     HIP_OR_FAIL(tim_record(tim, 2, s));
     float* depth = depth_out ? depth_out : (float*)(ws + M.depth);
     VisRun vr{};
