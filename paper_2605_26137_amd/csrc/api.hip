@@ -508,7 +508,7 @@ Side* side_stream(hipStream_t s) {
 // chains, which would all meet in this one stream (four streams of 5,120 faces: 79
 // us a bake against 40): below kSideMinFaces a call takes it only when the call
 // before it on the device came from the same stream.  Captured work runs with its
-// graph.
+// graph, and timed calls of few faces keep their stages apart.
 Side* side_for(hipStream_t s, int64_t faces, bool alone) {
     Side* d = faces < (alone ? kSideMinFacesAlone : kSideMinFaces) ? nullptr : side_stream(s);
     if (!d || faces >= kSideMinFaces) return d;
@@ -542,7 +542,7 @@ int32_t run_forward(Plan& P, const Opts& o, void* workspace, hipStream_t s) {
                             (int64_t)(L.table / 4), save ? (int64_t)(L.gcnt / 4 + kGcSeal) : -1, nonce));
     const bool one_stream = (o.flags & BAKE_FLAG_ONE_STREAM) != 0;
     std::unique_lock<std::mutex> side_lock(g_side_mu);
-    Side* side = one_stream ? nullptr : side_for(s, L.t_hf, !save);
+    Side* side = one_stream ? nullptr : side_for(s, L.t_hf, !save && !tim);
     if (side) {
         // the build, the longer chain, is enqueued first: kernels are handed
         // to the device one by one in the order they were enqueued (also on
@@ -1117,14 +1117,13 @@ int32_t bake_view_maps(const float* V, const int32_t* F, const float* UV, int64_
     forget_saved(workspace);
     {
         std::unique_lock<std::mutex> side_lock(g_side_mu);
-        Side* side = side_for(s, L.t_hf, true);
+        Side* side = tim ? nullptr : side_for(s, L.t_hf, true);
         if (side) {
             HIP_OR_FAIL(hipEventRecord(side->fork, s));
             HIP_OR_FAIL(launch_bvh_build(H, s));
             HIP_OR_FAIL(hipStreamWaitEvent(side->s, side->fork, 0));
             HIP_OR_FAIL(launch_lo_prep(H, side->s));
             HIP_OR_FAIL(launch_raster(H, side->s, false));
-            HIP_OR_FAIL(tim_record(tim, 1, side->s));
             HIP_OR_FAIL(hipEventRecord(side->join, side->s));
             HIP_OR_FAIL(hipStreamWaitEvent(s, side->join, 0));
         } else {
