@@ -169,12 +169,12 @@ constexpr int kMaxFusedPasses = 4;  // more dilation passes run one launch per p
 // Tree build: leaves per tile, tiles (groups) per group and in the last group,
 // and the most subtrees that a tile or group leaves waiting: along each of its
 // two edges one per distinct prefix length (62).
-constexpr int kBuildTile = 1024, kJoin = 64, kJoinLast = 128, kSpine = 128;
+constexpr int kBuildTile = 1024, kJoinLog = 6, kJoin = 1 << kJoinLog, kJoinLast = 128, kSpine = 128;
 constexpr int kJoinLevels = 4;  // 2^30 leaves: 2^20 tiles, 16384, 256, 4, 1 groups
 static_assert(kSpine >= 2 * 62, "a list holds every waiting subtree");
 // Groups of a level of an asset with n leaves (level 0: tiles) and the leaves
 // that each covers; its rows in the level's lists: asset a's start at tile_base
-// / 64^level + a, which keeps assets apart.
+// / kJoin^level + a, which keeps assets apart.
 __host__ __device__ inline int64_t join_groups(int64_t n, int level, int64_t* span_out) {
     int64_t span = kBuildTile, g = (n + span - 1) / span;
     for (int l = 0; l < level; ++l) {
@@ -185,10 +185,10 @@ __host__ __device__ inline int64_t join_groups(int64_t n, int level, int64_t* sp
     return g;
 }
 __host__ __device__ inline int64_t join_row(int64_t tile_base, int64_t a, int level) {
-    return level == 0 ? tile_base : (tile_base >> (6 * level)) + a;
+    return level == 0 ? tile_base : (tile_base >> (kJoinLog * level)) + a;
 }
 __host__ __device__ inline int64_t join_rows(int64_t tiles, int64_t n, int level) {
-    return level == 0 ? tiles : (tiles >> (6 * level)) + n + 1;
+    return level == 0 ? tiles : (tiles >> (kJoinLog * level)) + n + 1;
 }
 
 // Per-asset counter slots.
