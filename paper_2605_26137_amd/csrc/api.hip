@@ -251,9 +251,14 @@ int32_t make_plan(const Sizes* z, int n, uint32_t flags, Plan* P) {
     L.hist = take(4 * 256 * (size_t)L.t_stile);
     L.nodes_c = take(32 * (size_t)L.t_node);
     L.leaves = take(48 * (size_t)L.t_hf);
+    // lists for the levels that some asset reaches; a tile that is a whole asset
+    // leaves nothing waiting
     int64_t rows = 0;
-    for (int level = 0; level <= kJoinLevels; ++level) rows += join_rows(L.t_tl, n, level);
-    L.items = take(32 * (size_t)kSpine * (size_t)rows);
+    const auto joins = [&](int level) {
+        return level >= 1 && level <= kJoinLevels && P->gpf[(size_t)(kGJoin1 + level - 1) * (n + 1) + n] > 0;
+    };
+    for (int level = 0; level == 0 || joins(level); ++level) rows += join_rows(L.t_tl, n, level);
+    L.items = take(joins(1) ? 32 * (size_t)kSpine * (size_t)rows : 0);
     L.item_cnt = take(4 * (size_t)rows);
     L.spill = take(4 * (size_t)kMaxDepth * (size_t)L.spill_lanes);
     if (L.save) {

@@ -4,7 +4,8 @@
 //   1. reduction of the triangle-centroid bounds,
 //   2. 30-bit Morton code of each centroid, value = original triangle index,
 //   3. stable LSD radix sort of (code, index), 8-bit digits, LDS-ranked with
-//      wave64 ballots, so equal codes keep ascending index order,
+//      wave64 ballots, so equal codes keep ascending index order (assets of at
+//      most 8,192 triangles: 1 to 3 by one workgroup, 10-bit digits),
 //   4. hierarchy, boxes and compressed nodes in one pass, bottom-up: a subtree
 //      joins the neighbour it shares the longer common prefix with (code,
 //      extended by the index on equal codes), so the tree is the radix tree over
