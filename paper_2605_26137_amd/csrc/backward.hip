@@ -173,10 +173,10 @@ __device__ __forceinline__ int merge_pairs(MergeLds& S, int lane, bool hit, cons
 // its bucket's.
 //
 // Bound by memory (rays, hits and the gathered corners in, 36 B of low-poly
-// terms out), which hides the merging.  A dense mesh has some forty vertices
-// under a wave's rays, so that a fifth of the pairs is left to sort and to add
-// up: at 1.9M rays on 655k vertices the sort 139 -> 85 us, bwd_hiN_kernel
-// 44 -> 20 and this kernel 50 -> 48 (it wrote 56 B per ray for the pairs), at 7.8M
+// terms out), which hides the merging.  A dense mesh has some sixty vertices
+// under a wave's rays, so that a third of the pairs is left to sort and to add
+// up: at 1.08M rays on 657k vertices the sort 139 -> 85 us, bwd_hiN_kernel
+// 44 -> 20 and this kernel 50 -> 48 (it wrote 56 B per ray for the pairs), at 4.3M
 // rays on 2.6M vertices this kernel 202 -> 179 and bwd_hiN_kernel 169 -> 61.
 struct RayArgs {
     Batch B;

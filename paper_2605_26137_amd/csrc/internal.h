@@ -224,7 +224,7 @@ struct Batch {
 
 // Merged pairs of the backward, per 64-ray batch and in sums over kPairBucket
 // of an asset's batches (asset a's sums start at pair_bucket(rb_pf[a], a)).  A sum
-// has a cache line to itself: 30,000 waves adding into 120 sums of one word each
+// has a cache line to itself: 17,000 waves adding into 66 sums of one word each
 // took 85 us.
 constexpr int kPairBucket = 256;
 constexpr int kBucketStride = 32;

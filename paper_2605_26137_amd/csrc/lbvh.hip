@@ -235,7 +235,7 @@ __device__ __forceinline__ int tile_thread() {
 
 // The keys of the backward's first pass lie batch by batch, each batch's at three
 // times its first ray.  Draws tile T's together into kout, with their places as
-// values, and counts their digits in h.  A batch has some forty of 192: the
+// values, and counts their digits in h.  A batch has some sixty of 192: the
 // bucket that holds the tile's first pair comes from the buckets' prefix, the
 // batches from there on are summed 1,024 at a time, and a wave copies a batch.
 // ONE: an asset by itself of at most 1,024 batches, which this launch sums
