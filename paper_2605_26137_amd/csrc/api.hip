@@ -514,12 +514,20 @@ Side* side_stream(hipStream_t s) {
 // us a bake against 40): below kSideMinFaces a call takes it only when the call
 // before it on the device came from the same stream.  Captured work runs with its
 // graph, and timed calls of few faces keep their stages apart.
+// A capture that forked into the second stream holds it until it ends; a call
+// outside of that capture does without.
 Side* side_for(hipStream_t s, int64_t faces, bool alone) {
     Side* d = faces < (alone ? kSideMinFacesAlone : kSideMinFaces) ? nullptr : side_stream(s);
-    if (!d || faces >= kSideMinFaces) return d;
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &st) != hipSuccess) return nullptr;
-    if (st != hipStreamCaptureStatusNone) return d;
+    if (!d) return nullptr;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone, held = hipStreamCaptureStatusNone;
+    unsigned long long id = 0, held_id = 0;
+    if (hipStreamGetCaptureInfo(s, &st, &id) != hipSuccess ||
+        hipStreamGetCaptureInfo(d->s, &held, &held_id) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    if (held != hipStreamCaptureStatusNone && (st == hipStreamCaptureStatusNone || id != held_id)) return nullptr;
+    if (faces >= kSideMinFaces || st != hipStreamCaptureStatusNone) return d;
     const bool same = d->caller == s;
     d->caller = s;
     return same ? d : nullptr;

@@ -61,3 +61,42 @@ def test_streams(n):
         torch.cuda.synchronize()
         assert b.maps[0].cpu().numpy().tobytes() == got[0][0].tobytes()
         assert b.hits[0].cpu().numpy().tobytes() == got[0][1].tobytes()
+
+
+@pytest.mark.parametrize("n", [5120, 20480])
+def test_eager_beside_a_capture(n):
+    """A capture that forked into the second stream keeps it until it ends: bakes on
+    another stream meanwhile run without it."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2605_26137_amd.bake as B
+    V, F = _mesh(n)
+    lo_V, lo_F = M.icosphere(2)
+    t = [torch.as_tensor(np.ascontiguousarray(x)).cuda() for x in
+         (V, F, M.vertex_normals(V, F), lo_V.astype(np.float32), lo_F.astype(np.int32),
+          M.face_grid_atlas(lo_F.shape[0], 128))]
+    a, b = B.BakeBatch([(*t, 128, 0.3)]), B.BakeBatch([(*t, 128, 0.3)])
+    other = torch.cuda.Stream()
+    for _ in range(2):
+        a.forward()
+        b.forward(stream=other)
+        b.forward(stream=other)
+    torch.cuda.synchronize()
+    want = a.maps[0].cpu().numpy()
+    print(f"[gpu] eager beside a capture n={n}", flush=True)
+    b.maps[0].zero_()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        a.forward()
+        b.forward(stream=other)
+        b.forward(stream=other)
+        a.forward()
+    torch.cuda.synchronize()
+    assert b.maps[0].cpu().numpy().tobytes() == want.tobytes()
+    for _ in range(2):
+        a.maps[0].zero_()
+        graph.replay()
+        b.forward()
+        torch.cuda.synchronize()
+        assert a.maps[0].cpu().numpy().tobytes() == want.tobytes()
