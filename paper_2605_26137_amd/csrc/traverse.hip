@@ -1172,14 +1172,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(COUNT ? 1 :
                         if (mask) key[h] = (__float_as_uint(tn) & ~127u) | (uint32_t)k;
                         S.c[0][k] = make_float4(q0.x, q0.y, q0.z, q1.x);
                         S.c[1][k] = make_float4(q1.y, q1.z, q2.x, q2.y);
-                        S.c[2][k] = make_float4(q2.z, L.c.y, __uint_as_float(key[h]), __uint_as_float(mask));
+                        // (the bound without the number, which would raise it above tn)
+                        S.c[2][k] = make_float4(q2.z, L.c.y, __uint_as_float(key[h] & ~127u), __uint_as_float(mask));
                     }
                     n += __popcll(__ballot(mask != 0u));
                 }
                 // sorted by the bound: a triangle's place is the number of
                 // smaller keys (the keys are distinct: their low bits number
-                // the triangles, which lowers a bound by at most 2^-16);
-                // triangles that touch no tile come after the n that do
+                // the triangles; a bound keeps the bits above those, so it is
+                // lowered by at most 2^-16 and is one for every later triangle
+                // too); triangles that touch no tile come after the n that do
                 int p0 = 0, p1 = 0;
                 auto count = [&](uint32_t kj) {
                     p0 += kj < key[0] ? 1 : 0;

@@ -88,3 +88,46 @@ def test_few_faces(B):
         ids, _ = hits(B, V, F, eyes, [0, 0, 0], 0.2, 17, 4.0)
         assert (ids[:, 6:10, 6:10] == face).all()
         assert set(np.unique(ids)) <= {-1, face}
+
+
+def coincident_sheets(n, pitch, seed):
+    """Two n x n sheets of quads in z = 0 with the same corners, faces in random
+    order, and two far triangles that leave the sheets' faces in one cell of the
+    tree's codes (so that the tree splits them by index); partner[f] = the face
+    that coincides with f."""
+    rng = np.random.default_rng(seed)
+    i, j = (x.ravel() for x in np.meshgrid(np.arange(n + 1), np.arange(n + 1), indexing="ij"))
+    V = np.stack([(i - n / 2) * pitch, (j - n / 2) * pitch, 0 * i], 1)
+    q = (np.arange(n)[:, None] * (n + 1) + np.arange(n)).ravel()
+    half = np.concatenate([np.stack([q, q + n + 1, q + 1], 1), np.stack([q + 1, q + n + 1, q + n + 2], 1)])
+    order = rng.permutation(2 * len(half))
+    place = np.argsort(order)  # where face k of the pair of sheets went
+    partner = np.empty(len(order), np.int64)
+    partner[place] = np.concatenate([place[len(half):], place[:len(half)]])
+    F = np.concatenate([half, half])[order]
+    far = 40 * np.array([[-1, -1, -1], [-1, -1.1, -1], [-1.1, -1, -1], [1, 1, 1.1], [1, 1.1, 1], [1.1, 1, 1]]) + 0.02
+    F = np.concatenate([F, len(V) + np.arange(6).reshape(2, 3)])
+    return (np.concatenate([V, far]).astype(np.float32), F.astype(np.int32),
+            np.concatenate([partner, len(partner) + np.arange(2)]))
+
+
+def test_equal_distances_take_the_lower_index(B, oracle_lib):
+    """Coincident faces seen head-on through a narrow lens: some hundred triangles
+    in a tile, all at one distance to a few ulp, two at every pixel."""
+    t_far = 1.5
+    z = 1.0 + np.arange(64) * 1.7e-5
+    eyes = np.stack([0 * z, 0 * z, z], 1).astype(np.float32)
+    for seed in range(12):
+        V, F, partner = coincident_sheets(13, 0.000476, seed)
+        ids, r = hits(B, V, F, eyes, [0, 0, 0], 0.001, 8, t_far)
+        assert (ids >= 0).all()
+        higher = ids > partner[ids]
+        print(f"[gpu] coincident sheets {seed}: {higher.sum()} of {ids.size} pixels take the higher index", flush=True)
+        assert not higher.any()
+        vis = np.zeros(F.shape[0], bool)
+        vis[np.unique(ids)] = True
+        assert np.array_equal(r.visible.cpu().numpy(), vis)
+        P, D = oracle_lib.camera_rays(eyes[:4], [0, 0, 0], 0.001, 8)
+        o_ids, o_t = oracle_lib.first_hit(V, F, P, D, t_far, "brute")
+        rep = check_first_hits(oracle_lib, V, F, P, D, ids[:4], o_ids, o_t, t_far, 0.9, "brute")
+        assert rep.ok(), str(rep)
