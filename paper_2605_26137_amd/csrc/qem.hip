@@ -37,7 +37,7 @@
 // Q [nv][10] in FP64 (q00 q01 q02 q03 q11 q12 q13 q22 q23 q33); face slots
 // [3] in their original order, dead ones marked by a negative first corner;
 // per vertex a list of its faces (off, num) in an arena; per round the sorted
-// unique neighbours (16 slots per vertex), the edges [ne][2], their float32
+// unique neighbours (16 slots per vertex, longer rings apart), the edges [ne][2], their float32
 // cost bits (0xFFFFFFFF: not collapsible), face counts and FP64 placements, and
 // the list of winners.
 //
@@ -68,6 +68,16 @@ namespace {
 
 constexpr int kQB = 256;                    // threads per block of the per-element kernels
 constexpr uint32_t kNoKey = 0xFFFFFFFFu;    // cost bits of a non-collapsible edge
+
+constexpr int kRingFaces = 16;              // faces per vertex sorted in registers (see the rings)
+
+// Counter slots
+constexpr int kQcEdges = 0, kQcValid = 1, kQcTau = 2, kQcLive = 3, kQcApplied = 4, kQcLiveNext = 5, kQcStatus = 6,
+              kQcOut = 7, kQcVerts = 8, kQcDone = 9, kQcDoneNext = 10, kQcArena = 11, kQcPrefix0 = 12, kQcRem0 = 13,
+              kQcPrefix1 = 14, kQcRem1 = 15, kQcWinners = 16 /* u64: winners | faces they remove << 32 */,
+              kQcRing = 18 /* entries of long rings this round */, kQcGather = 19 /* entries gathered for sorting */,
+              kQcLong = 20 /* lists of more than kRingFaces faces */, kQcLongIn = 21 /* of the input */,
+              kQcSlots = 32;
 
 inline int64_t blocks_for(int64_t n) { return n <= 0 ? 1 : (n + kQB - 1) / kQB; }
 
@@ -135,10 +145,11 @@ __global__ void qem_adj_kernel(const int32_t* __restrict__ F, int64_t live, cons
 // unordered list is walked by repeated minimum search).
 __global__ void qem_quadric_kernel(const double* __restrict__ P, const int32_t* __restrict__ F, int64_t nv,
                                    const uint32_t* __restrict__ off, const uint32_t* __restrict__ num,
-                                   const uint32_t* __restrict__ adj, double* __restrict__ Q) {
+                                   const uint32_t* __restrict__ adj, double* __restrict__ Q, uint32_t* __restrict__ cnt) {
     const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (v >= nv) return;
     const uint32_t b = off[v], n = num[v];
+    if (n > (uint32_t)kRingFaces) atomicAdd(&cnt[kQcLongIn], 1u);
     double q[10];
     for (int j = 0; j < 10; ++j) q[j] = 0.0;
     int64_t last = -1;
@@ -188,11 +199,6 @@ __device__ __forceinline__ uint32_t shared_count(const int32_t* F, const uint32_
     return c;
 }
 
-// Counter slots
-constexpr int kQcEdges = 0, kQcValid = 1, kQcTau = 2, kQcLive = 3, kQcApplied = 4, kQcLiveNext = 5, kQcStatus = 6,
-              kQcOut = 7, kQcVerts = 8, kQcDone = 9, kQcDoneNext = 10, kQcArena = 11, kQcPrefix0 = 12, kQcRem0 = 13,
-              kQcPrefix1 = 14, kQcRem1 = 15, kQcWinners = 16 /* u64: winners | faces they remove << 32 */, kQcSlots = 32;
-
 // Cost-bit histograms: digits of 11, 11 and 10 bits.
 constexpr int kHistBins = 2048, kHistWords = 2 * kHistBins + 1024;
 constexpr int kSupBlocks = 32;  // ring blocks whose edge counts are summed together
@@ -202,14 +208,22 @@ constexpr int kSupBlocks = 32;  // ring blocks whose edge counts are summed toge
 // list are the unique neighbours in ascending order, and a run of length one
 // is an edge with a single face (v is then a boundary vertex).  The lists of up
 // to 8 and up to 16 faces are loaded whole (three load latencies) and sorted in
-// registers by a network (63 and 191 compare-exchanges; mean valence is six);
-// vertices with more take a slower path over global memory.
+// registers by a network (63 and 191 compare-exchanges; mean valence is six),
+// those of up to 24 too where many are that long (384).  A wave sorts one of up to
+// 256 faces in LDS, a workgroup a longer one, in LDS or, past 1,024 faces, in
+// global memory.
 // A ring entry is (x << 3) | min(faces shared with x, 7): the ring carries
 // each edge's face count for the per-edge evaluation (vertex indices are
-// below 2^28).  Rings of up to kRingKeep vertices are kept in slots; of longer
-// ones only the counts are (info), and the passes walk the face list instead.
+// below 2^28).  Rings of up to kRingKeep vertices are kept in slots of the
+// vertex; the first slot of a longer ring says where in RingArgs::longs it lies.
+// Only where those run out (many edges of a single face around few vertices) the
+// passes walk the face list instead, at a cubic cost.
+// 46,080 faces, every ninth vertex with 24 of them, -> 2,304: 5.8 ms, 151 with every
+// ring past 16 walked, 10.9 with a wave for each.
 constexpr int kRB = 256;        // threads per block of the ring and edge kernels
-constexpr int kRingFaces = 16;  // faces per vertex sorted in registers
+constexpr int kRingWide = 24;   // faces per vertex sorted in registers where many lists are long
+constexpr int kRingWave = 256;  // by a wave
+constexpr int kRingLds = 4 * 2 * kRingWave;  // entries a workgroup sorts in LDS
 constexpr int kRingKeep = 16;   // ring entries kept per vertex
 constexpr uint32_t kBoundary = 1u << 31;  // info: boundary flag, the ring's length below it
 
@@ -255,6 +269,9 @@ struct RingArgs {
     int64_t nv;
     uint32_t *off, *num, *adj;
     int32_t* ring;      // [nv][kRingKeep]
+    int32_t* longs;     // [longs_n] longer rings
+    uint32_t longs_n;
+    int32_t* gather;    // lists that exceed LDS: 2^ceil(log2(2n)) entries each, less than 12 per face in all
     uint32_t* info;     // [nv]
     uint32_t* hcnt;     // [nv] neighbours above v
     uint32_t *part, *sup;  // edges per block and per kSupBlocks blocks
@@ -262,10 +279,153 @@ struct RingArgs {
     uint32_t *hist, *cnt;
 };
 
+// The ring of a vertex whose ring has no slots of its own, or null where the
+// walk over its faces has to do (see above).
+__device__ __forceinline__ const int32_t* long_ring(const int32_t* ring, const int32_t* longs, int64_t v) {
+    const int32_t at = ring[kRingKeep * v];
+    return at >= 0 ? longs + at : nullptr;
+}
+
+// Room for a ring of n entries: the vertex's slots or, past them, a place in
+// a.longs; null when that is full.
+__device__ __forceinline__ int32_t* ring_room(const RingArgs& a, int64_t v, uint32_t n) {
+    int32_t* slots = a.ring + (int64_t)kRingKeep * v;
+    if (n <= (uint32_t)kRingKeep) return slots;
+    const uint32_t at = atomicAdd(&a.cnt[kQcRing], n);
+    const bool fits = at <= a.longs_n && n <= a.longs_n - at;
+    slots[0] = fits ? (int32_t)at : -1;
+    return fits ? a.longs + at : nullptr;
+}
+
+// First entry of a sorted ring whose vertex is x or above, when there is one.
+__device__ __forceinline__ uint32_t ring_find(const int32_t* ring, uint32_t m, int32_t x) {
+    uint32_t at = 0;
+    for (uint32_t len = m; len > 1;) {
+        const uint32_t half = len >> 1;
+        at += (ring[at + half - 1] >> 3) < x ? half : 0u;
+        len -= half;
+    }
+    return at;
+}
+
+// What a vertex's ring is known by.
+struct RingSums {
+    uint32_t uniq, higher, boundary;
+};
+
+template <bool BLOCK>
+__device__ __forceinline__ void ring_sync() {
+    if constexpr (BLOCK) {
+        __syncthreads();
+    } else {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+}
+
+// Inclusive count of `on` over the group's threads up to this one, and in all.
+template <bool BLOCK>
+__device__ __forceinline__ uint32_t ring_count(bool on, uint32_t* s_wave, uint32_t* all) {
+    const uint64_t bal = __ballot(on);
+    uint32_t before = (uint32_t)__popcll(bal & __lanemask_lt()) + (on ? 1u : 0u), n = (uint32_t)__popcll(bal);
+    if constexpr (BLOCK) {
+        const int wave = threadIdx.x >> 6;
+        __syncthreads();
+        if ((threadIdx.x & 63) == 0) s_wave[wave] = n;
+        __syncthreads();
+        n = 0;
+        for (int w = 0; w < kRB / 64; ++w) {
+            if (w < wave) before += s_wave[w];
+            n += s_wave[w];
+        }
+    }
+    *all = n;
+    return before;
+}
+
+// The ring of a vertex of many faces, by a wave or by the workgroup: drops the
+// dead faces, gathers the other corners into buf (LDS or global, room for
+// 2^ceil(log2(2n))), sorts them (bitonic) and writes the runs.
+template <bool BLOCK>
+__device__ RingSums ring_by_group(const RingArgs& a, int64_t v, int32_t* buf, uint32_t* s_wave, int32_t** s_out) {
+    constexpr uint32_t G = BLOCK ? kRB : 64;
+    const uint32_t t = threadIdx.x & (G - 1), b = a.off[v], n = a.num[v];
+    const int32_t vi = (int32_t)v;
+    uint32_t left = 0;
+    for (uint32_t i0 = 0; i0 < n; i0 += G) {
+        const uint32_t i = i0 + t, f = a.adj[b + min(i, n - 1)];
+        const int32_t c0 = a.F[3 * (int64_t)f], c1 = a.F[3 * (int64_t)f + 1], c2 = a.F[3 * (int64_t)f + 2];
+        const bool alive = i < n && c0 >= 0;
+        uint32_t all;
+        const uint32_t at = left + ring_count<BLOCK>(alive, s_wave, &all) - 1;  // (the reads above come first)
+        if (alive) {
+            a.adj[b + at] = f;
+            const int2 xy = others(vi, c0, c1, c2);
+            buf[2 * at] = xy.x;
+            buf[2 * at + 1] = xy.y;
+        }
+        left += all;
+    }
+    uint32_t N = 2;
+    while (N < 2 * left) N *= 2;
+    for (uint32_t i = 2 * left + t; i < N; i += G) buf[i] = INT32_MAX;
+    if (t == 0) a.num[v] = left;
+    ring_sync<BLOCK>();
+    for (uint32_t k = 2; k <= N; k *= 2)
+        for (uint32_t j = k / 2; j > 0; j /= 2) {
+            for (uint32_t i = t; i < N / 2; i += G) {
+                const uint32_t lo = 2 * i - (i & (j - 1)), hi = lo + j;
+                const int32_t x = buf[lo], y = buf[hi];
+                if ((x > y) == ((lo & k) == 0)) {
+                    buf[lo] = y;
+                    buf[hi] = x;
+                }
+            }
+            ring_sync<BLOCK>();
+        }
+    RingSums r{0, 0, 0};
+    int32_t* out = nullptr;
+    for (int pass = 0; pass < 2; ++pass) {  // counts, then entries
+        uint32_t at = 0;
+        for (uint32_t i0 = 0; i0 < 2 * left; i0 += G) {
+            const uint32_t i = i0 + t;
+            const int32_t x = i < 2 * left ? buf[i] : INT32_MAX;
+            const bool head = i < 2 * left && (i == 0 || buf[i - 1] != x);
+            uint32_t all, run = 1;
+            const uint32_t mine = at + ring_count<BLOCK>(head, s_wave, &all) - 1;
+            at += all;
+            while (head && run < 7 && i + run < 2 * left && buf[i + run] == x) ++run;
+            if (pass == 0) {
+                uint32_t some;
+                ring_count<BLOCK>(head && x > vi, s_wave, &some);
+                r.higher += some;
+                ring_count<BLOCK>(head && run == 1, s_wave, &some);
+                if (some) r.boundary = kBoundary;
+            } else if (head) {
+                out[mine] = (x << 3) | (int32_t)run;
+            }
+        }
+        if (pass == 0) {
+            r.uniq = at;
+            if (t == 0) *s_out = ring_room(a, v, at);
+            ring_sync<BLOCK>();
+            out = *s_out;
+            if (!out) break;
+        }
+    }
+    return r;
+}
+
 // Start of a round: drops dead faces from the lists, forms the rings, sums
 // the edges per block; clears what the later launches of the round count in.
+template <bool WIDE>
 __global__ void __launch_bounds__(kRB) qem_ring_kernel(RingArgs a) {
     __shared__ uint32_t s_sum[kRB / 64];
+    __shared__ uint64_t s_big[kRB / 64];
+    __shared__ int32_t s_buf[kRingLds];
+    __shared__ uint32_t s_wave[kRB / 64], s_at;
+    __shared__ int32_t* s_out[kRB / 64];
     const int64_t v = (int64_t)blockIdx.x * kRB + threadIdx.x;
     const int t = threadIdx.x;
     if (a.cnt[kQcDoneNext]) {
@@ -277,106 +437,131 @@ __global__ void __launch_bounds__(kRB) qem_ring_kernel(RingArgs a) {
         a.cnt[kQcLive] = a.cnt[kQcLiveNext];
         a.cnt[kQcWinners] = a.cnt[kQcWinners + 1] = 0u;
     }
-    uint32_t higher = 0;
-    if (v < a.nv) {
-        a.m[v] = ~0ull;
-        const uint32_t b = a.off[v];
-        uint32_t n = a.num[v], uniq = 0, boundary = 0;
-        int32_t* ring = a.ring + (int64_t)kRingKeep * v;
-        const int32_t vi = (int32_t)v;
-        auto emit = [&](int32_t x, uint32_t faces) {
-            if (faces == 1) boundary = kBoundary;
-            if (uniq < (uint32_t)kRingKeep) ring[uniq] = (x << 3) | (int32_t)(faces < 7 ? faces : 7);
-            ++uniq;
-            if (x > vi) ++higher;
-        };
-        auto sorted = [&](auto faces) {
-            constexpr int kN = decltype(faces)::value;
-            uint32_t f[kN];
-            int32_t c[kN][3];
+    uint32_t uniq = 0, higher = 0, boundary = 0, n = 0, b = 0, keep = kRingKeep;
+    bool many = false;
+    int32_t* ring = a.ring + (int64_t)kRingKeep * v;
+    const int32_t vi = (int32_t)v;
+    auto emit = [&](int32_t x, uint32_t faces) {
+        if (faces == 1) boundary = kBoundary;
+        if (uniq < keep) ring[uniq] = (x << 3) | (int32_t)(faces < 7 ? faces : 7);
+        ++uniq;
+        if (x > vi) ++higher;
+    };
+    // a list of up to kN faces by its thread, kC loaded at once
+    auto sorted = [&](auto faces, auto at_once) {
+        constexpr int kN = decltype(faces)::value, kC = decltype(at_once)::value;
+        uint32_t left = 0;
+        int32_t e[2 * kN];
 #pragma unroll
-            for (int i = 0; i < kN; ++i) f[i] = a.adj[b + min((uint32_t)i, n - 1)];  // (no branch around a load)
+        for (int i0 = 0; i0 < kN; i0 += kC) {
+            uint32_t f[kC];
+            int32_t c[kC][3];
 #pragma unroll
-            for (int i = 0; i < kN; ++i)
+            for (int i = 0; i < kC; ++i) f[i] = a.adj[b + min((uint32_t)(i0 + i), n - 1)];  // (no branch around a load)
+#pragma unroll
+            for (int i = 0; i < kC; ++i)
 #pragma unroll
                 for (int k = 0; k < 3; ++k) c[i][k] = a.F[3 * (int64_t)f[i] + k];
-            uint32_t left = 0;
-            int32_t e[2 * kN];
 #pragma unroll
-            for (int i = 0; i < kN; ++i) {
-                const bool alive = (uint32_t)i < n && c[i][0] >= 0;
+            for (int i = 0; i < kC; ++i) {
+                const bool alive = (uint32_t)(i0 + i) < n && c[i][0] >= 0;
                 const int2 xy = others(vi, c[i][0], c[i][1], c[i][2]);
-                e[2 * i] = alive ? xy.x : INT32_MAX;
-                e[2 * i + 1] = alive ? xy.y : INT32_MAX;
+                e[2 * (i0 + i)] = alive ? xy.x : INT32_MAX;
+                e[2 * (i0 + i) + 1] = alive ? xy.y : INT32_MAX;
                 if (alive) {
-                    if (left != (uint32_t)i) a.adj[b + left] = f[i];
+                    if (left != (uint32_t)(i0 + i)) a.adj[b + left] = f[i];
                     ++left;
                 }
             }
-            if (left != n) a.num[v] = left;
-            sort_network<2 * kN>(e);
-            int32_t cur = e[0];
-            uint32_t run = 1;
+        }
+        if (left != n) a.num[v] = left;
+        sort_network<2 * kN>(e);
+        if constexpr (kN > kRingFaces) {  // the length decides on the place
+            uint32_t len = e[0] != INT32_MAX ? 1u : 0u;
 #pragma unroll
-            for (int i = 1; i < 2 * kN; ++i) {
-                if (e[i] == cur) {
-                    ++run;
-                } else {
-                    emit(cur, run);
-                    cur = e[i];
-                    run = 1;
-                }
-            }
-            if (cur != INT32_MAX) emit(cur, run);
-        };
-        if (n == 0) {
-        } else if (n <= 8) {
-            sorted(std::integral_constant<int, 8>());
-        } else if (n <= (uint32_t)kRingFaces) {
-            sorted(std::integral_constant<int, kRingFaces>());
-        } else {
-            uint32_t left = 0;
-            for (uint32_t i = 0; i < n; ++i) {
-                const uint32_t f = a.adj[b + i];
-                if (a.F[3 * (int64_t)f] < 0) continue;
-                if (left != i) a.adj[b + left] = f;
-                ++left;
-            }
-            if (left != n) a.num[v] = left;
-            n = left;
-            {
-                // counted here; the ring, if it fits its slots, in order of index
-                each_neighbour(a.F, a.adj, b, n, vi, [&](int32_t x) {
-                    ++uniq;
-                    if (x > vi) ++higher;
-                    if (shared_count(a.F, a.adj, b, n, x) == 1) boundary = kBoundary;
-                });
-                if (uniq <= (uint32_t)kRingKeep) {
-                    const uint32_t all = uniq, hi = higher;
-                    uniq = higher = 0;
-                    int32_t last = -1;
-                    while (uniq < all) {
-                        int32_t x = INT32_MAX;
-                        each_neighbour(a.F, a.adj, b, n, vi, [&](int32_t y) {
-                            if (y > last && y < x) x = y;
-                        });
-                        emit(x, shared_count(a.F, a.adj, b, n, x));
-                        last = x;
-                    }
-                    higher = hi;
-                }
+            for (int i = 1; i < 2 * kN; ++i) len += e[i] != e[i - 1] && e[i] != INT32_MAX ? 1u : 0u;
+            ring = ring_room(a, v, len);
+            keep = ring ? len : 0u;
+        }
+        int32_t cur = e[0];
+        uint32_t run = 1;
+#pragma unroll
+        for (int i = 1; i < 2 * kN; ++i) {
+            if (e[i] == cur) {
+                ++run;
+            } else {
+                emit(cur, run);
+                cur = e[i];
+                run = 1;
             }
         }
+        if (cur != INT32_MAX) emit(cur, run);
+    };
+    if (v < a.nv) {
+        a.m[v] = ~0ull;
+        b = a.off[v];
+        n = a.num[v];
+        if (n == 0) {
+        } else if (n <= 8) {
+            sorted(std::integral_constant<int, 8>(), std::integral_constant<int, 8>());
+        } else if (n <= (uint32_t)kRingFaces) {
+            sorted(std::integral_constant<int, kRingFaces>(), std::integral_constant<int, kRingFaces>());
+            many = uniq > (uint32_t)kRingKeep;  // (edges of a single face each)
+        } else if (WIDE && n <= (uint32_t)kRingWide) {
+            sorted(std::integral_constant<int, WIDE ? kRingWide : 8>(), std::integral_constant<int, 8>());
+        } else {
+            many = true;
+        }
+    }
+    const int lane = t & 63, wave = t >> 6;
+    const bool big = n > (uint32_t)kRingWave;
+    const uint64_t longer = __ballot(n > (uint32_t)kRingFaces);
+    auto take = [&](const RingSums& x) {
+        uniq = x.uniq;
+        higher = x.higher;
+        boundary = x.boundary;
+    };
+    for (uint64_t todo = __ballot(many && !big); todo != 0; todo &= todo - 1) {
+        const int src = __builtin_ctzll(todo);
+        const RingSums x = ring_by_group<false>(a, v - lane + src, s_buf + 2 * kRingWave * wave, nullptr, &s_out[wave]);
+        if (lane == src) take(x);
+        ring_sync<false>();
+    }
+    uint32_t s = big ? 0u : higher;
+    for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o, 64);
+    const uint64_t bigs = __ballot(big);
+    if (lane == 0) {
+        s_sum[wave] = s;
+        s_big[wave] = bigs;
+        if (longer) atomicAdd(&a.cnt[kQcLong], (uint32_t)__popcll(longer));
+    }
+    __syncthreads();
+    uint32_t tot = 0;
+    for (int k = 0; k < kRB / 64; ++k) {
+        tot += s_sum[k];
+        for (uint64_t todo = s_big[k]; todo != 0; todo &= todo - 1) {  // by the workgroup (none, mostly)
+            const int src = 64 * k + __builtin_ctzll(todo);
+            const int64_t w = v - t + src;
+            const uint32_t len = a.num[w];
+            int32_t* buf = s_buf;
+            if (2 * len > (uint32_t)kRingLds) {
+                uint32_t N = 2;
+                while (N < 2 * len) N *= 2;
+                if (t == 0) s_at = atomicAdd(&a.cnt[kQcGather], N);
+                __syncthreads();
+                buf = a.gather + s_at;
+            }
+            const RingSums x = ring_by_group<true>(a, w, buf, s_wave, &s_out[0]);
+            if (t == src) take(x);
+            tot += x.higher;
+            __syncthreads();
+        }
+    }
+    if (v < a.nv) {
         a.info[v] = uniq | boundary;
         a.hcnt[v] = higher;
     }
-    uint32_t s = higher;
-    for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o, 64);
-    if ((t & 63) == 0) s_sum[t >> 6] = s;
-    __syncthreads();
     if (t == 0) {
-        uint32_t tot = 0;
-        for (int k = 0; k < kRB / 64; ++k) tot += s_sum[k];
         a.part[blockIdx.x] = tot;
         if (tot) atomicAdd(&a.sup[blockIdx.x / kSupBlocks], tot);
     }
@@ -415,16 +600,20 @@ __global__ void __launch_bounds__(kRB) qem_edge_kernel(RingArgs a, uint32_t* __r
     }
     uint32_t e = base + x - h;
     if (blockIdx.x == gridDim.x - 1 && t == kRB - 1) a.cnt[kQcEdges] = e + h;
-    if (v >= a.nv) return;
-    eoff[v] = e;
-    const uint32_t m = ring_len(a.info[v]);
+    uint32_t m = 0;
+    const int32_t* ring = a.ring;
+    if (v < a.nv) {
+        eoff[v] = e;
+        m = ring_len(a.info[v]);
+        ring = m <= (uint32_t)kRingKeep ? a.ring + (int64_t)kRingKeep * v : long_ring(a.ring, a.longs, v);
+    }
+    // ascending: those above v come last
     if (m <= (uint32_t)kRingKeep) {
-        const int32_t* ring = a.ring + (int64_t)kRingKeep * v;
-        for (uint32_t j = m - h; j < m; ++j, ++e) {  // ascending: those above v come last
+        for (uint32_t j = m - h; j < m; ++j, ++e) {
             E[2 * (int64_t)e] = (int32_t)v;
             E[2 * (int64_t)e + 1] = ring[j] >> 3;
         }
-    } else {
+    } else if (!ring) {
         const uint32_t b = a.off[v], n = a.num[v];
         int32_t last = (int32_t)v;
         for (uint32_t j = 0; j < h; ++j, ++e) {
@@ -435,6 +624,17 @@ __global__ void __launch_bounds__(kRB) qem_edge_kernel(RingArgs a, uint32_t* __r
             E[2 * (int64_t)e] = (int32_t)v;
             E[2 * (int64_t)e + 1] = next;
             last = next;
+        }
+    }
+    // a longer ring by the whole wave
+    for (uint64_t todo = __ballot(m > (uint32_t)kRingKeep && ring); todo != 0; todo &= todo - 1) {
+        const int src = __builtin_ctzll(todo);
+        const int64_t w = v - lane + src;
+        const uint32_t first = __shfl(e, src, 64), n = __shfl(h, src, 64), below = __shfl(m, src, 64) - n;
+        const int32_t* r = long_ring(a.ring, a.longs, w) + below;
+        for (uint32_t j = lane; j < n; j += 64) {
+            E[2 * (int64_t)(first + j)] = (int32_t)w;
+            E[2 * (int64_t)(first + j) + 1] = r[j] >> 3;
         }
     }
 }
@@ -487,8 +687,8 @@ struct EvalArgs {
     const double* P;
     const double* Q;
     const int32_t* F;
-    const uint32_t *off, *num, *adj, *info, *eoff;
-    const int32_t* ring;
+    const uint32_t *off, *num, *adj, *info, *hcnt, *eoff;
+    const int32_t *ring, *longs;
     const int32_t* E;
     const uint32_t* cnt;
     int64_t nv;
@@ -514,8 +714,7 @@ __global__ void __launch_bounds__(kQB) qem_eval_kernel(EvalArgs a) {
         const int32_t v0 = a.E[2 * e], v1 = a.E[2 * e + 1];
         const uint32_t i0 = a.info[v0], i1 = a.info[v1];
         const uint32_t m0 = ring_len(i0), m1 = ring_len(i1);
-        const int32_t* ring0 = a.ring + (int64_t)kRingKeep * v0;
-        const int32_t* ring1 = a.ring + (int64_t)kRingKeep * v1;
+        const int32_t *ring0 = a.ring + (int64_t)kRingKeep * v0, *ring1 = a.ring + (int64_t)kRingKeep * v1;
         const bool long0 = m0 > (uint32_t)kRingKeep, long1 = m1 > (uint32_t)kRingKeep;
         // faces on the edge (seven stands for more), and common neighbours
         uint32_t c = 0, common = 0;
@@ -549,6 +748,37 @@ __global__ void __launch_bounds__(kQB) qem_eval_kernel(EvalArgs a) {
 #pragma unroll
                             for (int l = 0; l < 4; ++l) common += r0[q + k] == r1[t + l] ? 1u : 0u;
                     }
+        } else if ((!long0 || (ring0 = long_ring(a.ring, a.longs, v0))) &&
+                   (!long1 || (ring1 = long_ring(a.ring, a.longs, v1)))) {
+            // the shorter ring's entries looked up in the longer one, eight at a
+            // time; the other end's entry holds the edge's faces, and is in
+            // neither ring twice
+            const bool swap = m0 > m1;
+            const int32_t *few = swap ? ring1 : ring0, *all = swap ? ring0 : ring1, other = swap ? v0 : v1;
+            const uint32_t mf = swap ? m1 : m0, ma = swap ? m0 : m1;
+            for (uint32_t i = 0; i < mf; i += 8) {
+                int32_t x[8];
+                uint32_t at[8];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    x[q] = few[min(i + q, mf - 1)];
+                    at[q] = 0;
+                }
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    const uint32_t f = (uint32_t)(x[q] & 7);
+                    x[q] = i + q < mf ? x[q] >> 3 : -1;
+                    if (x[q] == other) c = f;
+                }
+                for (uint32_t len = ma; len > 1;) {
+                    const uint32_t half = len >> 1;
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) at[q] += (all[at[q] + half - 1] >> 3) < x[q] ? half : 0u;
+                    len -= half;
+                }
+#pragma unroll
+                for (int q = 0; q < 8; ++q) common += (all[at[q]] >> 3) == x[q] ? 1u : 0u;
+            }
         } else {
             const uint32_t b0 = a.off[v0], n0 = a.num[v0], b1 = a.off[v1], n1 = a.num[v1];
             c = shared_count(a.F, a.adj, b0, n0, v1);
@@ -699,6 +929,8 @@ __global__ void __launch_bounds__(kQB) qem_fold_kernel(EvalArgs a) {
                         for (int k = 0; k < 4; ++k)
                             r += (uint32_t)(4 * q + k) < mx && y[k] > x[h] && y[k] < vi ? 1u : 0u;
                     }
+                } else if (const int32_t* rx = long_ring(a.ring, a.longs, x[h])) {
+                    r = ring_find(rx, mx, vi) - (mx - a.hcnt[x[h]]);
                 } else {
                     each_neighbour(a.F, a.adj, a.off[x[h]], a.num[x[h]], x[h],
                                    [&](int32_t y) { r += y > x[h] && y < vi ? 1u : 0u; });
@@ -914,7 +1146,7 @@ __global__ void __launch_bounds__(kQB) qem_vmin_kernel(const int32_t* __restrict
 }
 
 struct WinArgs {
-    const int32_t *E, *F, *ring;
+    const int32_t *E, *F, *ring, *longs;
     const uint32_t *bits, *info, *off, *num, *adj;
     const uint8_t* faces;
     const uint64_t* m;
@@ -968,6 +1200,17 @@ __global__ void __launch_bounds__(kWinBlock) qem_win_kernel(WinArgs a) {
 #pragma unroll
             for (int k = 0; k < kRingKeep; ++k) least = x[k] < least ? x[k] : least;
             return least >= key;
+        }
+        if (const int32_t* r = long_ring(a.ring, a.longs, v)) {
+            for (uint32_t i = 0; i < m; i += kRingKeep) {
+                uint64_t x[kRingKeep], least = ~0ull;
+#pragma unroll
+                for (int k = 0; k < kRingKeep; ++k) x[k] = a.m[r[min(i + k, m - 1)] >> 3];
+#pragma unroll
+                for (int k = 0; k < kRingKeep; ++k) least = x[k] < least ? x[k] : least;
+                if (least < key) return false;
+            }
+            return true;
         }
         const uint32_t b = a.off[v], n = a.num[v];
         for (uint32_t i = 0; i < n; ++i)
@@ -1098,6 +1341,8 @@ __global__ void __launch_bounds__(kQB) qem_apply_kernel(ApplyArgs a) {
     if ((int64_t)nf > live - a.target)
         cut = find_cut(a.list, nw, a.bits, a.faces, (uint32_t)(live > a.target ? live - a.target : 0));
     if (blockIdx.x == 0 && threadIdx.x == 0) {
+        a.rec[kQcLong] = a.cnt[kQcLong];
+        a.cnt[kQcRing] = a.cnt[kQcGather] = a.cnt[kQcLong] = 0u;  // for the next round's rings
         a.cnt[kQcApplied] = cut.applied;
         a.cnt[kQcLiveNext] = (uint32_t)(live - cut.removed);
         const uint32_t done = cut.applied == 0 || live - cut.removed <= a.target ? 1u : 0u;
@@ -1138,48 +1383,84 @@ __global__ void __launch_bounds__(kQB) qem_apply_kernel(ApplyArgs a) {
         uint32_t base = 0;
         if (lane == 63 && x) base = atomicAdd(&a.cnt[kQcArena], x);
         base = __shfl(base, 63, 64) + x - need;
-        if (!on) continue;
-        uint32_t to = need ? base : b0;
+        const uint32_t to = need ? base : b0;
         if (need && (base + need > a.arena || base + need < base)) {  // the host keeps room for every round
             atomicOr(&a.cnt[kQcStatus], 2u);
-            continue;
+            on = false;
         }
-        for (int k = 0; k < 3; ++k) a.P[3 * (int64_t)v0 + k] = a.pl[3 * (int64_t)e + k];
-        for (int k = 0; k < 10; ++k) a.Q[10 * (int64_t)v0 + k] = a.Q[10 * (int64_t)v0 + k] + a.Q[10 * (int64_t)v1 + k];
-        // both lists eight faces at a time, their loads issued together (the
-        // faces of a batch are distinct, and only this thread changes them)
-        uint32_t w = 0;
-        auto walk = [&](uint32_t b, uint32_t n, bool second) {
-            for (uint32_t q0 = 0; q0 < n; q0 += 8) {
-                uint32_t f[8];
-                int32_t x[8][3];
+        const bool many = on && n0 + n1 > 64;
+        if (on) {
+            for (int k = 0; k < 3; ++k) a.P[3 * (int64_t)v0 + k] = a.pl[3 * (int64_t)e + k];
+            for (int k = 0; k < 10; ++k) a.Q[10 * (int64_t)v0 + k] = a.Q[10 * (int64_t)v0 + k] + a.Q[10 * (int64_t)v1 + k];
+        }
+        if (on && !many) {
+            // both lists eight faces at a time, their loads issued together (the
+            // faces of a batch are distinct, and only this thread changes them)
+            uint32_t w = 0;
+            auto walk = [&](uint32_t b, uint32_t n, bool second) {
+                for (uint32_t q0 = 0; q0 < n; q0 += 8) {
+                    uint32_t f[8];
+                    int32_t x[8][3];
 #pragma unroll
-                for (int q = 0; q < 8; ++q) f[q] = a.adj[b + min(q0 + q, n - 1)];
+                    for (int q = 0; q < 8; ++q) f[q] = a.adj[b + min(q0 + q, n - 1)];
 #pragma unroll
-                for (int q = 0; q < 8; ++q)
+                    for (int q = 0; q < 8; ++q)
 #pragma unroll
-                    for (int k = 0; k < 3; ++k) x[q][k] = a.F[3 * (int64_t)f[q] + k];
+                        for (int k = 0; k < 3; ++k) x[q][k] = a.F[3 * (int64_t)f[q] + k];
 #pragma unroll
-                for (int q = 0; q < 8; ++q) {
-                    if (q0 + q >= n || x[q][0] < 0) continue;  // past the end, or dead with v0's list
-                    if (holds(x[q], v1) && holds(x[q], v0)) {
-                        a.F[3 * (int64_t)f[q]] = -1;
-                        continue;
+                    for (int q = 0; q < 8; ++q) {
+                        if (q0 + q >= n || x[q][0] < 0) continue;  // past the end, or dead with v0's list
+                        if (holds(x[q], v1) && holds(x[q], v0)) {
+                            a.F[3 * (int64_t)f[q]] = -1;
+                            continue;
+                        }
+                        if (second) {
+#pragma unroll
+                            for (int k = 0; k < 3; ++k)
+                                if (x[q][k] == v1) a.F[3 * (int64_t)f[q] + k] = v0;
+                        }
+                        if (w < nn) a.adj[to + w++] = f[q];
                     }
-                    if (second) {
-#pragma unroll
-                        for (int k = 0; k < 3; ++k)
-                            if (x[q][k] == v1) a.F[3 * (int64_t)f[q] + k] = v0;
-                    }
-                    if (w < nn) a.adj[to + w++] = f[q];
                 }
+            };
+            walk(b0, n0, false);
+            walk(b1, n1, true);
+            a.off[v0] = to;
+            a.num[v0] = w;
+            a.num[v1] = 0u;
+        }
+        // long lists by the whole wave, 64 faces at a time (a place written is
+        // never past the faces read; a face of both lists is met in each)
+        for (uint64_t todo = __ballot(many); todo != 0; todo &= todo - 1) {
+            const int src = __builtin_ctzll(todo);
+            const int32_t u0 = __shfl(v0, src, 64), u1 = __shfl(v1, src, 64);
+            const uint32_t at = __shfl(to, src, 64), room = __shfl(nn, src, 64);
+            uint32_t w = 0;
+            for (int list = 0; list < 2; ++list) {
+                const uint32_t b = __shfl(list ? b1 : b0, src, 64), n = __shfl(list ? n1 : n0, src, 64);
+                for (uint32_t q0 = 0; q0 < n; q0 += 64) {
+                    const uint32_t f = a.adj[b + min(q0 + lane, n - 1)];
+                    const int32_t x[3] = {a.F[3 * (int64_t)f], a.F[3 * (int64_t)f + 1], a.F[3 * (int64_t)f + 2]};
+                    const bool in = q0 + lane < n && x[0] >= 0, both = in && holds(x, u0) && holds(x, u1);
+                    const uint64_t kept = __ballot(in && !both);
+                    const uint32_t o = w + (uint32_t)__popcll(kept & __lanemask_lt());
+                    if (both) a.F[3 * (int64_t)f] = -1;
+                    if (in && !both) {
+                        for (int k = 0; k < 3; ++k)
+                            if (list && x[k] == u1) a.F[3 * (int64_t)f + k] = u0;
+                        if (o < room) a.adj[at + o] = f;
+                    }
+                    w += (uint32_t)__popcll(kept);
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
             }
-        };
-        walk(b0, n0, false);
-        walk(b1, n1, true);
-        a.off[v0] = to;
-        a.num[v0] = w;
-        a.num[v1] = 0u;
+            if (lane == src) {
+                a.off[v0] = to;
+                a.num[v0] = min(w, nn);
+                a.num[v1] = 0u;
+            }
+        }
     }
 }
 
@@ -1377,8 +1658,26 @@ hipError_t build_lists(int64_t nv, const QemPtrs& p, int64_t live, hipStream_t s
     return hipGetLastError();
 }
 
-// rings and edges of the current mesh; edge count at cnt[kQcEdges]
-hipError_t build_edges(int64_t nv, const QemPtrs& p, hipStream_t s) {
+// Where the rings that have no slots go: the spare positions and quadrics or, if
+// that is more, the spare faces, which only a renumbering or the output write,
+// with no round in flight.  All rings together have at most six entries per face:
+// the former holds them from 0.23 vertices per face on, the latter those of
+// vertices whose edges have two faces each.
+bool longs_by_vertex(const QemLayout& L) { return 26 * L.nv >= 3 * L.nf; }
+int32_t* longs_at(const QemLayout& L, const QemPtrs& p) { return longs_by_vertex(L) ? (int32_t*)p.P2 : p.F2; }
+uint32_t longs_room(const QemLayout& L) {
+    return (uint32_t)std::min<int64_t>(longs_by_vertex(L) ? 26 * L.nv : 3 * L.nf, INT32_MAX);
+}
+
+// Lists of more than kRingFaces faces from which a thread sorts those of up to
+// kRingWide by itself.  Otherwise a wave does, one after the other, 2 us each; but
+// the wider network costs every launch registers (9.2 -> 12.4 us at 20,172 faces,
+// 17 -> 25 us a round of 1,306,800 -> 10,000) and few long lists lie apart.
+constexpr uint32_t kManyLong = 16;
+
+// rings and edges of the current mesh; edge count at cnt[kQcEdges].  longs: about
+// the lists of more than kRingFaces faces
+hipError_t build_edges(const QemLayout& L, int64_t nv, const QemPtrs& p, uint32_t longs, hipStream_t s) {
     const int64_t g = std::max<int64_t>((nv + kRB - 1) / kRB, 1);
     RingArgs a{};
     a.F = p.F;
@@ -1387,6 +1686,9 @@ hipError_t build_edges(int64_t nv, const QemPtrs& p, hipStream_t s) {
     a.num = p.num;
     a.adj = p.adj;
     a.ring = p.ring;
+    a.longs = longs_at(L, p);
+    a.longs_n = longs_room(L);
+    a.gather = (int32_t*)p.pl;  // placements are written after the rings
     a.info = p.info;
     a.hcnt = p.hcnt;
     a.part = p.part;
@@ -1394,14 +1696,18 @@ hipError_t build_edges(int64_t nv, const QemPtrs& p, hipStream_t s) {
     a.m = p.m;
     a.hist = p.hist;
     a.cnt = p.cnt;
-    hipLaunchKernelGGL(qem_ring_kernel, dim3(g), dim3(kRB), 0, s, a);
+    if (longs > kManyLong)
+        hipLaunchKernelGGL(qem_ring_kernel<true>, dim3(g), dim3(kRB), 0, s, a);
+    else
+        hipLaunchKernelGGL(qem_ring_kernel<false>, dim3(g), dim3(kRB), 0, s, a);
     QEM_TRY(hipGetLastError());
     hipLaunchKernelGGL(qem_edge_kernel, dim3(g), dim3(kRB), 0, s, a, p.eoff, p.E);
     return hipGetLastError();
 }
 
 // `edges`: about the mesh's edge count (the kernel strides over all of them)
-hipError_t eval_edges(int64_t nv, const QemPtrs& p, int64_t edges, int midpoint, double* cost, hipStream_t s) {
+hipError_t eval_edges(const QemLayout& L, int64_t nv, const QemPtrs& p, int64_t edges, int midpoint, double* cost,
+                      hipStream_t s) {
     EvalArgs a{};
     a.P = p.P;
     a.Q = p.Q;
@@ -1410,8 +1716,10 @@ hipError_t eval_edges(int64_t nv, const QemPtrs& p, int64_t edges, int midpoint,
     a.num = p.num;
     a.adj = p.adj;
     a.info = p.info;
+    a.hcnt = p.hcnt;
     a.eoff = p.eoff;
     a.ring = p.ring;
+    a.longs = longs_at(L, p);
     a.E = p.E;
     a.cnt = p.cnt;
     a.nv = nv;
@@ -1439,7 +1747,7 @@ hipError_t set_up(const QemLayout& L, const QemPtrs& p, const float* V, const in
     QEM_TRY(hipGetLastError());
     QEM_TRY(build_lists(L.nv, p, L.nf, s));
     hipLaunchKernelGGL(qem_quadric_kernel, dim3(blocks_for(L.nv)), dim3(kQB), 0, s, p.P, p.F, L.nv, p.off, p.num,
-                       p.adj, p.Q);
+                       p.adj, p.Q, p.cnt);
     return hipGetLastError();
 }
 
@@ -1457,12 +1765,12 @@ hipError_t compact_faces(QemPtrs& p, int64_t slots, hipStream_t s) {
 }
 
 // One round: ten launches.  `live` bounds the live faces from above.
-hipError_t enqueue_round(const QemLayout& L, const QemPtrs& p, int64_t nv, int64_t live, int64_t target, double rho,
-                         int midpoint, uint32_t* rec, hipEvent_t before_eval, hipEvent_t after_eval, hipStream_t s) {
-    QEM_TRY(build_edges(nv, p, s));
+hipError_t enqueue_round(const QemLayout& L, const QemPtrs& p, int64_t nv, int64_t live, uint32_t longs, int64_t target,
+                         double rho, int midpoint, uint32_t* rec, hipEvent_t before_eval, hipEvent_t after_eval, hipStream_t s) {
+    QEM_TRY(build_edges(L, nv, p, longs, s));
     const int64_t edges = 3 * live / 2 + 1;  // of a closed mesh; an open one has more, and the kernels stride
     if (before_eval) QEM_TRY(hipEventRecord(before_eval, s));
-    QEM_TRY(eval_edges(nv, p, edges, midpoint, nullptr, s));
+    QEM_TRY(eval_edges(L, nv, p, edges, midpoint, nullptr, s));
     if (after_eval) QEM_TRY(hipEventRecord(after_eval, s));
     const int64_t hgrid = std::min<int64_t>(blocks_for(edges), 512);
     hipLaunchKernelGGL(qem_hist_kernel<0>, dim3(hgrid), dim3(kQB), 0, s, p.bits, p.hist, p.cnt, rho);
@@ -1476,6 +1784,7 @@ hipError_t enqueue_round(const QemLayout& L, const QemPtrs& p, int64_t nv, int64
     w.E = p.E;
     w.F = p.F;
     w.ring = p.ring;
+    w.longs = longs_at(L, p);
     w.bits = p.bits;
     w.info = p.info;
     w.off = p.off;
@@ -1523,14 +1832,14 @@ hipError_t qem_edges_run(const QemLayout& L, char* ws, const float* V, const int
                          double* cost_out, double* p_out, uint32_t* status, int64_t* n_edges, hipStream_t s) {
     const QemPtrs p = ptrs(L, ws);
     QEM_TRY(set_up(L, p, V, F, s));
-    QEM_TRY(build_edges(L.nv, p, s));
+    QEM_TRY(build_edges(L, L.nv, p, ~0u, s));
     uint32_t h[kQcSlots];
     QEM_TRY(hipMemcpyAsync(h, p.cnt, sizeof h, hipMemcpyDeviceToHost, s));
     QEM_TRY(hipStreamSynchronize(s));
     *status = h[kQcStatus];
     *n_edges = h[kQcEdges];
     if (h[kQcStatus] || (int64_t)h[kQcEdges] > cap) return hipSuccess;
-    QEM_TRY(eval_edges(L.nv, p, h[kQcEdges], midpoint, cost_out, s));
+    QEM_TRY(eval_edges(L, L.nv, p, h[kQcEdges], midpoint, cost_out, s));
     hipLaunchKernelGGL(qem_edge_out_kernel, dim3(blocks_for(h[kQcEdges])), dim3(kQB), 0, s, p.E, p.faces, p.bits, p.pl,
                        p.cnt + kQcEdges, cap, E_out, valid_out, faces_out, p_out);
     QEM_TRY(hipGetLastError());
@@ -1569,6 +1878,7 @@ hipError_t qem_simplify_run(const QemLayout& L, char* ws, const float* V, const 
     int64_t slots = L.nf;    // face slots in use
     int64_t live = L.nf;     // live faces after the last round that was read back
     int64_t arena = h[kQcArena];  // list entries in use then
+    uint32_t longs = h[kQcLongIn];  // lists of more than kRingFaces faces then
     int32_t done = 0, queued = 0;  // rounds read back and rounds enqueued
     bool more = live > target && max_rounds > 0;
     // reads round `done` back
@@ -1577,6 +1887,7 @@ hipError_t qem_simplify_run(const QemLayout& L, char* ws, const float* V, const 
         const volatile uint32_t* c = h + kQcSlots * (1 + (done & 1));
         live = c[kQcLiveNext];
         arena = c[kQcArena];
+        longs = c[kQcLong];
         if (stats) {
             stats[4 * done] = c[kQcEdges];
             stats[4 * done + 1] = c[kQcValid];
@@ -1618,7 +1929,7 @@ hipError_t qem_simplify_run(const QemLayout& L, char* ws, const float* V, const 
                 std::swap(p.P, p.P2);
                 std::swap(p.Q, p.Q2);
             }
-            QEM_TRY(enqueue_round(L, p, nv, live, target, rho, midpoint, h + kQcSlots * (1 + (queued & 1)), tev[0].e,
+            QEM_TRY(enqueue_round(L, p, nv, live, longs, target, rho, midpoint, h + kQcSlots * (1 + (queued & 1)), tev[0].e,
                                   tev[1].e, s));
             QEM_TRY(hipEventRecord(ready[queued & 1].e, s));
             ++queued;
