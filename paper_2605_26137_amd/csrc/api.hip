@@ -174,6 +174,7 @@ int32_t make_plan(const Sizes* z, int n, uint32_t flags, Plan* P) {
         d.stile = L.t_stile;
         d.btile = L.t_btile;
         d.tl = L.t_tl;
+        d.join = L.n_join;
         const int64_t tex = (int64_t)z[a].res * z[a].res;
         L.t_lv += z[a].nlv;
         L.t_lf += z[a].nlf;
@@ -183,7 +184,10 @@ int32_t make_plan(const Sizes* z, int n, uint32_t flags, Plan* P) {
         L.t_tex += tex;
         L.t_stile += cdiv(z[a].nhf, kSortTile);
         L.t_btile += cdiv(3 * tex, kSortTile);
-        L.t_tl += cdiv(z[a].nhf, kBuildTile);
+        if (z[a].nhf > kBuildTile) {
+            L.t_tl += cdiv(z[a].nhf, kBuildTile);
+            ++L.n_join;
+        }
         max_hv = std::max(max_hv, z[a].nhv);
         L.max_hf = std::max(L.max_hf, (int64_t)z[a].nhf);
         for (int g = 0; g < kGridCount; ++g) {
@@ -251,13 +255,12 @@ int32_t make_plan(const Sizes* z, int n, uint32_t flags, Plan* P) {
     L.hist = take(4 * 256 * (size_t)L.t_stile);
     L.nodes_c = take(32 * (size_t)L.t_node);
     L.leaves = take(48 * (size_t)L.t_hf);
-    // lists for the levels that some asset reaches; a tile that is a whole asset
-    // leaves nothing waiting
+    // lists for the levels that some asset reaches
     int64_t rows = 0;
     const auto joins = [&](int level) {
         return level >= 1 && level <= kJoinLevels && P->gpf[(size_t)(kGJoin1 + level - 1) * (n + 1) + n] > 0;
     };
-    for (int level = 0; level == 0 || joins(level); ++level) rows += join_rows(L.t_tl, n, level);
+    for (int level = 0; level == 0 || joins(level); ++level) rows += join_rows(L.t_tl, L.n_join, level);
     L.items = take(joins(1) ? 32 * (size_t)kSpine * (size_t)rows : 0);
     L.item_cnt = take(4 * (size_t)rows);
     L.spill = take(4 * (size_t)kMaxDepth * (size_t)L.spill_lanes);

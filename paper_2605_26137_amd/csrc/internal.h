@@ -122,7 +122,8 @@ struct AssetDev {
     int64_t tex;    // texels
     int64_t stile;  // sort tiles of the BVH keys
     int64_t btile;  // sort tiles of the backward pairs (capacity 3 res^2)
-    int64_t tl;     // tiles of the tree build
+    int64_t tl;     // tiles of the tree build, of the assets of more than one (the others leave no list)
+    int64_t join;   // such assets
 };
 
 // Inputs and outputs of the backward pass, one per asset.
@@ -173,8 +174,8 @@ constexpr int kBuildTile = 1024, kJoinLog = 6, kJoin = 1 << kJoinLog, kJoinLast 
 constexpr int kJoinLevels = 4;  // 2^30 leaves: 2^20 tiles, 16384, 256, 4, 1 groups
 static_assert(kSpine >= 2 * 62, "a list holds every waiting subtree");
 // Groups of a level of an asset with n leaves (level 0: tiles) and the leaves
-// that each covers; its rows in the level's lists: asset a's start at tile_base
-// / kJoin^level + a, which keeps assets apart.
+// that each covers; its rows in the level's lists: those of the a-th asset of more
+// than one tile start at tile_base / kJoin^level + a, which keeps assets apart.
 __host__ __device__ inline int64_t join_groups(int64_t n, int level, int64_t* span_out) {
     int64_t span = kBuildTile, g = (n + span - 1) / span;
     for (int l = 0; l < level; ++l) {
@@ -318,6 +319,7 @@ struct Layout {
     // batch totals
     int n;
     int64_t max_hf;  // largest asset
+    int64_t n_join;  // assets of more than one tile of the tree build
     int64_t t_lv, t_lf, t_hv, t_hf, t_node, t_tex, t_stile, t_btile, t_tl;
     int64_t spill_lanes, scan_tmp_n;
     int max_hv_bits;  // bit length of the largest nhv (backward sort keys lie in [0, nhv])

@@ -1065,7 +1065,7 @@ __global__ __launch_bounds__(kBuildBlock) __attribute__((amdgpu_waves_per_eu(8))
     __syncthreads();
     const int64_t row = As.tl + lt;
     const uint32_t left = climb_out(Bt, S, m, nodes_all + As.node, items + row * kSpine, first);
-    if (tid == 0) counts[row] = left;
+    if (tid == 0 && n > kBuildTile) counts[row] = left;  // (a tile that is the whole asset leaves none)
 }
 
 // Joins the lists of up to kJoinLast tiles (level 1) or groups (higher levels),
@@ -1098,7 +1098,7 @@ __global__ __launch_bounds__(kBuildBlock) void build_join_kernel(JoinArgs p) {
     const int64_t lists = join_groups(n, p.level - 1, &span), groups = join_groups(n, p.level, nullptr);
     const int64_t c0 = groups == 1 ? 0 : lg * kJoin;
     const int nc = (int)min((int64_t)(groups == 1 ? kJoinLast : kJoin), lists - c0);
-    const int64_t row_in = join_row(As.tl, a, p.level - 1) + c0, row = join_row(As.tl, a, p.level) + lg;
+    const int64_t row_in = join_row(As.tl, As.join, p.level - 1) + c0, row = join_row(As.tl, As.join, p.level) + lg;
     static_assert(kJoinLast == 128, "two waves sum the list lengths");
     if (tid < 128) {
         int x = tid < nc ? (int)min(p.in_count[row_in + tid], (uint32_t)kSpine) : 0;
@@ -1272,7 +1272,7 @@ hipError_t launch_bvh_build(const BatchHost& H, hipStream_t s) {
     for (int level = 1; level <= kJoinLevels; ++level) {
         const int64_t blocks = H.blocks(kGJoin1 + level - 1);
         if (blocks == 0) break;  // every asset is whole
-        const int64_t next = row + join_rows(L.t_tl, L.n, level - 1);
+        const int64_t next = row + join_rows(L.t_tl, L.n_join, level - 1);
         JoinArgs j;
         j.B = H.dev;
         j.keys = k0;

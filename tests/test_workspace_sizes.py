@@ -1,0 +1,23 @@
+"""Workspace sizes stay within those of the previous layout (the figures here), so
+that a caller's buffer of that size is still taken."""
+import ctypes as C
+
+import pytest
+
+import paper_2605_26137_amd.bake as B
+
+
+def batch_size(specs, save):
+    A = (B.BakeAsset * len(specs))()
+    for a, (hv, hf, lv, lf, res) in zip(A, specs):
+        a.n_hi_v, a.n_hi_f, a.n_lo_v, a.n_lo_f, a.res, a.max_dist = hv, hf, lv, lf, res, 1.0
+    o, n = B.make_options(2, save), C.c_size_t()
+    assert B.lib().bake_batch_workspace_size(A, len(specs), C.byref(o), C.byref(n)) == 0
+    return n.value
+
+
+@pytest.mark.parametrize("faces,tiny,before", [(2000, 100, 1459712), (2000, 10000, 105124352), (200000, 100, 36538368),
+                                               (200000, 10000, 140207104), (200000, 65535, 721537792)])
+def test_batches_of_tiny_assets(faces, tiny, before):
+    """One asset of many tiles beside assets of a single face."""
+    assert batch_size([(faces // 2, faces, 5, 4, 1)] + [(3, 1, 5, 4, 1)] * tiny, False) <= before
