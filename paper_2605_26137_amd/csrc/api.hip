@@ -43,6 +43,11 @@ int32_t fail(int32_t code, const char* fmt, ...) {
 constexpr int64_t kMaxLanes = 256 * 2560;  // upper bound on resident traversal lanes
 constexpr int64_t kMaxCount = (int64_t)1 << 30;
 constexpr int kMaxAssets = 65536;
+// Texels of a batch past which the backward's two chains run in turn, in the sort's
+// memory one after the other: the merged sums take 4 B a texel more than the
+// terms did that an earlier layout kept, up to here the spilled stacks (256 B for
+// each of kMaxLanes lanes) make up for it.
+constexpr int64_t kBesideTexels = 48 << 20;
 
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -210,6 +215,7 @@ int32_t make_plan(const Sizes* z, int n, uint32_t flags, Plan* P) {
     L.max_hv_bits = 1;
     while (L.max_hv_bits < 32 && ((int64_t)1 << L.max_hv_bits) < max_hv) ++L.max_hv_bits;  // keys in [0, nhv)
     P->sig = sig ^ (L.save ? 0x5A5Aull : 0ull);
+    L.in_turn = L.t_tex > kBesideTexels;
 
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -244,7 +250,6 @@ int32_t make_plan(const Sizes* z, int n, uint32_t flags, Plan* P) {
     L.face_off = take(4 * (size_t)(L.t_lf + 1));
     L.scan_tmp = take(4 * (size_t)L.scan_tmp_n);
     L.facemap = take(4 * (size_t)L.t_tex);
-    L.level = take((size_t)L.t_tex);
     L.rays = take(16 * (size_t)L.t_tex);
     L.hits = L.save ? take(16 * (size_t)L.t_tex) : off;
     L.bounds_part = take(24 * (size_t)kBoundsSplit * (size_t)L.t_stile);
@@ -263,15 +268,20 @@ int32_t make_plan(const Sizes* z, int n, uint32_t flags, Plan* P) {
     for (int level = 0; level == 0 || joins(level); ++level) rows += join_rows(L.t_tl, L.n_join, level);
     L.items = take(joins(1) ? 32 * (size_t)kSpine * (size_t)rows : 0);
     L.item_cnt = take(4 * (size_t)rows);
+    L.level = take((size_t)L.t_tex);
     L.spill = take(4 * (size_t)kMaxDepth * (size_t)L.spill_lanes);
     if (L.save) {
+        // the backward's scratch begins where the forward's ends that nothing reads
+        // after it: levels of the fill and spilled stacks
+        const size_t forward = off;
+        off = L.level;
         const size_t items = 3 * (size_t)L.t_tex;
         L.bwd_ray = take(36 * (size_t)L.t_tex);
         L.bwd_term = take(12 * items);
         const size_t batches = (size_t)(L.t_tex / 64 + n);
         L.bwd_pairs = take(4 * batches);
         L.bwd_k0 = take(4 * items);
-        L.bwd_v0 = take(4 * items);
+        L.bwd_v0 = L.in_turn ? L.bwd_ray : take(4 * items);
         L.bwd_k1 = take(4 * items);
         L.bwd_v1 = take(4 * items);
         L.bwd_hist = take(4 * 256 * (size_t)L.t_btile);
@@ -283,6 +293,7 @@ int32_t make_plan(const Sizes* z, int n, uint32_t flags, Plan* P) {
         L.bwd_face2 = take(36 * (size_t)L.t_lf);
         L.bwd_sbar = take(12 * (size_t)L.t_lv);
         L.bwd_vbar = take(12 * (size_t)L.t_lv);
+        off = std::max(off, forward);
     }
     L.total = off;
     return BAKE_OK;
@@ -614,7 +625,7 @@ int32_t run_backward(Plan& P, void* workspace, uint32_t nonce, bool one_stream, 
     HIP_OR_FAIL(write_table(ws + P.L.grads, P.G.data(), sizeof(AssetGrad) * (size_t)P.L.n, s,
                             (uint32_t*)(ws + P.L.bwd_sup), bwd_sort_zero_words(P.L)));
     std::lock_guard<std::mutex> side_lock(g_side_mu);
-    Side* side = one_stream ? nullptr : side_for(s, P.L.t_hf, false);
+    Side* side = one_stream || P.L.in_turn ? nullptr : side_for(s, P.L.t_hf, false);
     if (side) {
         HIP_OR_FAIL(launch_backward(H, any_lo, any_hi, s, side->s, side->fork, side->join));
     } else {

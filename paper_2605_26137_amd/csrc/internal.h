@@ -324,6 +324,7 @@ struct Layout {
     int64_t spill_lanes, scan_tmp_n;
     int max_hv_bits;  // bit length of the largest nhv (backward sort keys lie in [0, nhv])
     bool save;
+    bool in_turn;  // the backward's low-poly chain ends before its sort begins (they share memory)
 };
 
 struct BatchHost {

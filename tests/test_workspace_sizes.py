@@ -21,3 +21,16 @@ def batch_size(specs, save):
 def test_batches_of_tiny_assets(faces, tiny, before):
     """One asset of many tiles beside assets of a single face."""
     assert batch_size([(faces // 2, faces, 5, 4, 1)] + [(3, 1, 5, 4, 1)] * tiny, False) <= before
+
+
+@pytest.mark.parametrize("sizes,before", [
+    ((3, 1, 3, 1, 1), 99840), ((2562, 5120, 42, 80, 128), 7663104), ((12, 20, 42, 80, 4096), 2748890368),
+    ((655362, 1310720, 10242, 20480, 2048), 1049435904), ((12, 20, 42, 80, 8192), 10492099840),
+    ((12, 20, 42, 80, 16384), 41464937728)])
+def test_saved_bakes(sizes, before):
+    """Few faces onto large atlases above all: what the backward keeps per texel counts."""
+    assert batch_size([sizes], True) <= before
+
+
+def test_saved_batch():
+    assert batch_size([(12, 20, 42, 80, 8192)] + [(3, 1, 5, 4, 1)] * 500, True) <= 10500167680
