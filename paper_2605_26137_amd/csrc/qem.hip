@@ -47,8 +47,8 @@
 // half of the vertices are gone (or the arena runs low) the survivors are
 // renumbered in their order, the faces compacted and the lists laid out anew:
 // the edge order, the keys and the lower-index rule do not change.  A round is
-// ten launches: ring, edges, evaluation (two), three histogram levels, vertex
-// minima, winners, collapse.  The counts of a round are read back while the
+// ten launches (seven of a small mesh): ring, edges, evaluation (two), three
+// histogram levels, vertex minima, winners, collapse.  The counts of a round are read back while the
 // next one already runs; a round enqueued after the last one finds the `done`
 // word set and does nothing.
 // Before, every round rebuilt the lists with atomics, scanned and compacted the
@@ -201,6 +201,11 @@ __device__ __forceinline__ uint32_t shared_count(const int32_t* F, const uint32_
 
 // Cost-bit histograms: digits of 11, 11 and 10 bits.
 constexpr int kHistBins = 2048, kHistWords = 2 * kHistBins + 1024;
+// Faces of an input up to which one workgroup finds the rank (qem_vmin_small_kernel):
+// past them the faces' flags and offsets, idle in the rounds, hold the histograms.
+constexpr int64_t kSmallFaces = 2560;
+constexpr int kSmallPer = (3 * (int)kSmallFaces + kQB) / kQB;  // cost bits a thread
+static_assert(8 * kSmallFaces >= 4 * kHistWords, "keep and koff hold the histograms");
 constexpr int kSupBlocks = 32;  // ring blocks whose edge counts are summed together
 
 // The rings.  Around v, the other two corners of every face name v's
@@ -277,6 +282,7 @@ struct RingArgs {
     uint32_t *part, *sup;  // edges per block and per kSupBlocks blocks
     uint64_t* m;
     uint32_t *hist, *cnt;
+    int32_t hist_n;
 };
 
 // The ring of a vertex whose ring has no slots of its own, or null where the
@@ -432,7 +438,7 @@ __global__ void __launch_bounds__(kRB) qem_ring_kernel(RingArgs a) {
         if (v == 0) a.cnt[kQcDone] = 1u;
         return;
     }
-    for (int64_t i = v; i < kHistWords; i += (int64_t)gridDim.x * kRB) a.hist[i] = 0u;
+    for (int64_t i = v; i < a.hist_n; i += (int64_t)gridDim.x * kRB) a.hist[i] = 0u;
     if (v == 0) {
         a.cnt[kQcLive] = a.cnt[kQcLiveNext];
         a.cnt[kQcWinners] = a.cnt[kQcWinners + 1] = 0u;
@@ -1127,6 +1133,13 @@ __global__ void __launch_bounds__(kQB) qem_hist_kernel(const uint32_t* __restric
 }
 
 // m(v): least key of the eligible edges at v.
+__device__ __forceinline__ void vertex_min(const int32_t* __restrict__ E, int64_t e, uint32_t x, uint64_t* __restrict__ m) {
+    const unsigned long long key = ((unsigned long long)x << 32) | (unsigned long long)(uint32_t)e;
+    const int2 v = reinterpret_cast<const int2*>(E)[e];
+    atomicMin((unsigned long long*)&m[v.x], key);
+    atomicMin((unsigned long long*)&m[v.y], key);
+}
+
 __global__ void __launch_bounds__(kQB) qem_vmin_kernel(const int32_t* __restrict__ E,
                                                        const uint32_t* __restrict__ bits,
                                                        const uint32_t* __restrict__ hist, uint32_t* __restrict__ cnt,
@@ -1138,11 +1151,47 @@ __global__ void __launch_bounds__(kQB) qem_vmin_kernel(const int32_t* __restrict
     for (int64_t e = (int64_t)blockIdx.x * kQB + threadIdx.x; e < ne; e += (int64_t)gridDim.x * kQB) {
         const uint32_t x = bits[e];
         if (x > st.prefix) continue;  // kNoKey too: it is above every cost
-        const unsigned long long key = ((unsigned long long)x << 32) | (unsigned long long)(uint32_t)e;
-        const int2 v = reinterpret_cast<const int2*>(E)[e];
-        atomicMin((unsigned long long*)&m[v.x], key);
-        atomicMin((unsigned long long*)&m[v.y], key);
+        vertex_min(E, e, x, m);
     }
+}
+
+// The three levels and the minima of a small mesh by one workgroup, which keeps the
+// edges' cost bits in registers and the histograms in LDS: no memory for them in
+// the workspace, whose 20 KB would be most of a small mesh's.
+__global__ void __launch_bounds__(kQB) qem_vmin_small_kernel(const int32_t* __restrict__ E,
+                                                             const uint32_t* __restrict__ bits,
+                                                             uint32_t* __restrict__ cnt, double rho,
+                                                             uint64_t* __restrict__ m) {
+    __shared__ uint32_t h[kHistBins];
+    if (cnt[kQcDone]) return;
+    const int64_t ne = cnt[kQcEdges];
+    uint32_t x[kSmallPer];
+#pragma unroll
+    for (int k = 0; k < kSmallPer; ++k) {
+        const int64_t e = (int64_t)k * kQB + threadIdx.x;
+        x[k] = e < ne ? bits[e] : kNoKey;
+    }
+    Select st{0u, 0u};
+    uint32_t total = 0;
+    for (int level = 0; level < 3; ++level) {
+        const int bins = level == 2 ? 1024 : kHistBins, shift = level == 0 ? 21 : (level == 1 ? 10 : 0),
+                  up = level == 1 ? 21 : 10;
+        for (int i = threadIdx.x; i < bins; i += kQB) h[i] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kSmallPer; ++k)
+            if (x[k] != kNoKey && (level == 0 || (x[k] >> up) == st.prefix)) atomicAdd(&h[(x[k] >> shift) & (bins - 1)], 1u);
+        __syncthreads();
+        st = select_digit(h, bins, st, level == 0 ? rho : -1.0, level == 0 ? &total : nullptr);
+    }
+    if (threadIdx.x == 0) {
+        cnt[kQcValid] = total;
+        cnt[kQcTau] = st.prefix;
+    }
+    if (total == 0) return;
+#pragma unroll
+    for (int k = 0; k < kSmallPer; ++k)
+        if (x[k] <= st.prefix) vertex_min(E, (int64_t)k * kQB + threadIdx.x, x[k], m);  // (kNoKey is above every cost)
 }
 
 struct WinArgs {
@@ -1569,14 +1618,13 @@ size_t qem_layout(int64_t nv, int64_t nf, QemLayout* L) {
     // append (each at most one entry per live face) and for those before them
     L->arena = std::min<int64_t>(7 * nf + 64, (int64_t)0xFFFFFFF0);
     L->cnt = take(4 * kQcSlots);
-    L->hist = take(4 * kHistWords);
     L->P = take(24 * (size_t)nv);
     L->Q = take(80 * (size_t)nv);
     L->P2 = take(24 * (size_t)nv);
     L->Q2 = take(80 * (size_t)nv);
     L->F = take(12 * (size_t)nf);
     L->F2 = take(12 * (size_t)nf);
-    L->keep = take(4 * (size_t)nf);
+    L->hist = L->keep = take(4 * (size_t)nf);
     L->koff = take(4 * (size_t)(nf + 1));
     L->num = take(4 * (size_t)(nv + 1));
     L->off = take(4 * (size_t)(nv + 1));
@@ -1695,6 +1743,7 @@ hipError_t build_edges(const QemLayout& L, int64_t nv, const QemPtrs& p, uint32_
     a.sup = p.sup;
     a.m = p.m;
     a.hist = p.hist;
+    a.hist_n = L.nf > kSmallFaces ? kHistWords : 0;
     a.cnt = p.cnt;
     if (longs > kManyLong)
         hipLaunchKernelGGL(qem_ring_kernel<true>, dim3(g), dim3(kRB), 0, s, a);
@@ -1764,7 +1813,7 @@ hipError_t compact_faces(QemPtrs& p, int64_t slots, hipStream_t s) {
     return hipSuccess;
 }
 
-// One round: ten launches.  `live` bounds the live faces from above.
+// One round: ten launches (seven of a small mesh).  `live` bounds the live faces from above.
 hipError_t enqueue_round(const QemLayout& L, const QemPtrs& p, int64_t nv, int64_t live, uint32_t longs, int64_t target,
                          double rho, int midpoint, uint32_t* rec, hipEvent_t before_eval, hipEvent_t after_eval, hipStream_t s) {
     QEM_TRY(build_edges(L, nv, p, longs, s));
@@ -1772,13 +1821,16 @@ hipError_t enqueue_round(const QemLayout& L, const QemPtrs& p, int64_t nv, int64
     if (before_eval) QEM_TRY(hipEventRecord(before_eval, s));
     QEM_TRY(eval_edges(L, nv, p, edges, midpoint, nullptr, s));
     if (after_eval) QEM_TRY(hipEventRecord(after_eval, s));
-    const int64_t hgrid = std::min<int64_t>(blocks_for(edges), 512);
-    hipLaunchKernelGGL(qem_hist_kernel<0>, dim3(hgrid), dim3(kQB), 0, s, p.bits, p.hist, p.cnt, rho);
-    hipLaunchKernelGGL(qem_hist_kernel<1>, dim3(hgrid), dim3(kQB), 0, s, p.bits, p.hist, p.cnt, rho);
-    hipLaunchKernelGGL(qem_hist_kernel<2>, dim3(hgrid), dim3(kQB), 0, s, p.bits, p.hist, p.cnt, rho);
-    QEM_TRY(hipGetLastError());
-    hipLaunchKernelGGL(qem_vmin_kernel, dim3(std::min<int64_t>(blocks_for(edges), 2048)), dim3(kQB), 0, s, p.E, p.bits,
-                       p.hist, p.cnt, p.m);
+    if (L.nf <= kSmallFaces) {
+        hipLaunchKernelGGL(qem_vmin_small_kernel, dim3(1), dim3(kQB), 0, s, p.E, p.bits, p.cnt, rho, p.m);
+    } else {
+        const int64_t hgrid = std::min<int64_t>(blocks_for(edges), 512);
+        hipLaunchKernelGGL(qem_hist_kernel<0>, dim3(hgrid), dim3(kQB), 0, s, p.bits, p.hist, p.cnt, rho);
+        hipLaunchKernelGGL(qem_hist_kernel<1>, dim3(hgrid), dim3(kQB), 0, s, p.bits, p.hist, p.cnt, rho);
+        hipLaunchKernelGGL(qem_hist_kernel<2>, dim3(hgrid), dim3(kQB), 0, s, p.bits, p.hist, p.cnt, rho);
+        hipLaunchKernelGGL(qem_vmin_kernel, dim3(std::min<int64_t>(blocks_for(edges), 2048)), dim3(kQB), 0, s, p.E,
+                           p.bits, p.hist, p.cnt, p.m);
+    }
     QEM_TRY(hipGetLastError());
     WinArgs w{};
     w.E = p.E;

@@ -34,3 +34,9 @@ def test_saved_bakes(sizes, before):
 
 def test_saved_batch():
     assert batch_size([(12, 20, 42, 80, 8192)] + [(3, 1, 5, 4, 1)] * 500, True) <= 10500167680
+
+
+@pytest.mark.parametrize("n_v,n_f,before", [(3, 1, 11776), (12, 20, 16128), (10, 1000, 193792), (502, 1000, 351488),
+                                            (10, 2560, 478720)])
+def test_simplification(n_v, n_f, before):
+    assert B.qem_workspace_size(n_v, n_f) <= before
