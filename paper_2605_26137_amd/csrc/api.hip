@@ -439,6 +439,7 @@ hipError_t tim_record(bool on, int k, hipStream_t s) {
             }
         g_tim.created = true;
     }
+    if (k == 0) g_tim.beside[g_tim.next] = false;  // the slot's last pass may have set it
     return hipEventRecord(g_tim.ev[g_tim.next][k], s);
 }
 
