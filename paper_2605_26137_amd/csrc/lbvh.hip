@@ -345,10 +345,39 @@ struct HistArgs {
     uint32_t *kout, *vout, *bt_pf;
 };
 
+// An asset's partial bounds reduced into the first of them, by one workgroup.
+__global__ __launch_bounds__(kSortBlock) void bounds_reduce_kernel(Batch Bt, float* __restrict__ part) {
+    __shared__ float s_red[kSortWaves][6];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const AssetDev& As = Bt.A[blockIdx.x];
+    const int64_t nparts = kBoundsSplit * ceil_div(As.nhf, kSortTile);
+    if (nparts == 0) return;
+    float* p = part + 6 * kBoundsSplit * As.stile;
+    float v[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
+#pragma unroll 4
+    for (int64_t i = tid; i < nparts; i += kSortBlock)
+#pragma unroll
+        for (int k = 0; k < 6; ++k) v[k] = k < 3 ? fminf(v[k], p[6 * i + k]) : fmaxf(v[k], p[6 * i + k]);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) v[k] = k < 3 ? wave_min(v[k]) : wave_max(v[k]);
+    if (lane == 0)
+#pragma unroll
+        for (int k = 0; k < 6; ++k) s_red[wave][k] = v[k];
+    __syncthreads();
+    if (wave > 0) return;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        const float x = s_red[lane & (kSortWaves - 1)][k];
+        v[k] = k < 3 ? wave_min(x) : wave_max(x);
+        if (lane == 0) p[k] = v[k];
+    }
+}
+
 // Codes of a sort tile, their indices and the first pass's digit counts.  Each
 // tile reduces its asset's partial bounds by itself (four per tile of the asset, from
-// L2), which a launch by one workgroup per asset did in 2.4 to 4.8 us, and counts
-// the digits that a histogram launch read the keys again for.
+// L2), or takes the one that bounds_reduce_kernel left (ONE), and counts the digits
+// that a histogram launch read the keys again for.
+template <bool ONE>
 __global__ __launch_bounds__(kSortBlock) __attribute__((amdgpu_waves_per_eu(8))) void code_kernel(
     Batch Bt, const float* __restrict__ part, uint32_t* __restrict__ keys, uint32_t* __restrict__ vals,
     uint32_t* __restrict__ hist, uint32_t* __restrict__ sup) {
@@ -367,7 +396,7 @@ __global__ __launch_bounds__(kSortBlock) __attribute__((amdgpu_waves_per_eu(8)))
         bool bad;
         t[r] = tri_idx(F, min(g0 + (int64_t)r * kSortBlock, T.count - 1), As.nhv, &bad);
     }
-    const int64_t nparts = kBoundsSplit * ceil_div(T.count, kSortTile);
+    const int64_t nparts = ONE ? 1 : kBoundsSplit * ceil_div(T.count, kSortTile);
     const float* p = part + 6 * kBoundsSplit * As.stile;
     float v[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
     for (int64_t i = tid; i < nparts; i += kSortBlock)
@@ -1238,6 +1267,12 @@ hipError_t launch_sort(const BatchHost& H, int which, int bits, bool* result_in_
     return hipGetLastError();
 }
 
+// Faces of an asset past which its partial bounds are reduced by a launch of their
+// own: the tiles' reading of all of them grows with the square.  code_kernel with it
+// and without, us: 33 and 29 at 2.6M, 59 and 58 at 5.2M, 126 and 150 at 10.5M, 480 and
+// 857 at 42M.
+constexpr int64_t kBoundsFaces = 6 << 20;
+
 hipError_t launch_bvh_build(const BatchHost& H, hipStream_t s) {
     const Layout& L = H.L;
     if (L.t_hf <= 0) return hipSuccess;
@@ -1255,10 +1290,12 @@ hipError_t launch_bvh_build(const BatchHost& H, hipStream_t s) {
     } else {
         hipLaunchKernelGGL(bounds_part_kernel, dim3((unsigned)(H.blocks(kGSort) * kBoundsSplit)), dim3(kBlock), 0, s,
                            H.dev, part);
-        hipLaunchKernelGGL(code_kernel, dim3((unsigned)H.blocks(kGSort)), dim3(kSortBlock), 0, s, H.dev,
-                           (const float*)part, k0, v0, (uint32_t*)(ws + L.hist), (uint32_t*)(ws + L.sup));
+        const bool one = L.max_hf > kBoundsFaces;
+        if (one) hipLaunchKernelGGL(bounds_reduce_kernel, dim3((unsigned)L.n), dim3(kSortBlock), 0, s, H.dev, part);
+        hipLaunchKernelGGL(one ? code_kernel<true> : code_kernel<false>, dim3((unsigned)H.blocks(kGSort)),
+                           dim3(kSortBlock), 0, s, H.dev, (const float*)part, k0, v0, (uint32_t*)(ws + L.hist),
+                           (uint32_t*)(ws + L.sup));
         if ((e = hipGetLastError()) != hipSuccess) return e;
-    
         bool in1 = false;
         if ((e = launch_sort(H, kSortBvh, 30, &in1, s)) != hipSuccess) return e;
     }
