@@ -17,6 +17,7 @@
 
 #include "../../include/bake.h"
 #include "internal.h"
+#include "side.h"
 
 using namespace bake;
 
@@ -489,15 +490,15 @@ constexpr int kMaxDevices = 64;
 // High-poly faces of a batch from which the second stream is used.  A forward that
 // saves for a backward is one of a training step's many launches, which wait for
 // the host below this: the fork and join cost a 256^2 step at 20,000 faces more of it
-// than the 6 us they save the device.  A bake or view maps alone: 129 -> 110 us at 5,120 faces and 128^2,
-// 115 -> 97 at 2,000, 210 -> 184 at 20,000 and 512^2, 630 -> 587 for ten views
-// at 20,480; 115 -> 119 at 1,000.
+// than the 6 us they save the device.  A bake or view maps alone: 129 -> 110 us at
+// 5,120 faces and 128^2, 115 -> 97 at 2,000, 210 -> 184 at 20,000 and 512^2, 630 -> 587
+// for ten views at 20,480; 115 -> 119 at 1,000.
 constexpr int64_t kSideMinFaces = 1 << 16, kSideMinFacesAlone = 1 << 11;
 struct Side {
     hipStream_t s = nullptr;
     hipEvent_t fork = nullptr, join = nullptr;
-    hipStream_t caller = nullptr;  // stream of the last call of few faces (compared only)
 };
+SteadyCaller g_callers[kMaxDevices];
 Side g_side[kMaxDevices];
 std::mutex g_side_mu;
 
@@ -523,29 +524,36 @@ Side* side_stream(hipStream_t s) {
     return &d;
 }
 
-// The second stream for a call on s over `faces` faces, null to do without.  Bakes
-// of few faces on several streams overlap each other better than their own two
-// chains, which would all meet in this one stream (four streams of 5,120 faces: 79
-// us a bake against 40): below kSideMinFaces a call takes it only when the call
-// before it on the device came from the same stream.  Captured work runs with its
-// graph, and timed calls of few faces keep their stages apart.
+// The second stream for a call on s over `faces` faces, null to do without; `lock`
+// then holds it while the call is queued.  Below kSideMinFaces it depends on the
+// calls before (SteadyCaller), and a call does not wait for another that is queueing
+// with it.  Captured work runs with its graph, and timed calls of few faces keep
+// their stages apart.
 // A capture that forked into the second stream holds it until it ends; a call
 // outside of that capture does without.
-Side* side_for(hipStream_t s, int64_t faces, bool alone) {
-    Side* d = faces < (alone ? kSideMinFacesAlone : kSideMinFaces) ? nullptr : side_stream(s);
-    if (!d) return nullptr;
+Side* side_for(hipStream_t s, int64_t faces, bool alone, std::unique_lock<std::mutex>* lock) {
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return nullptr;
+    const bool steady = g_callers[dev].call(s);
+    if (faces < (alone ? kSideMinFacesAlone : kSideMinFaces)) return nullptr;
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone, held = hipStreamCaptureStatusNone;
     unsigned long long id = 0, held_id = 0;
-    if (hipStreamGetCaptureInfo(s, &st, &id) != hipSuccess ||
-        hipStreamGetCaptureInfo(d->s, &held, &held_id) != hipSuccess) {
+    if (hipStreamGetCaptureInfo(s, &st, &id) != hipSuccess) {
         (void)hipGetLastError();
         return nullptr;
     }
-    if (held != hipStreamCaptureStatusNone && (st == hipStreamCaptureStatusNone || id != held_id)) return nullptr;
-    if (faces >= kSideMinFaces || st != hipStreamCaptureStatusNone) return d;
-    const bool same = d->caller == s;
-    d->caller = s;
-    return same ? d : nullptr;
+    const bool few = faces < kSideMinFaces && st == hipStreamCaptureStatusNone;
+    if (few && !steady) return nullptr;
+    if (few) *lock = std::unique_lock<std::mutex>(g_side_mu, std::try_to_lock);
+    else *lock = std::unique_lock<std::mutex>(g_side_mu);
+    Side* d = lock->owns_lock() ? side_stream(s) : nullptr;
+    if (d && hipStreamGetCaptureInfo(d->s, &held, &held_id) != hipSuccess) {
+        (void)hipGetLastError();
+        d = nullptr;
+    }
+    if (d && held != hipStreamCaptureStatusNone && (st == hipStreamCaptureStatusNone || id != held_id)) d = nullptr;
+    if (!d && lock->owns_lock()) lock->unlock();
+    return d;
 }
 
 // The forward launch sequence of a planned batch.
@@ -569,8 +577,8 @@ int32_t run_forward(Plan& P, const Opts& o, void* workspace, hipStream_t s) {
     HIP_OR_FAIL(write_table(ws + L.table, blob.data(), (L.gpf - L.table) + 4 * P.gpf.size(), s, (uint32_t*)ws,
                             (int64_t)(L.table / 4), save ? (int64_t)(L.gcnt / 4 + kGcSeal) : -1, nonce));
     const bool one_stream = (o.flags & BAKE_FLAG_ONE_STREAM) != 0;
-    std::unique_lock<std::mutex> side_lock(g_side_mu);
-    Side* side = one_stream ? nullptr : side_for(s, L.t_hf, !save && !tim);
+    std::unique_lock<std::mutex> side_lock;
+    Side* side = one_stream ? nullptr : side_for(s, L.t_hf, !save && !tim, &side_lock);
     if (side) {
         // the build, the longer chain, is enqueued first: kernels are handed
         // to the device one by one in the order they were enqueued (also on
@@ -585,7 +593,6 @@ int32_t run_forward(Plan& P, const Opts& o, void* workspace, hipStream_t s) {
         HIP_OR_FAIL(hipEventRecord(side->join, side->s));
         HIP_OR_FAIL(hipStreamWaitEvent(s, side->join, 0));
     } else {
-        side_lock.unlock();
         HIP_OR_FAIL(launch_lo_prep(H, s));
         HIP_OR_FAIL(tim_record(tim, 1, s));
         HIP_OR_FAIL(launch_raster(H, s));
@@ -625,8 +632,8 @@ int32_t run_backward(Plan& P, void* workspace, uint32_t nonce, bool one_stream, 
     // the gradient table, and the backward sort's super-tile rows zeroed
     HIP_OR_FAIL(write_table(ws + P.L.grads, P.G.data(), sizeof(AssetGrad) * (size_t)P.L.n, s,
                             (uint32_t*)(ws + P.L.bwd_sup), bwd_sort_zero_words(P.L)));
-    std::lock_guard<std::mutex> side_lock(g_side_mu);
-    Side* side = one_stream || P.L.in_turn ? nullptr : side_for(s, P.L.t_hf, false);
+    std::unique_lock<std::mutex> side_lock;
+    Side* side = one_stream || P.L.in_turn ? nullptr : side_for(s, P.L.t_hf, false, &side_lock);
     if (side) {
         HIP_OR_FAIL(launch_backward(H, any_lo, any_hi, s, side->s, side->fork, side->join));
     } else {
@@ -1144,8 +1151,8 @@ int32_t bake_view_maps(const float* V, const int32_t* F, const float* UV, int64_
                             (int64_t)(L.table / 4)));
     forget_saved(workspace);
     {
-        std::unique_lock<std::mutex> side_lock(g_side_mu);
-        Side* side = tim ? nullptr : side_for(s, L.t_hf, true);
+        std::unique_lock<std::mutex> side_lock;
+        Side* side = tim ? nullptr : side_for(s, L.t_hf, true, &side_lock);
         if (side) {
             HIP_OR_FAIL(hipEventRecord(side->fork, s));
             HIP_OR_FAIL(launch_bvh_build(H, s));
@@ -1155,7 +1162,6 @@ int32_t bake_view_maps(const float* V, const int32_t* F, const float* UV, int64_
             HIP_OR_FAIL(hipEventRecord(side->join, side->s));
             HIP_OR_FAIL(hipStreamWaitEvent(s, side->join, 0));
         } else {
-            side_lock.unlock();
             HIP_OR_FAIL(launch_lo_prep(H, s));
             HIP_OR_FAIL(launch_raster(H, s, false));
             HIP_OR_FAIL(tim_record(tim, 1, s));
