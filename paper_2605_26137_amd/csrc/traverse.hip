@@ -878,12 +878,17 @@ __device__ __forceinline__ float3 pixel_dir(float3 f, float3 r, float3 u, float 
 //   * Same results as the per-ray traversal: the triangle test is the same,
 //     operation for operation, and the winner (least distance bin, then least
 //     index) does not depend on which triangles are tested beside it or in
-//     which order.  The culls only drop what the test would reject: the
+//     which order.  The culls keep every triangle that a ray crosses: the
 //     planes lie half a pixel outside the outermost pixel centres, and every
 //     cull adds the test's edge tolerance (weights down to -2^-14 leave a
 //     triangle by at most 3 2^-14 of its extent; 2^-12 is taken) and 2^-18 of
 //     the distance, 30 times the rounding of the evaluation.  Anything not
-//     finite compares false and is kept.
+//     finite compares false and is kept.  What the test accepts beside a
+//     triangle they need not keep: the edge functions round to 2^-24 of their
+//     products, so the weights of a sliver whose projected height is less than
+//     some 2^-12 of its length err by more than 2^-12, and a ray past its tip on
+//     its very line may pass the test.  Whether such a ray meets the sliver
+//     depends on the tiles here, on the tree's boxes in the per-ray traversal.
 //   * A block whose triangles exceed the wave's LDS list is split into four;
 //     a single tile that does traces its rays through the tree one by one.
 // Bound by vector issue (94 % of the cycles): 538 vector instructions per tile
