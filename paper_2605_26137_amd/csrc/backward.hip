@@ -87,12 +87,6 @@ struct MergeLds {
     uint8_t list[192];             // slots in use
 };
 
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Which vertex a slot holds depends on the order of the insertions, the sums do
 // not: a vertex's rays are added in ascending order, those of a slot that more
 // than one lane shares (few vertices) by stride and then in a fixed tree.

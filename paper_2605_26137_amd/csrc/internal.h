@@ -259,6 +259,13 @@ __device__ __forceinline__ int block_asset(const Batch& B, int g, int64_t blk, i
     return a;
 }
 
+// A wave's writes before its later reads of them (LDS, or memory that it alone uses).
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 __device__ __forceinline__ void set_status(const Batch& B, uint32_t bits) { atomicOr(B.status, bits); }
 
 // ---------------------------------------------------------------------------

@@ -30,12 +30,6 @@ constexpr int kSortBlock = 1024;                     // sort workgroups: 16 wave
 constexpr int kSortRounds = kSortTile / kSortBlock;  // 4 keys per thread and pass
 constexpr int kSortWaves = kSortBlock / 64;
 constexpr int kBwdSortGrid = 1024;                   // two workgroups a CU, twice
-// LDS writes of a wave before its later reads
-__device__ __forceinline__ void wave_order() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 constexpr float kLeafEps = 1.0f / 16384.0f;  // edge tolerance of the hit rule (traverse.hip)
 
@@ -767,9 +761,9 @@ __global__ __launch_bounds__(kFrontBlock) void front_kernel(Batch Bt, uint32_t* 
             const uint32_t in = (uint32_t)__popcll(peers & __lanemask_lt());
             const uint32_t was = s_cnt[wave][dig];
             rank[r] = was + in;
-            wave_order();
+            wave_sync();
             if (valid && in == 0) s_cnt[wave][dig] = (uint16_t)(was + __popcll(peers));
-            wave_order();
+            wave_sync();
         }
         __syncthreads();
         uint32_t sum = 0;

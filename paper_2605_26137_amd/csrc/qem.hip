@@ -324,9 +324,7 @@ __device__ __forceinline__ void ring_sync() {
     if constexpr (BLOCK) {
         __syncthreads();
     } else {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        wave_sync();
     }
 }
 
@@ -966,9 +964,7 @@ __global__ void __launch_bounds__(kQB) qem_fold_kernel(EvalArgs a) {
             }
         }
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_sync();
     uint32_t turned = 0;  // bit j: edge j turns a face (the same in all lanes of the vertex)
     for (uint32_t f0 = 0; __ballot(f0 < n) != 0; f0 += 8) {
         const bool has = f0 + l < n;
@@ -1501,8 +1497,7 @@ __global__ void __launch_bounds__(kQB) qem_apply_kernel(ApplyArgs a) {
                     }
                     w += (uint32_t)__popcll(kept);
                 }
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                wave_sync();
             }
             if (lane == src) {
                 a.off[v0] = to;
