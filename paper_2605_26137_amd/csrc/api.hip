@@ -122,7 +122,6 @@ int64_t grid_blocks(int g, const Sizes& z) {
         case kGLoFWave: return cdiv(z.nlf, 4);
         case kGLoV: return cdiv(z.nlv, 256);
         case kGHiV: return cdiv(z.nhv, 256);
-        case kGHiF: return cdiv(z.nhf, 256);
         case kGSort: return cdiv(z.nhf, kSortTile);
         case kGTex: return cdiv(tex, 256);
         case kGTex3: return cdiv(3 * tex, 256);
