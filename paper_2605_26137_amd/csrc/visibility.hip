@@ -12,16 +12,18 @@
 // Layout: per-vertex face lists (CSR: deg -> off by a scan, adj filled with
 // per-vertex cursors), and per face a union-find parent.  Visible faces are
 // exterior as they are, and most faces are visible; a hidden face joins the
-// hidden faces it agrees with (union-find over the whole device: the larger
-// root hooks onto the smaller with a compare-and-swap, so parents only ever
-// decrease and every search ends) and notes whether it agrees with a visible
-// one.  A hidden face is then exterior when any face of its set noted that.
+// hidden faces it agrees with (union-find over the whole device: the later root
+// hooks onto the earlier, in a fixed order, with a compare-and-swap, so parents
+// only ever move forward in it and every search ends) and notes whether it agrees
+// with a visible one.  A hidden face is then exterior when any face of its set
+// noted that.
 // The sets, and with them the result, do not depend on the order of the
 // unions.  Bound by the latency of a handful of dependent gathers: lists and
 // fill of 21,425 faces 1.06 -> 0.10 ms and of 106,254 faces 4.39 -> 0.14 ms
 // (8 views of 96^2, which leave most faces to the fill), 0.37 -> 0.10 ms after
 // 512 views of 1024^2, against the breadth-first expansion in one workgroup
-// that it replaced.
+// that it replaced; a hidden fan of 20,000 faces in a shell of 20,480 0.69 -> 0.51
+// (11.0 with the tip's list walked for each face, 1.3 with roots hooked by index).
 #include "internal.h"
 
 namespace bake {
@@ -88,21 +90,16 @@ __global__ __launch_bounds__(256) void fv_fill_kernel(Batch B, const uint32_t* _
         if ((i < 1 || v[i] != v[0]) && (i < 2 || v[i] != v[1])) adj[off[v[i]] + atomicAdd(&cur[v[i]], 1u)] = (uint32_t)f;
 }
 
-// Distinct vertex indices f and g share (f's vertices in fv).
-__device__ __forceinline__ int shared_count(const int32_t fv[3], const int32_t gv[3]) {
-    int n = 0;
-    for (int i = 0; i < 3; ++i) {
-        if ((i >= 1 && fv[i] == fv[0]) || (i >= 2 && fv[i] == fv[1])) continue;
-        n += (gv[0] == fv[i] || gv[1] == fv[i] || gv[2] == fv[i]) ? 1 : 0;
-    }
-    return n;
-}
-
 // Parents are read and written by workgroups on every XCD while the unions
 // run, so both go past the XCDs' own caches (device scope).
 __device__ __forceinline__ uint32_t ld_parent(const uint32_t* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+
+// The order in which roots hook onto each other.  By index, faces numbered along a
+// strip or a fan would hook each onto the one before it, all at once, and the
+// first search through them would walk the whole chain.
+__device__ __forceinline__ bool before(uint32_t a, uint32_t b) { return a * 2654435761u < b * 2654435761u; }
 
 // Root of x, halving the path on the way (only links of non-roots are moved,
 // to an ancestor).
@@ -125,22 +122,29 @@ __global__ __launch_bounds__(256) void fill_union_kernel(Batch B, FillRun r) {
     if (!face_verts(As, f, fv)) return;
     const d3 nf_ = face_normal(As, fv);
     bool met = false;
+    // the faces across an edge are in both its ends' lists: the shorter is walked
+    // (the tip of a fan of n faces would cost each of them n)
     for (int i = 0; i < 3; ++i) {
-        if ((i >= 1 && fv[i] == fv[0]) || (i >= 2 && fv[i] == fv[1])) continue;
-        for (uint32_t e = r.off[fv[i]]; e < r.off[fv[i] + 1]; ++e) {
+        const int32_t p = fv[i], q = fv[i == 2 ? 0 : i + 1];
+        if (p == q) continue;
+        const bool swap = r.off[q + 1] - r.off[q] < r.off[p + 1] - r.off[p];
+        const int32_t at = swap ? q : p, other = swap ? p : q;
+        for (uint32_t e = r.off[at]; e < r.off[at + 1]; ++e) {
             const int64_t g = r.adj[e];
             const bool vis = r.visible[g] != 0u;
             // a pair of hidden faces is joined by the larger of the two
             if (vis ? met : g >= f) continue;
             int32_t gv[3];
-            if (!face_verts(As, g, gv) || shared_count(fv, gv) < 2 || !agree(nf_, face_normal(As, gv))) continue;
+            if (!face_verts(As, g, gv) || (gv[0] != other && gv[1] != other && gv[2] != other) ||
+                !agree(nf_, face_normal(As, gv)))
+                continue;
             if (vis) {
                 met = true;
                 continue;
             }
             uint32_t a = find_root(r.parent, (uint32_t)f), b = find_root(r.parent, (uint32_t)g);
             while (a != b) {
-                if (a < b) {
+                if (before(a, b)) {
                     const uint32_t t = a;
                     a = b;
                     b = t;
