@@ -152,8 +152,39 @@ def cpu_baseline(asset, target_s, max_dist, kind):
 VIS_WORKLOAD = ("hidden-face pass: noise-displaced shell (icosphere L5, 20,480 tris) around a hidden "
                 "sphere (1,280 tris), 512 viewpoints on a sphere of radius 2.5, 1024^2 rays each, "
                 "BVH build + first-hit rays + normal-gated flood fill")
-# camera ray setup per ray (frame, pixel direction, ray-space shear): ~60 FP32 ops
-OPS_CAM = 60
+# Camera rays by pixel blocks (tile_rays_kernel), counted from the kernel source:
+#   box test: a lane's test of one child box against its block's pyramid:
+#             6 sub, tolerance 7, four planes x (3 mul/fma + compare + or)    = 33
+#   triangle test of a ray, corners relative to the eye: the test above
+#             without its 9 subtractions                                      = 45
+# Not counted: the rays' directions and shears, and the staging of a block's
+# triangles (projection, tiles touched, order).  `achieved` is what the counted
+# tests alone come to; `valu_issue` says how busy the vector units were.
+OPS_PYRAMID, OPS_TRI_EYE = 33, 45
+VALU_FILE = os.path.join(ROOT, "profiles", "valu_tile_rays.json")
+
+
+def tile_rays_roofline(which, n_box, n_tri, trips, rays, tiles, ms):
+    achieved = (n_box * OPS_PYRAMID + n_tri * OPS_TRI_EYE) / (ms / 1e3) / 1e12
+    return {"kernel": f"tile_rays_kernel ({which})", "bound": "alu", "achieved": achieved, "peak": VALU_PEAK_TOPS,
+            "unit": "TOP/s", "frac": achieved / VALU_PEAK_TOPS, "traffic": None,
+            "pyramid_box_tests_per_tile": n_box / tiles, "tri_tests_per_ray": n_tri / rays,
+            "lane_utilisation": (n_box / 2 + n_tri) / (64 * trips) if trips else None,
+            "valu_issue": measured_issue(which, ms), "launch_ms": ms}
+
+
+def measured_issue(which, ms):
+    """Wave instructions of the vector units per CU and cycle (2.4 GHz) over a
+    launch of `ms`, from the committed counters when they belong to the
+    current sources; else None."""
+    try:
+        with open(VALU_FILE) as f:
+            d = json.load(f)
+    except (OSError, ValueError):
+        return None
+    if d.get("source_hash") != source_hash("traverse.hip", "lbvh.hip", "internal.h") or which not in d:
+        return None
+    return d[which] / (256 * 2.4e9 * ms / 1e3)
 
 
 def bench_visibility(args, B, log):
@@ -194,8 +225,6 @@ def bench_visibility(args, B, log):
     assert r.status() == 0
     log(f"[bench] visibility: {ms:.3f} ms/step, stages {stage_ms}; shell visible {vis[:n_out].mean():.4f}, "
         f"exterior {ext[:n_out].mean():.4f}, inner visible {int(vis[n_out:].sum())}")
-    ops = n_box * OPS_BOX + n_tri * OPS_TRI + rays * OPS_CAM
-    achieved = ops / (stage_ms["rays"] / 1e3) / 1e12
     out_json = {
         "metric": "camera rays/s of the hidden-face pass (512 views x 1024^2, 21,760-tri mesh)",
         "value": rays / (ms / 1e3), "unit": "rays/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
@@ -203,11 +232,7 @@ def bench_visibility(args, B, log):
         "data": "synthetic",
         "config": {"workload": VIS_WORKLOAD, "rays": rays, "tris": int(F.shape[0]), "views": n_views, "res": res},
         "stages_ms": stage_ms,
-        "roofline": {"kernel": "tile_rays_kernel (camera rays, first hit)", "bound": "alu", "achieved": achieved,
-                     "peak": VALU_PEAK_TOPS, "unit": "TOP/s", "frac": achieved / VALU_PEAK_TOPS, "traffic": None,
-                     "box_tests_per_ray": n_box / rays, "tri_tests_per_ray": n_tri / rays,
-                     "lane_utilisation": (n_box / 2 + n_tri) / (64 * trips) if trips else None,
-                     "launch_ms": stage_ms["rays"]},
+        "roofline": tile_rays_roofline("camera rays", n_box, n_tri, trips, rays, rays // 64, stage_ms["rays"]),
         "paper_context_s_per_mesh": 0.179,
     }
     if not args.no_cpu_baseline:
@@ -274,11 +299,9 @@ def bench_view_maps(args, B, log):
     tv = covered * K
     log(f"[bench] view maps: {ms:.3f} ms/step, stages {stage_ms}; {covered} covered texels, weight from some view "
         f"{(inc.reshape(K, -1).max(0) > 0).sum() / max(covered, 1):.4f}")
-    ops = n_box * OPS_BOX + n_tri * OPS_TRI + rays_depth * OPS_CAM
-    achieved = ops / (stage_ms["depth_rays"] / 1e3) / 1e12
     # the maps stage writes 12 B per texel-view (both outputs, every texel)
-    # after reading the ray list (16 B per covered texel) and the depth buffers
-    map_bytes = 12 * K * res * res + 16 * covered + 4 * rays_depth
+    # after reading the face map (4 B per texel) and the depth buffers
+    map_bytes = 12 * K * res * res + 4 * res * res + 4 * rays_depth
     out_json = {
         "metric": "covered texel-views/s of the backprojection precompute (20,480-tri mesh, 2048^2 atlas, 10 views)",
         "value": tv / (ms / 1e3), "unit": "texel-views/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
@@ -287,11 +310,8 @@ def bench_view_maps(args, B, log):
         "config": {"workload": MAP_WORKLOAD, "covered_texels": covered, "views": K, "depth_res": img,
                    "tris": int(F.shape[0])},
         "stages_ms": stage_ms,
-        "roofline": {"kernel": "tile_rays_kernel (depth rays, first hit)", "bound": "alu", "achieved": achieved,
-                     "peak": VALU_PEAK_TOPS, "unit": "TOP/s", "frac": achieved / VALU_PEAK_TOPS, "traffic": None,
-                     "box_tests_per_ray": n_box / rays_depth, "tri_tests_per_ray": n_tri / rays_depth,
-                     "lane_utilisation": (n_box / 2 + n_tri) / (64 * trips) if trips else None,
-                     "launch_ms": stage_ms["depth_rays"]},
+        "roofline": tile_rays_roofline("depth rays", n_box, n_tri, trips, rays_depth, rays_depth // 64,
+                                       stage_ms["depth_rays"]),
         "maps_stage": {"bound": "hbm", "bytes": map_bytes, "ms": stage_ms["maps"],
                        "achieved_GBps": map_bytes / (stage_ms["maps"] / 1e3) / 1e9, "peak_GBps": 8000.0},
         "paper_context_s": 1.455,
@@ -362,7 +382,7 @@ def bench_simplify(args, B, log):
                    ", rho 0.25 (cheapest quarter of the allowed edges eligible per round)",
                    "faces_in": int(F.shape[0]), "faces_out": int(r.F.shape[0]), "rounds": int(r.rounds),
                    "edges_evaluated": int(r.stats[:, 0].sum())},
-        "roofline": {"kernel": "qem_eval_kernel (per-edge collapse evaluation, summed over the rounds of a run)",
+        "roofline": {"kernel": "qem_eval_kernel, qem_fold_kernel (per-edge collapse evaluation, summed over the rounds of a run)",
                      "bound": "hbm", "achieved": achieved, "peak": 8000.0, "unit": "GB/s",
                      "frac": achieved / 8000.0, "traffic": measured_qem_traffic(),
                      "algorithmic_bytes_per_run": algo, "eval_ms_per_run": eval_ms,
