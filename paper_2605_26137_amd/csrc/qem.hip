@@ -53,7 +53,7 @@
 // word set and does nothing.
 // Before, every round rebuilt the lists with atomics, scanned and compacted the
 // faces (27 launches) and waited for its counts: 1,306,800 -> 10,000 faces
-// 33.2 -> 16.2 ms, 20,172 -> 1,000 faces 6.3 -> 3.3 ms.
+// 32.5 -> 15.9 ms, 20,172 -> 1,000 faces 6.3 -> 3.4 ms.
 #pragma clang fp contract(off)
 
 #include <algorithm>
