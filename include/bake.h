@@ -443,8 +443,8 @@ int32_t bake_autotune(const bake_asset *assets, int32_t n_assets, const bake_opt
  * original placement the section compares against).  Workspace >=
  * bake_qem_workspace_size bytes, 256-byte aligned, overwritten; nothing is
  * allocated.  Unlike the bake, these calls are BLOCKING: the number of rounds
- * depends on the data, so the stream is synchronised once per round to read
- * its counts; they return once the outputs are written.
+ * depends on the data, so the host waits for each round's counts (with the
+ * next round already queued); they return once the outputs are written.
  * Errors: BAKE_E_INVALID_ARG (NULL pointers, negative counts, target_faces < 4,
  * rho outside (0, 1], max_rounds < 0), BAKE_E_UNSUPPORTED (n_v or n_f >= 2^28),
  * BAKE_E_INDEX (a face with an index outside [0, n_v) or a repeated vertex),
